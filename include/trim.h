@@ -171,7 +171,15 @@ typedef struct {
 #define TRIM_SCHED_REVERSE 1
 #define TRIM_SCHED_JITTER 2
 
-/* Per-call statistics, written to device memory. */
+/*
+ * Per-call statistics, written to device memory.  One-sided AC-6 of a graph of
+ * up to 65,536 vertices (and 2^21 edges; implicit graphs up to 2^15 vertices)
+ * runs in one workgroup, where a vertex finds its support removed by watching
+ * its status instead of by a walk over the support's list.  The successor
+ * checks are the same; a vertex that finds its support removed counts in
+ * `visited`, one that finds another in `joins`, `phases` counts the passes over
+ * the vertices, and nothing goes through queues.
+ */
 typedef struct {
     uint64_t edges_total;  /* sum of worker_edges: successor checks (AC-6, AC-3) or
                               reverse edges traversed (AC-4) */

@@ -1269,6 +1269,8 @@ hipError_t ac6_run(View g, int n, const Work& w, const LaunchCfg& lc, uint32_t* 
 
 hipError_t ac6_csr(const trim_csr_t& g, const Work& w, const LaunchCfg& lc, uint32_t* bitmap,
                    uint64_t* worker_edges, trim_stats_t* stats, const uint32_t* preset) {
+    if (ac6_small_ok(g.n, g.m, lc.rounds))
+        return ac6_small_csr(g, w, lc, bitmap, worker_edges, stats, preset);
     ExplicitView v{g.row_off, g.col};
     return ac6_run(v, g.n, w, lc, bitmap, worker_edges, stats, nullptr, nullptr, 0, preset);
 }
@@ -1276,6 +1278,8 @@ hipError_t ac6_csr(const trim_csr_t& g, const Work& w, const LaunchCfg& lc, uint
 hipError_t ac6_implicit(const trim_implicit_t& g, const Work& w, const LaunchCfg& lc,
                         uint32_t* bitmap, uint64_t* worker_edges, trim_stats_t* stats) {
     const int n = 1 << g.log2n;
+    if (ac6_small_implicit_ok(g.log2n, lc.rounds))
+        return ac6_small_implicit(g, w, lc, bitmap, worker_edges, stats);
     ImplicitView v{g.seed, g.zero_thr, g.deg_table, (uint32_t)(n - 1)};
     return ac6_run(v, n, w, lc, bitmap, worker_edges, stats);
 }

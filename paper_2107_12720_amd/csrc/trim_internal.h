@@ -181,6 +181,14 @@ hipError_t ac6_csr(const trim_csr_t& g, const Work& w, const LaunchCfg& lc, uint
                    uint64_t* worker_edges, trim_stats_t* stats, const uint32_t* preset = nullptr);
 hipError_t ac6_implicit(const trim_implicit_t& g, const Work& w, const LaunchCfg& lc,
                         uint32_t* bitmap, uint64_t* worker_edges, trim_stats_t* stats);
+// Small graphs by one workgroup (small.hip), when these say so.
+constexpr long long kSmallMaxM = 1 << 21;
+bool ac6_small_ok(long long n, long long m, int rounds);
+bool ac6_small_implicit_ok(int log2n, int rounds);
+hipError_t ac6_small_csr(const trim_csr_t& g, const Work& w, const LaunchCfg& lc, uint32_t* bitmap,
+                         uint64_t* worker_edges, trim_stats_t* stats, const uint32_t* preset);
+hipError_t ac6_small_implicit(const trim_implicit_t& g, const Work& w, const LaunchCfg& lc,
+                              uint32_t* bitmap, uint64_t* worker_edges, trim_stats_t* stats);
 // trim_batch with one workgroup per graph (batch.hip); the default.
 hipError_t ac6_batch_owned(int G, const int64_t* vbase, const int32_t* row_off,
                            const int32_t* col, int64_t total_n, const int64_t* bitmap_base,

@@ -92,7 +92,8 @@ typedef struct {
 
 /* Launch options; zero-initialise for defaults. */
 typedef struct {
-    int32_t block;      /* threads per workgroup of the sweep kernels (64..1024, 0 = 256) */
+    int32_t block;      /* threads per workgroup of the sweep kernels (64..1024, 0 = 256; 1024
+                           where trim_batch trims a graph with one workgroup) */
     int32_t workers;    /* persistent workgroups P (0 = sized from occupancy) */
     int32_t chunk;      /* AC-6: vertices claimed per dynamic work chunk of the first
                            sweep (Section 8, schedule(dynamic, s)); rounded up to a

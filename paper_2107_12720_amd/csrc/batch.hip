@@ -1,11 +1,19 @@
 // batch.hip -- trim_batch: AC-6 over a batch of independent graphs, each graph
-// owned by one workgroup (Section 6.2, Alg. par-ac-6-trim, run per graph).
+// owned by one workgroup or one wavefront (Section 6.2, Alg. par-ac-6-trim, run
+// per graph).
 //
 // The graphs of a batch share nothing, so a graph needs no device-wide
-// coordination at all: one workgroup claims it, trims it start to finish and
-// claims the next.  Claims go largest first (graphs ordered by the size class
-// of n + m), so the biggest graphs start early and the small ones fill in
-// behind them.  Within a graph the AC-6 steps are those of the one-graph path:
+// coordination at all: whoever claims it trims it start to finish and claims
+// the next.  Claims go largest first (graphs ordered by the size class of
+// n + m), so the biggest graphs start early and the small ones fill in behind
+// them.  Graphs of up to kWatchMaxN vertices are trimmed as watch.h describes,
+// their statuses in LDS: by a wavefront when they are small, else by the whole
+// workgroup, with the supports in LDS, too, up to 65,536 vertices.  What bounds
+// the batch of 4,096 graphs (5.9 * 10^7 vertices) is the latency of a pass's
+// resumed scans in the middling graphs; with supporting sets as lists in
+// device memory it was the dependent accesses of every phase.
+//
+// Larger graphs are trimmed over lists (own_graph):
 //   init   both list heads kDead (no successor) or kEmpty;
 //   sweep  DoPost for every vertex: the first successor that is not a sink
 //          becomes its support (join: exchange into the support's S_more or
@@ -23,10 +31,13 @@
 // Items and list counters live in LDS; heads, records and the two phase lists
 // of a graph live in device memory at the graph's own vertex range, where the
 // workgroup's L2 keeps them for the graph's lifetime.
+#include <climits>
+
 #include "trim_internal.h"
 #include "trim_device.h"
 #include "trim_stats.h"
 #include "ac6_support.h"
+#include "watch.h"
 
 namespace trim {
 namespace {
@@ -46,33 +57,46 @@ enum : uint32_t { kOwnClose = 0, kOwnRescan = 1 };
 constexpr int kOwnMaxBlock = 1024;
 constexpr int kOwnStage = 128;    // items staged per wavefront before one reservation
 constexpr int kOwnUnroll = 2;     // sweep vertices per lane in flight
-// Graphs with n + m >= 2^15 are trimmed by a whole workgroup, smaller ones by
-// one wavefront each (size_key is the count of leading zeros of n + m).
-constexpr int kBigKey = 31 - 15;
+// LDS of a workgroup, shared out as the graph at hand needs it; a sixteenth for
+// each wavefront with a graph of its own, which holds the statuses, supports
+// and list of kOwnWaveN vertices.
+constexpr int kOwnLds = 155648;
+constexpr int kOwnWaveLds = kOwnLds / 16;
+constexpr int kOwnWaveN = 4096;
+static_assert(kOwnWaveN / 8 + kOwnWaveN * 2 + kWatchList * 2 <= kOwnWaveLds &&
+              kWatchList * 2 >= kOwnWaveN / 8, "a wavefront's share");
+static_assert(kWatchLdsN / 8 + kWatchLdsN * 2 + 16 * kWatchList * 2 <= kOwnLds,
+              "statuses, supports and lists of the largest graph with supports in LDS");
+static_assert(kWatchMaxN / 8 + 16 * kWatchList * 4 <= kOwnLds &&
+              kOwnLds - kWatchMaxN / 8 >= kWatchMaxN / 8, "the same without the supports");
+// A wavefront trims a graph alone up to this n + m (and kOwnWaveN vertices).
+constexpr uint32_t kOwnWaveSize = 1u << 16;
+constexpr int kKeys = 2 * 33;
 
-// Size class of graph gi: larger graphs get smaller keys.
+// Size class of graph gi: larger graphs get smaller keys, those that a
+// wavefront trims alone 33 and more.
 __device__ __forceinline__ int size_key(const int64_t* vbase, const int* row_off, int gi) {
     const int64_t v0 = vbase[gi], v1 = vbase[gi + 1];
     const uint32_t size = (uint32_t)(row_off[v1] - row_off[v0]) + (uint32_t)(v1 - v0);
-    return __clz(size > 0 ? size : 1u);
+    return __clz(size > 0 ? size : 1u) + (v1 - v0 <= kOwnWaveN && size < kOwnWaveSize ? 33 : 0);
 }
 
 // One block: order[] = graph indices by descending size class; zeroes the
 // control words and the statistics.
 __global__ void batch_order(const int64_t* vbase, const int* row_off, int G, int* order, int* ctr,
                             trim_stats_t* stats) {
-    __shared__ int hist[33];
+    __shared__ int hist[kKeys];
     for (int i = threadIdx.x; i < kCtrInts; i += blockDim.x) ctr[i] = 0;
     if (stats && threadIdx.x < (int)(sizeof(trim_stats_t) / 8))
         ((uint64_t*)stats)[threadIdx.x] = 0;
-    if (threadIdx.x < 33) hist[threadIdx.x] = 0;
+    if (threadIdx.x < kKeys) hist[threadIdx.x] = 0;
     __syncthreads();
     for (int gi = threadIdx.x; gi < G; gi += blockDim.x)
         atomicAdd(&hist[size_key(vbase, row_off, gi)], 1);
     __syncthreads();
     if (threadIdx.x == 0) {
         int run = 0;
-        for (int k = 0; k < 33; ++k) {
+        for (int k = 0; k < kKeys; ++k) {
             const int c = hist[k];
             hist[k] = run;
             run += c;
@@ -88,102 +112,71 @@ __global__ void batch_order(const int64_t* vbase, const int* row_off, int G, int
 // the workgroup's L2 serves them.
 constexpr int kWG = __HIP_MEMORY_SCOPE_WORKGROUP;
 
-// Dead-vertex bitmap of an owned graph in LDS: a bit per local vertex, set for
-// sinks at init and by every close.  Successor checks read it instead of a
-// list head in device memory (a random cache line per check); a join still
-// reads the head and its CAS fails on kDead, so a bit that is not yet set
-// only costs that attempt.  kBitsWords words per workgroup: the whole array
-// for a workgroup's graph, an equal share per wavefront for wavefront graphs.
-constexpr int kBitsWords = 16384;   // 64 KiB: 2^19 vertices
-
 // Shared state of an owned-graph kernel's workgroup (LDS).
 struct OwnShared {
-    uint32_t bits[kBitsWords];
-    uint32_t stage[kOwnMaxBlock / kWave][kOwnStage];   // per-wavefront item staging
-    int stage_n[kOwnMaxBlock / kWave];
-    int cnt[kOwnMaxBlock / kWave];   // items in the list being built: [0] for the
-                                     // workgroup, [wave] for a wavefront's own graph
+    __attribute__((aligned(16))) unsigned char raw[kOwnLds];
+    int cnt[kOwnMaxBlock / kWave][kWatchCnt];   // per wavefront with a graph of its own; [0] for
+                                                // the workgroup's
     int claim;
     uint64_t red[16];
 };
+// own_graph's use of raw: per-wavefront item staging, the length of the list
+// being built.
+struct OwnStage {
+    uint32_t item[kOwnMaxBlock / kWave][kOwnStage];
+    int n[kOwnMaxBlock / kWave];
+    int cnt;
+};
+static_assert(sizeof(OwnStage) <= kOwnLds, "");
 
 // Per-thread running totals of the kernel.
 struct OwnTotals {
-    uint64_t edges = 0, sweep = 0, closes = 0, joins = 0, visited = 0, live = 0, deg = 0;
+    WatchTotals w;
     int max_phases = 0;
 };
 
-__device__ __forceinline__ bool bit_dead(const uint32_t* bits, int l) {
-    return (bits[l >> 5] >> (l & 31)) & 1u;
-}
+// The batch's arrays.
+struct OwnArgs {
+    const int64_t* vbase;
+    const int* row_off;
+    const int* col;
+    const int64_t* bitmap_base;
+    int total_m;
+    int* head;
+    uint64_t* rec;
+    uint32_t* l0;
+    uint32_t* l1;
+    uint32_t* bitmaps;
+    uint64_t* graph_edges;
+    int sched;
+};
 
-// Resume DoPost of u (global id) from position p0, skipping targets whose
-// bit is set; as resume() otherwise (the same checks are counted).
-__device__ __forceinline__ bool resume_own(const OwnedView& g, int u, int p0, int* head,
-                                           uint64_t* rec, uint64_t& edges, int sched,
-                                           const uint32_t* bits) {
-    constexpr int kScan = 8;
-    const int e = g.end(u);
-    for (int p = p0; p < e; p += kScan) {
-        int w[kScan];
-#pragma unroll
-        for (int j = 0; j < kScan; ++j)
-            if (p + j < e) w[j] = g.col[p + j];
-#pragma unroll
-        for (int j = 0; j < kScan; ++j) {
-            if (p + j >= e) break;
-            if (bit_dead(bits, w[j])) continue;
-            int* slot = head + 2 * (g.vb + w[j]) + (p + j + 1 == e);
-            int hj = ld_s<kWG>(slot);
-            while (hj != kDead) {
-                st_s<kWG>(rec + u, pack_rec(hj, p + j));
-                complete_mem();
-                if (sched & TRIM_SCHED_JITTER) jitter_nap(((uint64_t)u << 24) ^ (p + j));
-                if (cas_s<kWG>(slot, hj, u)) {
-                    edges += (uint64_t)(p + j - p0 + 1);
-                    return true;
-                }
-            }
-        }
-    }
-    edges += (uint64_t)(e - p0);
-    return false;
-}
-
-// Trim graph gi with a group of threads: the whole workgroup (kWaveGroup
-// false; phases end at workgroup barriers) or one wavefront (true; its lanes
-// run in lock step, so a phase ends with the wavefront's own memory wait).
-// `bits`: the group's LDS bitmap, or nullptr if the graph does not fit it
-// (then statuses are read from the heads).
-template <bool kWaveGroup>
-__device__ void own_graph(int gi, const int64_t* vbase, const int* row_off, const int* col,
-                          const int64_t* bitmap_base, int* head, uint64_t* rec, uint32_t* l0,
-                          uint32_t* l1, uint32_t* bitmaps, uint64_t* graph_edges, int sched,
-                          OwnShared& sh, OwnTotals& t, uint32_t* bits) {
+// Trim graph gi over lists, by the whole workgroup; phases end at workgroup
+// barriers.
+__device__ void own_graph(const OwnArgs& a, int gi, OwnShared& sh, OwnTotals& t) {
+    OwnStage& st = *reinterpret_cast<OwnStage*>(sh.raw);
     const int wv = threadIdx.x / kWave;
-    const int rank = kWaveGroup ? lane_id() : (int)threadIdx.x;
-    const int size = kWaveGroup ? kWave : (int)blockDim.x;
-    int* cnt = kWaveGroup ? &sh.cnt[wv] : &sh.cnt[0];
+    const int rank = threadIdx.x, size = blockDim.x;
+    const int *row_off = a.row_off, *col = a.col;
+    int* head = a.head;
+    uint64_t* rec = a.rec;
     auto sync = [&]() {
         complete_mem();
-        if (kWaveGroup)
-            __builtin_amdgcn_wave_barrier();
-        else
-            __syncthreads();
+        __syncthreads();
     };
-    const int vb = (int)vbase[gi], ve = (int)vbase[gi + 1];
+    const int vb = (int)a.vbase[gi], ve = (int)a.vbase[gi + 1];
     const OwnedView g{row_off, col, vb};
     uint32_t* out = nullptr;
     // move this wavefront's staged items to the list being built (wave-uniform)
     auto flush = [&]() {
-        const int k = sh.stage_n[wv];
+        const int k = st.n[wv];
         if (k == 0) return;
         int base = 0;
-        if (lane_id() == 0) base = atomicAdd(cnt, k);
+        if (lane_id() == 0) base = atomicAdd(&st.cnt, k);
         base = __shfl(base, 0);
-        for (int i = lane_id(); i < k; i += kWave) out[base + i] = sh.stage[wv][i];
+        for (int i = lane_id(); i < k; i += kWave) out[base + i] = st.item[wv][i];
         __builtin_amdgcn_wave_barrier();
-        if (lane_id() == 0) sh.stage_n[wv] = 0;
+        if (lane_id() == 0) st.n[wv] = 0;
         __builtin_amdgcn_wave_barrier();
     };
     // stage this lane's item, if any (wave-uniform)
@@ -191,34 +184,28 @@ __device__ void own_graph(int gi, const int64_t* vbase, const int* row_off, cons
         const uint64_t mk = ballot(it != kNone);
         const int k = popc(mk);
         if (k == 0) return;
-        if (sh.stage_n[wv] + k > kOwnStage) flush();
-        const int base = sh.stage_n[wv];
-        if (it != kNone) sh.stage[wv][base + popc(mk & lanes_below())] = it;
+        if (st.n[wv] + k > kOwnStage) flush();
+        const int base = st.n[wv];
+        if (it != kNone) st.item[wv][base + popc(mk & lanes_below())] = it;
         __builtin_amdgcn_wave_barrier();
-        if (lane_id() == 0) sh.stage_n[wv] = base + k;
+        if (lane_id() == 0) st.n[wv] = base + k;
         __builtin_amdgcn_wave_barrier();
     };
     uint64_t edges = 0;
-    // init: the heads of the graph's vertices and the sinks' bits (one word of
-    // the bitmap per 32 local vertices: a lane ORs its vertex's bit in)
-    if (bits)
-        for (int i = rank; i < ((ve - vb + 31) >> 5); i += size) bits[i] = 0;
-    sync();
+    if (lane_id() == 0) st.n[wv] = 0;
+    if (rank == 0) st.cnt = 0;
+    // init: the heads of the graph's vertices
     for (int v = vb + rank; v < ve; v += size) {
         const int b = row_off[v], e = row_off[v + 1];
         const int h = b == e ? kDead : kEmpty;
         reinterpret_cast<int2*>(head)[v] = make_int2(h, h);
-        if (bits && b == e) atomicOr(&bits[(v - vb) >> 5], 1u << ((v - vb) & 31));
-        t.deg += (uint64_t)(e - b);
+        t.w.deg += (uint64_t)(e - b);
     }
-    if (rank == 0) *cnt = 0;
     sync();
     // sweep: only sinks are removed while it runs, so a target is live iff it
     // has a successor
-    auto sink = [&](int w) {
-        return bits ? bit_dead(bits, w - vb) : row_off[w] == row_off[w + 1];
-    };
-    out = l0 + vb;
+    auto sink = [&](int w) { return row_off[w] == row_off[w + 1]; };
+    out = a.l0 + vb;
     for (int base = vb; base < ve; base += kOwnUnroll * size) {
         int v[kOwnUnroll], b[kOwnUnroll], e[kOwnUnroll], p[kOwnUnroll], w[kOwnUnroll];
         bool ok[kOwnUnroll];
@@ -248,7 +235,8 @@ __device__ void own_graph(int gi, const int64_t* vbase, const int* row_off, cons
 #pragma unroll
         for (int k = 0; k < kOwnUnroll; ++k) {
             if (ok[k]) {
-                if (sched & TRIM_SCHED_JITTER) jitter_nap(((uint64_t)gi << 32) ^ (uint32_t)v[k]);
+                if (a.sched & TRIM_SCHED_JITTER)
+                    jitter_nap(((uint64_t)gi << 32) ^ (uint32_t)v[k]);
                 old[k] = xchg_s<kWG>(head + 2 * w[k] + (p[k] + 1 == e[k]), v[k]);
             }
         }
@@ -266,15 +254,15 @@ __device__ void own_graph(int gi, const int64_t* vbase, const int* row_off, cons
         }
     }
     flush();
-    t.sweep += edges;
+    t.w.sweep += edges;
     sync();
     // phases
-    uint32_t* in = l0 + vb;
-    out = l1 + vb;
+    uint32_t* in = a.l0 + vb;
+    out = a.l1 + vb;
     int ph = 0;
-    for (int n_in = *cnt; n_in > 0; n_in = *cnt) {
+    for (int n_in = st.cnt; n_in > 0; n_in = st.cnt) {
         sync();   // every thread has read the count
-        if (rank == 0) *cnt = 0;
+        if (rank == 0) st.cnt = 0;
         sync();
         ++ph;
         for (int base = 0; base < n_in; base += size) {
@@ -286,13 +274,9 @@ __device__ void own_graph(int gi, const int64_t* vbase, const int* row_off, cons
                 if (item_kind(it) == kOwnRescan) {
                     // x is in no list until it joins again: its record is stable
                     const uint64_t r = ld_s<kWG>(rec + x);
-                    if (sched & TRIM_SCHED_JITTER) jitter_nap((uint64_t)x);
-                    const bool joined =
-                        bits ? resume_own(g, x, rec_cursor(r) + 1, head, rec, edges, sched, bits)
-                             : resume<OwnedView, kWG>(g, x, rec_cursor(r) + 1, head, rec, edges,
-                                                      sched);
-                    if (joined)
-                        t.joins += 1;
+                    if (a.sched & TRIM_SCHED_JITTER) jitter_nap((uint64_t)x);
+                    if (resume<OwnedView, kWG>(g, x, rec_cursor(r) + 1, head, rec, edges, a.sched))
+                        t.w.joins += 1;
                     else
                         cx = x;
                 } else {
@@ -300,10 +284,9 @@ __device__ void own_graph(int gi, const int64_t* vbase, const int* row_off, cons
                 }
             }
             if (cx >= 0) {
-                if (sched & TRIM_SCHED_JITTER) jitter_nap((uint64_t)cx << 8);
+                if (a.sched & TRIM_SCHED_JITTER) jitter_nap((uint64_t)cx << 8);
                 const int2 ab = xchg2_s<kWG>(head + 2 * cx, kDead, kDead);
-                if (bits) atomicOr(&bits[(cx - vb) >> 5], 1u << ((cx - vb) & 31));
-                t.closes += 1;
+                t.w.closes += 1;
                 walk_more = ab.x;
                 walk_last = ab.y;
             }
@@ -321,7 +304,7 @@ __device__ void own_graph(int gi, const int64_t* vbase, const int* row_off, cons
                     e = make_item(kOwnRescan, walk_more);
                     walk_more = nx;
                 }
-                t.visited += e != kNone;
+                t.w.visited += e != kNone;
                 emit(e);
             }
         }
@@ -333,50 +316,75 @@ __device__ void own_graph(int gi, const int64_t* vbase, const int* row_off, cons
     }
     t.max_phases = ph > t.max_phases ? ph : t.max_phases;
     // pack: the graph's bitmap words (bits past its n stay zero)
-    const int64_t wb = bitmap_base[gi], we = bitmap_base[gi + 1];
+    const int64_t wb = a.bitmap_base[gi], we = a.bitmap_base[gi + 1];
     const int nwords = (ve - vb + 31) >> 5;
-    if (bits) {
-        for (int i = rank; i < nwords; i += size) {
-            const int nb = ve - vb - 32 * i;   // vertices in this word
-            const uint32_t valid = nb >= 32 ? 0xFFFFFFFFu : ((1u << nb) - 1u);
-            const uint32_t word = ~bits[i] & valid;
-            bitmaps[wb + i] = word;
-            t.live += (uint64_t)__popc(word);
-        }
-    } else {
-        const int gwave = kWaveGroup ? 0 : wv, gwaves = size / kWave;
-        for (int base = vb + gwave * kWave; base < ve; base += gwaves * kWave) {
-            const int v = base + lane_id();
-            const uint64_t m = ballot(v < ve && ld_s<kWG>(head + 2 * v) != kDead);
-            if (lane_id() == 0) {
-                const int wi = (base - vb) >> 5;
-                bitmaps[wb + wi] = (uint32_t)m;
-                if (wi + 1 < nwords) bitmaps[wb + wi + 1] = (uint32_t)(m >> 32);
-                t.live += (uint64_t)popc(m);
-            }
+    for (int base = vb + wv * kWave; base < ve; base += size) {
+        const int v = base + lane_id();
+        const uint64_t m = ballot(v < ve && ld_s<kWG>(head + 2 * v) != kDead);
+        if (lane_id() == 0) {
+            const int wi = (base - vb) >> 5;
+            a.bitmaps[wb + wi] = (uint32_t)m;
+            if (wi + 1 < nwords) a.bitmaps[wb + wi + 1] = (uint32_t)(m >> 32);
+            t.w.live += (uint32_t)popc(m);
         }
     }
-    for (int64_t wi = wb + nwords + rank; wi < we; wi += size) bitmaps[wi] = 0;
-    edges = kWaveGroup ? wave_sum(edges) : block_sum(edges, sh.red);
+    for (int64_t wi = wb + nwords + rank; wi < we; wi += size) a.bitmaps[wi] = 0;
+    edges = block_sum(edges, sh.red);
     if (rank == 0) {
-        graph_edges[gi] = edges;
-        t.edges += edges;
+        a.graph_edges[gi] = edges;
+        t.w.edges += edges;
     }
     sync();
 }
 
-// Graphs are claimed in order (largest first).  A workgroup trims the graphs
-// of at least kBigKey's size class together; once it claims a smaller one,
-// its wavefronts go their own ways: each trims that graph or graphs it claims
-// itself, so up to one small graph per wavefront is in flight.
-__global__ __launch_bounds__(kOwnMaxBlock) void ac6_owned(
-    const int64_t* vbase, const int* row_off, const int* col, const int64_t* bitmap_base, int G,
-    const int* order, int* head, uint64_t* rec, uint32_t* l0, uint32_t* l1, int* ctr,
-    uint32_t* bitmaps, uint64_t* graph_edges, uint64_t* wedges, uint64_t* part, int big_key,
-    int sched) {
+// Trim graph gi as watch.h describes: by the workgroup, or (kWaveGroup) by this
+// wavefront.  `raw` holds its statuses, then its supports when they are 16-bit,
+// then its list.  The supports (32-bit) and positions in device memory lie in
+// the graph's own part of the head and record arrays.
+template <class Sup, class Item, bool kWaveGroup>
+__device__ __forceinline__ void own_watch(const OwnArgs& a, int gi, unsigned char* raw, int max_n,
+                                          int* cnt, OwnShared& sh, OwnTotals& t) {
+    const int vb = (int)a.vbase[gi], n = (int)a.vbase[gi + 1] - vb;
+    const CachedView g{a.row_off + vb, a.col, a.total_m};
+    uint32_t* bits = reinterpret_cast<uint32_t*>(raw);
+    unsigned char* rest = raw + max_n / 8;
+    Sup* sup;
+    if constexpr (sizeof(Sup) == 2) {
+        sup = reinterpret_cast<uint16_t*>(rest);
+        rest += max_n * 2;
+    } else {
+        sup = a.head + 2 * (long long)vb;
+    }
+    const uint64_t before = t.w.edges;
+    Watch<CachedView, Sup, int, Item, kWaveGroup> w{
+        g, n, bits, sup, reinterpret_cast<int*>(a.rec + vb), reinterpret_cast<Item*>(rest), cnt,
+        a.sched, t.w};
+    w.init(nullptr);
+    w.template sweep<false>((int*)nullptr);
+    w.passes(INT_MAX);
+    t.max_phases = w.steps > t.max_phases ? w.steps : t.max_phases;
+    const int64_t wb = a.bitmap_base[gi], we = a.bitmap_base[gi + 1];
+    const int nwords = (n + 31) >> 5;
+    for (int64_t i = w.rank(); i < we - wb; i += w.size()) {
+        const uint32_t word = i < nwords ? ~bits[i] : 0;   // the positions past n are set in bits
+        a.bitmaps[wb + i] = word;
+        t.w.live += (uint32_t)__popc(word);
+    }
+    const uint64_t edges = kWaveGroup ? wave_sum(t.w.edges - before)
+                                      : block_sum(t.w.edges - before, sh.red);
+    if (w.rank() == 0) a.graph_edges[gi] = edges;
+    w.sync();
+}
+
+// Graphs are claimed in order (largest first).  A workgroup trims the larger
+// ones together; once it claims one that a wavefront trims alone (all the
+// later ones are), its wavefronts go their own ways: each trims that graph or
+// graphs it claims itself, so up to one small graph per wavefront is in flight.
+__global__ __launch_bounds__(kOwnMaxBlock) void ac6_owned(OwnArgs a, int G, const int* order,
+                                                          int* ctr, uint64_t* wedges,
+                                                          uint64_t* part) {
     __shared__ OwnShared sh;
-    const int wv = threadIdx.x / kWave;
-    if (lane_id() == 0) sh.stage_n[wv] = 0;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     OwnTotals t;
     int first = -1;   // the small graph that ended the workgroup's part, if any
     for (;;) {
@@ -386,18 +394,20 @@ __global__ __launch_bounds__(kOwnMaxBlock) void ac6_owned(
         __syncthreads();
         if (claim >= G) break;
         const int gi = order[claim];
-        if (size_key(vbase, row_off, gi) > big_key) {
+        if (size_key(a.vbase, a.row_off, gi) >= 33) {
             first = gi;
             break;
         }
-        const int ng = (int)(vbase[gi + 1] - vbase[gi]);
-        own_graph<false>(gi, vbase, row_off, col, bitmap_base, head, rec, l0, l1, bitmaps,
-                         graph_edges, sched, sh, t,
-                         ((ng + 31) >> 5) <= kBitsWords ? sh.bits : nullptr);
+        const int64_t n = a.vbase[gi + 1] - a.vbase[gi];
+        if (n <= kWatchLdsN)
+            own_watch<uint16_t, uint16_t, false>(a, gi, sh.raw, kWatchLdsN, sh.cnt[0], sh, t);
+        else if (n <= kWatchMaxN)
+            own_watch<int, uint32_t, false>(a, gi, sh.raw, kWatchMaxN, sh.cnt[0], sh, t);
+        else
+            own_graph(a, gi, sh, t);
     }
     // wavefront part: wavefront 0 takes the graph that ended the workgroup part
-    const int wave_words = kBitsWords / (blockDim.x / kWave);
-    __syncthreads();   // the workgroup's bitmap is free for the wavefronts
+    __syncthreads();   // the workgroup's LDS is free for the wavefronts
     for (int gi = (wv == 0) ? first : -1;;) {
         if (gi < 0) {
             int c = 0;
@@ -406,20 +416,18 @@ __global__ __launch_bounds__(kOwnMaxBlock) void ac6_owned(
             if (c >= G) break;
             gi = order[c];
         }
-        const int ng = (int)(vbase[gi + 1] - vbase[gi]);
-        own_graph<true>(gi, vbase, row_off, col, bitmap_base, head, rec, l0, l1, bitmaps,
-                        graph_edges, sched, sh, t,
-                        ((ng + 31) >> 5) <= wave_words ? sh.bits + wv * wave_words : nullptr);
+        own_watch<uint16_t, uint16_t, true>(a, gi, sh.raw + wv * kOwnWaveLds, kOwnWaveN,
+                                            sh.cnt[wv], sh, t);
         gi = -1;
     }
     __syncthreads();
-    const uint64_t sweep = block_sum(t.sweep, sh.red);
-    const uint64_t closes = block_sum(t.closes, sh.red);
-    const uint64_t joins = block_sum(t.joins, sh.red);
-    const uint64_t visited = block_sum(t.visited, sh.red);
-    const uint64_t live = block_sum(t.live, sh.red);
-    const uint64_t deg = block_sum(t.deg, sh.red);
-    const uint64_t edges = block_sum(t.edges, sh.red);
+    const uint64_t sweep = block_sum(t.w.sweep, sh.red);
+    const uint64_t closes = block_sum(t.w.closes, sh.red);
+    const uint64_t joins = block_sum(t.w.joins, sh.red);
+    const uint64_t visited = block_sum(t.w.visited, sh.red);
+    const uint64_t live = block_sum(t.w.live, sh.red);
+    const uint64_t deg = block_sum(t.w.deg, sh.red);
+    const uint64_t edges = block_sum(t.w.edges, sh.red);
     if (threadIdx.x == 0) {
         wedges[blockIdx.x] = edges;
         part[kPartSweep * kPartStride + blockIdx.x] = sweep;
@@ -444,9 +452,9 @@ int ac6_owned_blocks_per_cu(int block) {
 }
 
 hipError_t ac6_batch_owned(int G, const int64_t* vbase, const int32_t* row_off,
-                           const int32_t* col, int64_t total_n, const int64_t* bitmap_base,
-                           const Work& w, const LaunchCfg& lc, uint32_t* bitmaps,
-                           uint64_t* graph_edges, trim_stats_t* stats) {
+                           const int32_t* col, int64_t total_n, int64_t total_m,
+                           const int64_t* bitmap_base, const Work& w, const LaunchCfg& lc,
+                           uint32_t* bitmaps, uint64_t* graph_edges, trim_stats_t* stats) {
     const int B = lc.block;
     int W = lc.workers > 0 ? lc.workers : lc.cus * ac6_owned_blocks_per_cu(B);
     if (W > kPartStride) W = kPartStride;
@@ -457,9 +465,10 @@ hipError_t ac6_batch_owned(int G, const int64_t* vbase, const int32_t* row_off,
     }
     {
         Timed t(lc, "ac6_owned");
-        hipLaunchKernelGGL(ac6_owned, dim3(W), dim3(B), 0, lc.stream, vbase, row_off, col,
-                           bitmap_base, G, w.d, w.a, w.b, w.e, w.e + w.cap, w.ctr, bitmaps,
-                           graph_edges, w.wedges, w.part, kBigKey, lc.schedule);
+        const OwnArgs a{vbase, row_off, col,     bitmap_base, (int)total_m, w.a,
+                        w.b,   w.e,     w.e + w.cap, bitmaps,  graph_edges,  lc.schedule};
+        hipLaunchKernelGGL(ac6_owned, dim3(W), dim3(B), 0, lc.stream, a, G, w.d, w.ctr, w.wedges,
+                           w.part);
     }
     if (stats) {
         Timed t(lc, "finalize");

@@ -696,14 +696,17 @@ int trim_batch(trim_ctx* c, int32_t G, const int64_t* vbase, const int32_t* row_
     trim::LaunchCfg lc = launch_cfg(c, TRIM_AC6, o, stream);
     if (o && o->graph) lc.timer = nullptr;   // no event records inside a captured graph
     const bool uni = o && (o->flags & TRIM_FLAG_BATCH_UNION);
-    // the owned path sizes its grid from its own occupancy unless workers are given
+    // the owned path sizes its grid from its own occupancy unless workers are
+    // given, and takes the largest workgroups unless a size is: one holds all
+    // of a compute unit's LDS whatever its size
     trim::LaunchCfg lco = lc;
+    lco.block = (o && o->block) ? o->block : 1024;
     lco.workers = (o && o->workers > 0) ? o->workers : 0;
     auto run = [&]() {
         return uni ? trim::ac6_batch(G, vbase, row_off, col, total_n, bitmap_base, c->w, lc,
                                      live_bitmaps, graph_edges, stats)
-                   : trim::ac6_batch_owned(G, vbase, row_off, col, total_n, bitmap_base, c->w,
-                                           lco, live_bitmaps, graph_edges, stats);
+                   : trim::ac6_batch_owned(G, vbase, row_off, col, total_n, total_m, bitmap_base,
+                                           c->w, lco, live_bitmaps, graph_edges, stats);
     };
     if (!(o && o->graph)) {
         e = run();

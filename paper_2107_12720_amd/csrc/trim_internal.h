@@ -191,9 +191,9 @@ hipError_t ac6_small_implicit(const trim_implicit_t& g, const Work& w, const Lau
                               uint32_t* bitmap, uint64_t* worker_edges, trim_stats_t* stats);
 // trim_batch with one workgroup per graph (batch.hip); the default.
 hipError_t ac6_batch_owned(int G, const int64_t* vbase, const int32_t* row_off,
-                           const int32_t* col, int64_t total_n, const int64_t* bitmap_base,
-                           const Work& w, const LaunchCfg& lc, uint32_t* bitmaps,
-                           uint64_t* graph_edges, trim_stats_t* stats);
+                           const int32_t* col, int64_t total_n, int64_t total_m,
+                           const int64_t* bitmap_base, const Work& w, const LaunchCfg& lc,
+                           uint32_t* bitmaps, uint64_t* graph_edges, trim_stats_t* stats);
 int ac6_owned_blocks_per_cu(int block);
 hipError_t ac6_batch(int G, const int64_t* vbase, const int32_t* row_off, const int32_t* col,
                      int64_t total_n, const int64_t* bitmap_base, const Work& w,

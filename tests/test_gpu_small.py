@@ -83,3 +83,32 @@ def test_preset_and_schedules(ctx, schedule):
     assert np.array_equal(res.bitmap_numpy()[:(g.n + 31) // 32], oracle.bitmap(r.live))
     assert int(res.worker_edges.sum()) == c.T6 == res.stats_dict()["edges_total"]
     say(f"  preset, schedule {schedule}: {res.stats_dict()}")
+
+
+@pytest.mark.parametrize("block,workers", [(0, 0), (64, 3), (256, 40)])
+def test_batch_sizes(ctx, block, workers):
+    """A batch with graphs at the edges of its size classes: one wavefront's,
+    a workgroup's with and without supports in LDS, and lists."""
+    import torch
+    import paper_2107_12720_amd as T
+    sizes = [4095, 4096, 4097, 65535, 65536, 65537, (1 << 19) - 1, 1 << 19, (1 << 19) + 1, 1, 64, 65]
+    graphs = [gg.core_tail(n, seed=n, min_sink=1) if n > 100 else gg.uniform(n, 2 * n, seed=n)
+              for n in sizes]
+    graphs += [doubled_path(700), dying_hub(30000, 20000), last_link_cycles(4000),
+               gg.uniform(3000, 70000, seed=1)]   # few vertices, too many edges for a wavefront
+    vbase = np.cumsum([0] + [g.n for g in graphs]).astype(np.int64)
+    ebase = np.cumsum([0] + [g.m for g in graphs]).astype(np.int64)
+    row_off = np.concatenate([g.row_off[:-1].astype(np.int64) + e
+                              for g, e in zip(graphs, ebase)] + [ebase[-1:]]).astype(np.int32)
+    col = np.concatenate([g.col for g in graphs]).astype(np.int32)
+    words = np.cumsum([0] + [(g.n + 31) // 32 for g in graphs]).astype(np.int64)
+    live = torch.full((int(words[-1]),), -1, dtype=torch.int32, device="cuda")
+    res = ctx.trim_batch(T.to_device(vbase), T.to_device(row_off), T.to_device(col),
+                         T.to_device(words), int(vbase[-1]), int(ebase[-1]), live_bitmaps=live,
+                         opts=T.make_opts(block=block, workers=workers))
+    torch.cuda.synchronize()
+    got, edges = res.bitmap_numpy(), res.worker_edges.cpu().numpy()
+    for i, g in enumerate(graphs):
+        r = oracle.peel(g)
+        assert np.array_equal(got[words[i]:words[i + 1]], oracle.bitmap(r.live)), (i, g.n)
+        assert edges[i] == oracle.counts(g, r).T6, (i, g.n)

@@ -125,6 +125,7 @@ struct Weights {
     float b3;
 };
 
+// p: the parameters, in LDS or device memory.
 __device__ __forceinline__ void load_weights(const short* p, Weights& W) {
     const int l = lane_id();
     for (int t = 0; t < 4; ++t) W.w1[t] = p[kW1 + (l & 31) * 8 + 4 * (l >> 5) + t];
@@ -175,25 +176,45 @@ __device__ __forceinline__ long long sample_edge(const long long* ids, uint64_t 
     return (long long)(mix64(seed ^ ((uint64_t)step << 40) ^ (uint64_t)idx) % (uint64_t)m);
 }
 
-// Per-wave LDS tiles for the weight gradients (32 hidden x 32 edges, padded).
+// Per-wave LDS tiles for the weight gradients, BF16 bits: hidden units x edges
+// (x: features x edges).  A lane's eight operands of an MFMA over the edges lie
+// side by side; the row length keeps them 16-byte aligned.
+constexpr int kTileRow = 40;
 struct Tiles {
-    float a[32][33];
-    float b[32][33];
-    float x[32][8];
+    short a[32][kTileRow];
+    short b[32][kTileRow];
+    short x[8][kTileRow];
 };
+constexpr int kGradParams = 1378;   // the gradients and the loss
+constexpr int kGradWaves = 8;
 
 // Gradients of the mean loss over `count` sampled edges, accumulated into
 // grad[0..1376]; grad[1377] accumulates the loss.  Edges are ids[k] when ids
 // is given, else hashed samples.  Loss weight 1/count per edge, 0 when the
 // source is not live.
-__global__ __launch_bounds__(256) void mlp_grad(Graph g, const uint32_t* live, const short* p,
-                                                const long long* ids, long long count,
-                                                uint64_t seed, int step, float* grad) {
-    __shared__ Tiles tiles[4];
-    Tiles& T = tiles[threadIdx.x / kWave];
+//
+// A step's few thousand edges leave a wavefront one tile, so the sums are the
+// larger part of the work: with every wavefront adding its 1,378 to the same
+// words, 16,384 edges took 94 us, most of it the queue at those words.  The
+// wavefronts of a workgroup add up in LDS first, and the largest workgroup the
+// registers allow (eight wavefronts of 256 registers) leaves 64 adds a word.
+__global__ __launch_bounds__(kGradWaves * kWave) void mlp_grad(Graph g, const uint32_t* live,
+                                                               const short* p,
+                                                               const long long* ids,
+                                                               long long count, uint64_t seed,
+                                                               int step, float* grad) {
+    union Lds {
+        Tiles tiles[kGradWaves];
+        float sums[kGradWaves][kGradParams];
+    };
+    __shared__ __attribute__((aligned(16))) Lds lds;
+    __shared__ short wts[kGradParams];
+    Tiles& T = lds.tiles[threadIdx.x / kWave];
     const int l = lane_id(), half = l >> 5, col = l & 31;
+    for (int i = threadIdx.x; i < kGradParams - 1; i += blockDim.x) wts[i] = p[i];
+    __syncthreads();
     Weights W;
-    load_weights(p, W);
+    load_weights(wts, W);
     const f32x16 zero = {};
     f32x16 gw2 = zero, gw1 = zero;
     float gb1[16] = {}, gb2[16] = {}, gw3[16] = {};
@@ -202,6 +223,11 @@ __global__ __launch_bounds__(256) void mlp_grad(Graph g, const uint32_t* live, c
     const long long tiles_total = (count + 31) / 32;
     const long long wave = (blockIdx.x * (long long)blockDim.x + threadIdx.x) / kWave;
     const long long nwaves = (gridDim.x * (long long)blockDim.x) / kWave;
+    auto fence = [&]() {   // the wavefront's tiles, written by some lanes, read by others
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    };
+    auto row8 = [](const short* q) { return *reinterpret_cast<const bf16x8*>(q); };
     for (long long t = wave; t < tiles_total; t += nwaves) {
         const long long k = t * 32 + col;
         float f[4] = {0.f, 0.f, 0.f, 0.f};
@@ -236,44 +262,34 @@ __global__ __launch_bounds__(256) void mlp_grad(Graph g, const uint32_t* live, c
         dh1 = mfma16(cat(W.w2t[2], W.w2t[3]), cat(dz2b[2], dz2b[3]), dh1);
         // stage dZ2, H1 and X for the weight gradients (contraction over edges)
         for (int r = 0; r < 16; ++r) {
-            T.a[drow(r, l)][col] = bf2f(dz2b[r >> 2][r & 3]);
-            T.b[drow(r, l)][col] = bf2f(h1[r >> 2][r & 3]);
+            T.a[drow(r, l)][col] = dz2b[r >> 2][r & 3];
+            T.b[drow(r, l)][col] = h1[r >> 2][r & 3];
         }
-        for (int t4 = 0; t4 < 4; ++t4) T.x[col][4 * half + t4] = rbf(f[t4]);
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        for (int j = 0; j < 2; ++j) {
-            bf16x8 a, b;
-            for (int t8 = 0; t8 < 8; ++t8) {
-                const int e = 16 * j + 8 * half + t8;
-                a[t8] = f2bf(T.a[col][e]);
-                b[t8] = f2bf(T.b[col][e]);
-            }
-            gw2 = mfma16(a, b, gw2);   // dW2[h_out][h_in] += sum_e dZ2[h_out][e] H1[h_in][e]
-        }
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        for (int t4 = 0; t4 < 4; ++t4) T.x[4 * half + t4][col] = f2bf(f[t4]);
+        fence();
+        // dW2[h_out][h_in] += sum_e dZ2[h_out][e] H1[h_in][e]
+        for (int j = 0; j < 2; ++j)
+            gw2 = mfma16(row8(&T.a[col][16 * j + 8 * half]), row8(&T.b[col][16 * j + 8 * half]), gw2);
+        fence();
         // dZ1 = dH1 * relu'(Z1)
         for (int r = 0; r < 16; ++r) {
             const float dz1 = z1[r] > 0.f ? dh1[r] : 0.f;
             gb1[r] += dz1;
-            T.a[drow(r, l)][col] = rbf(dz1);
+            T.a[drow(r, l)][col] = f2bf(dz1);
         }
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        fence();
+        // dW1[h][f] += sum_e dZ1[h][e] X[e][f]
         for (int j = 0; j < 2; ++j) {
-            bf16x8 a, b;
-            for (int t8 = 0; t8 < 8; ++t8) {
-                const int e = 16 * j + 8 * half + t8;
-                a[t8] = f2bf(T.a[col][e]);
-                b[t8] = col < 8 ? f2bf(T.x[e][col]) : (short)0;
-            }
-            gw1 = mfma16(a, b, gw1);   // dW1[h][f] += sum_e dZ1[h][e] X[e][f]
+            const bf16x8 none = {};
+            const bf16x8 x = row8(&T.x[col & 7][16 * j + 8 * half]);
+            gw1 = mfma16(row8(&T.a[col][16 * j + 8 * half]), col < 8 ? x : none, gw1);
         }
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        fence();
     }
-    // reduce over the 32 edges of each half, then one atomic per parameter
+    // sums over the 32 edges of each half, then over the wavefronts, then one
+    // atomic per parameter
+    __syncthreads();   // the tiles are free
+    float* mine = lds.sums[threadIdx.x / kWave];
     for (int r = 0; r < 16; ++r) {
         float a = gb1[r], b = gb2[r], c = gw3[r];
         for (int off = 16; off > 0; off >>= 1) {
@@ -282,20 +298,26 @@ __global__ __launch_bounds__(256) void mlp_grad(Graph g, const uint32_t* live, c
             c += __shfl_xor(c, off);
         }
         if (col == 0) {
-            atomicAdd(grad + kB1 + drow(r, l), a);
-            atomicAdd(grad + kB2 + drow(r, l), b);
-            atomicAdd(grad + kW3 + drow(r, l), c);
+            mine[kB1 + drow(r, l)] = a;
+            mine[kB2 + drow(r, l)] = b;
+            mine[kW3 + drow(r, l)] = c;
         }
-        atomicAdd(grad + kW2 + drow(r, l) * 32 + col, gw2[r]);
-        if (col < 8) atomicAdd(grad + kW1 + drow(r, l) * 8 + col, gw1[r]);
+        mine[kW2 + drow(r, l) * 32 + col] = gw2[r];
+        if (col < 8) mine[kW1 + drow(r, l) * 8 + col] = gw1[r];
     }
     for (int off = 16; off > 0; off >>= 1) {
         gb3 += __shfl_xor(gb3, off);
         loss += __shfl_xor(loss, off);
     }
     if (l == 0) {
-        atomicAdd(grad + kB3, gb3);
-        atomicAdd(grad + 1377, loss);
+        mine[kB3] = gb3;
+        mine[kGradParams - 1] = loss;
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < kGradParams; i += blockDim.x) {
+        float sum = 0.f;
+        for (int w = 0; w < kGradWaves; ++w) sum += lds.sums[w][i];
+        atomicAdd(grad + i, sum);
     }
 }
 
@@ -357,9 +379,9 @@ hipError_t mlp_grad_launch(const int* row_off, const int* col, const int* indeg,
                            const long long* ids, long long count, uint64_t seed, int step,
                            float* grad, int cus, hipStream_t s) {
     Graph g{row_off, col, indeg, src, m, nullptr};
-    const int blocks = grid_for((count + 31) / 32, 4, cus * 8);
-    hipLaunchKernelGGL(mlp_grad, dim3(blocks), dim3(256), 0, s, g, live, pbf, ids, count, seed,
-                       step, grad);
+    const int blocks = grid_for((count + 31) / 32, kGradWaves, cus);
+    hipLaunchKernelGGL(mlp_grad, dim3(blocks), dim3(kGradWaves * kWave), 0, s, g, live, pbf, ids,
+                       count, seed, step, grad);
     return hipGetLastError();
 }
 

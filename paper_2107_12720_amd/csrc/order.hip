@@ -163,8 +163,222 @@ __global__ __launch_bounds__(kTileT) void tile_sources(const int* row_off, int n
     }
 }
 
-// In-degrees.  Device-wide atomics on one array are slow and serialise on
-// hubs; instead every XCD counts into its own copy with workgroup-scope
+// In-degrees by binning.  Counting at random places of an array of n counters
+// is bound by those places: with one copy of the counters per XCD (below) R-MAT
+// 24 took 13.7 ms, 51 ns for every thousand of its 2.7 * 10^8 edges, since the
+// copies do not fit the L2s and hub counters queue.  Instead the edges' targets
+// are dealt into bins of kBinV vertices, 16 bits each, and every bin is counted
+// in LDS: 4 + 4 + 2 + 2 bytes of streamed traffic per edge.
+//   bin_count    targets per (bin, slice of the edge array);
+//   bin_scan     their exclusive scan over the slices, and the bins' totals;
+//   bin_scatter  each slice's targets, a tile at a time sorted by bin in LDS, to
+//                the slice's places in the bins;
+//   bin_degrees  the counters of a bin, or of a part of a large one, in LDS.
+// Up to kBinV vertices bin_degrees reads the targets themselves.
+constexpr int kBinLog = 15;
+constexpr int kBinV = 1 << kBinLog;
+constexpr int kBinMax = 1024;               // bins
+constexpr int kBinThreads = 512;
+constexpr int kBinPer = 32;                 // targets per thread of a tile
+constexpr int kBinTile = kBinThreads * kBinPer;
+constexpr int kBinSlices = 1024;
+constexpr long long kBinChunk = 1 << 21;    // targets one workgroup counts at most
+constexpr long long kBinMinM = 1 << 16;     // fewer edges: the plain counters
+constexpr int kBinCountThreads = 1024;
+static_assert(kBinMax == 2 * kBinThreads && kBinMax == kBinCountThreads, "scans of the bins' totals");
+
+struct Bins {
+    uint16_t* id;   // m targets, by bin
+    int* cnt;       // bins x slices
+    int* tot;       // targets of each bin
+    int bins, slices;
+    int tiles;      // per slice
+};
+
+// Exclusive scan over the workgroup; *total gets the sum.  wtot: one word per
+// wavefront.
+__device__ __forceinline__ int block_scan(int x, int* wtot, int* total) {
+    int inc = x;
+    for (int d = 1; d < kWave; d <<= 1) {
+        const int y = __shfl_up(inc, d);
+        if (lane_id() >= d) inc += y;
+    }
+    const int wv = threadIdx.x / kWave, nw = blockDim.x / kWave;
+    __syncthreads();
+    if (lane_id() == kWave - 1) wtot[wv] = inc;
+    __syncthreads();
+    int pre = 0, sum = 0;
+    for (int w = 0; w < nw; ++w) {
+        if (w < wv) pre += wtot[w];
+        sum += wtot[w];
+    }
+    *total = sum;
+    return pre + inc - x;
+}
+
+__global__ __launch_bounds__(kBinThreads) void bin_count(const int* col, long long m, Bins b) {
+    __shared__ int hist[kBinMax];
+    for (int i = threadIdx.x; i < b.bins; i += kBinThreads) hist[i] = 0;
+    __syncthreads();
+    const long long t0 = (long long)blockIdx.x * b.tiles * kBinTile;
+    const long long t1 = min(m, t0 + (long long)b.tiles * kBinTile);
+    constexpr int U = 8;
+    for (long long e0 = t0 + threadIdx.x; e0 < t1; e0 += U * kBinThreads) {
+        int w[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const long long e = e0 + (long long)k * kBinThreads;
+            w[k] = e < t1 ? __builtin_nontemporal_load(col + e) : -1;
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+            if (w[k] >= 0) atomicAdd(&hist[w[k] >> kBinLog], 1);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < b.bins; i += kBinThreads)
+        b.cnt[(long long)i * b.slices + blockIdx.x] = hist[i];
+}
+
+// One workgroup per bin.
+__global__ __launch_bounds__(256) void bin_scan(Bins b) {
+    __shared__ int wtot[256 / kWave];
+    int* c = b.cnt + (long long)blockIdx.x * b.slices;
+    constexpr int K = kBinSlices / 256;
+    int x[K], sum = 0, total;
+    for (int k = 0; k < K; ++k) {
+        const int i = threadIdx.x * K + k;
+        x[k] = i < b.slices ? c[i] : 0;
+        sum += x[k];
+    }
+    int run = block_scan(sum, wtot, &total);
+    for (int k = 0; k < K; ++k) {
+        const int i = threadIdx.x * K + k;
+        if (i < b.slices) c[i] = run;
+        run += x[k];
+    }
+    if (threadIdx.x == 0) b.tot[blockIdx.x] = total;
+}
+
+__global__ __launch_bounds__(kBinThreads) void bin_scatter(const int* col, long long m, Bins b) {
+    __shared__ int tile[kBinTile];          // targets sorted by bin
+    __shared__ int hist[kBinMax], place[kBinMax], start[kBinMax];
+    __shared__ int wtot[kBinThreads / kWave];
+    const int t = threadIdx.x;
+    int total;
+    {   // place[p]: where this slice's next target of bin p goes
+        const int x0 = 2 * t < b.bins ? b.tot[2 * t] : 0;
+        const int x1 = 2 * t + 1 < b.bins ? b.tot[2 * t + 1] : 0;
+        const int pre = block_scan(x0 + x1, wtot, &total);
+        if (2 * t < b.bins) place[2 * t] = pre + b.cnt[(long long)(2 * t) * b.slices + blockIdx.x];
+        if (2 * t + 1 < b.bins)
+            place[2 * t + 1] = pre + x0 + b.cnt[(long long)(2 * t + 1) * b.slices + blockIdx.x];
+    }
+    for (int j = 0; j < b.tiles; ++j) {
+        const long long t0 = ((long long)blockIdx.x * b.tiles + j) * kBinTile;
+        if (t0 >= m) break;
+        const int len = (int)min(m - t0, (long long)kBinTile);
+        __syncthreads();   // the previous tile has been written
+        hist[2 * t] = 0;
+        hist[2 * t + 1] = 0;
+        __syncthreads();
+        int w[kBinPer], rank[kBinPer];
+#pragma unroll
+        for (int k = 0; k < kBinPer; ++k) {
+            const int i = k * kBinThreads + t;
+            w[k] = i < len ? __builtin_nontemporal_load(col + t0 + i) : -1;
+        }
+#pragma unroll
+        for (int k = 0; k < kBinPer; ++k)
+            rank[k] = w[k] >= 0 ? atomicAdd(&hist[w[k] >> kBinLog], 1) : 0;
+        __syncthreads();
+        const int h0 = hist[2 * t], h1 = hist[2 * t + 1];
+        const int pre = block_scan(h0 + h1, wtot, &total);
+        start[2 * t] = pre;
+        start[2 * t + 1] = pre + h0;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kBinPer; ++k)
+            if (w[k] >= 0) tile[start[w[k] >> kBinLog] + rank[k]] = w[k];
+        __syncthreads();
+        for (int i = t; i < len; i += kBinThreads) {
+            const int x = tile[i], p = x >> kBinLog;
+            b.id[(uint32_t)(place[p] + (i - start[p]))] = (uint16_t)(x & (kBinV - 1));
+        }
+        __syncthreads();
+        if (2 * t < b.bins) place[2 * t] += h0;
+        if (2 * t + 1 < b.bins) place[2 * t + 1] += h1;
+    }
+}
+
+// Workgroup i counts part i of the bins' parts in bin order, a bin of c targets
+// having max(1, ceil(c / chunk)).  A bin of one part stores its counters, one of
+// several adds them (indeg cleared before).  Without bins (b.id NULL) the one
+// bin's targets are col itself.
+__global__ __launch_bounds__(kBinCountThreads) void bin_degrees(const int* col, long long m, int n,
+                                                                Bins b, long long chunk,
+                                                                int* indeg) {
+    __shared__ int deg[kBinV];
+    __shared__ int wtot[kBinCountThreads / kWave];
+    __shared__ long long s_from, s_to;
+    __shared__ int s_bin, s_parts;
+    const int t = threadIdx.x;
+    if (t == 0) s_bin = -1;
+    for (int i = t; i < kBinV; i += kBinCountThreads) deg[i] = 0;
+    {
+        const long long c = t < b.bins ? (b.id ? (long long)b.tot[t] : m) : 0;
+        const int parts = t < b.bins ? (c > chunk ? (int)((c + chunk - 1) / chunk) : 1) : 0;
+        int total;
+        const int before = block_scan((int)c, wtot, &total);   // m < 2^31
+        const int p0 = block_scan(parts, wtot, &total);
+        const int mine = (int)blockIdx.x - p0;
+        if (mine >= 0 && mine < parts) {
+            s_bin = t;
+            s_parts = parts;
+            s_from = before + mine * chunk;
+            s_to = min((long long)before + c, s_from + chunk);
+        }
+    }
+    __syncthreads();
+    if (s_bin < 0) return;   // the grid covers the largest possible number of parts
+    const long long from = s_from, to = s_to;
+    if (b.id) {
+        // 16-byte loads from the aligned position at or before `from`
+        const uint16_t* id = b.id;
+        constexpr int U = 4;
+        for (long long q = (from & ~7ll) + 8 * t; q < to; q += 8ll * U * kBinCountThreads) {
+            uint4 x[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const long long at = q + 8ll * k * kBinCountThreads;
+                if (at < to) x[k] = *reinterpret_cast<const uint4*>(id + at);
+            }
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const long long at = q + 8ll * k * kBinCountThreads;
+                const uint32_t y[4] = {x[k].x, x[k].y, x[k].z, x[k].w};
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (at + j >= from && at + j < to)
+                        atomicAdd(&deg[(y[j >> 1] >> (16 * (j & 1))) & (kBinV - 1)], 1);
+            }
+        }
+    } else {
+        for (long long e = from + t; e < to; e += kBinCountThreads) atomicAdd(&deg[col[e]], 1);
+    }
+    __syncthreads();
+    const int v0 = s_bin << kBinLog;
+    const int len = min(kBinV, n - v0);
+    if (s_parts == 1) {
+        for (int i = t; i < len; i += kBinCountThreads) indeg[v0 + i] = deg[i];
+    } else {
+        for (int i = t; i < len; i += kBinCountThreads)
+            if (deg[i]) atomicAdd(indeg + v0 + i, deg[i]);
+    }
+}
+
+// In-degrees with one copy of the counters per XCD: graphs of more than
+// kBinMax * kBinV vertices, and contexts whose memory cap leaves no room for the
+// bins.  Every XCD counts into its own copy with workgroup-scope
 // atomics, which its L2 executes (no other XCD touches that copy), and
 // sum_copies adds the copies at the end.  A wave on an unexpected XCD id adds
 // to indeg directly with device-wide atomics.
@@ -475,19 +689,60 @@ inline int tile_grid(long long m) {
 
 }  // namespace
 
+bool bin_degrees_ok(long long n, long long m) {
+    return n <= (long long)kBinMax * kBinV && m >= kBinMinM;
+}
+
+// Bytes of scratch: the binned targets (whole 16-byte words) and the counts.
+// None up to kBinV vertices.
+size_t bin_scratch_bytes(long long n, long long m) {
+    if (n <= kBinV) return 0;
+    const long long bins = (n + kBinV - 1) >> kBinLog;
+    return (size_t)((m * 2 + 15) / 16 * 16 + (bins * kBinSlices + bins) * 4);
+}
+
+static void in_degrees_binned(const int* col, int n, long long m, int* indeg, void* scratch,
+                              hipStream_t s) {
+    Bins b{};
+    b.bins = (int)(((long long)n + kBinV - 1) >> kBinLog);
+    long long chunk = kBinChunk;
+    if (b.bins > 1) {
+        b.id = reinterpret_cast<uint16_t*>(scratch);
+        b.cnt = reinterpret_cast<int*>(reinterpret_cast<char*>(scratch) + (m * 2 + 15) / 16 * 16);
+        const long long tiles = (m + kBinTile - 1) / kBinTile;
+        b.tiles = (int)((tiles + kBinSlices - 1) / kBinSlices);
+        b.slices = (int)((tiles + b.tiles - 1) / b.tiles);
+        b.tot = b.cnt + (long long)b.bins * b.slices;
+        hipLaunchKernelGGL(bin_count, dim3(b.slices), dim3(kBinThreads), 0, s, col, m, b);
+        hipLaunchKernelGGL(bin_scan, dim3(b.bins), dim3(256), 0, s, b);
+        hipLaunchKernelGGL(bin_scatter, dim3(b.slices), dim3(kBinThreads), 0, s, col, m, b);
+        // parts enough for the device, but no more adds than four a target
+        while (chunk > 4 * kBinV && m / chunk + b.bins < 512) chunk >>= 1;
+    } else {
+        chunk = 4ll * n > 16384 ? 4ll * n : 16384;
+    }
+    const long long parts = b.bins + (m + chunk - 1) / chunk;
+    hipLaunchKernelGGL(bin_degrees, dim3((unsigned)parts), dim3(kBinCountThreads), 0, s, col, m, n,
+                       b, chunk, indeg);
+}
+
 hipError_t mlp_prepare(const int* row_off, const int* col, int n, long long m, int* indeg,
-                       int* src, int* tinfo, int* copies, hipStream_t s) {
+                       int* src, int* tinfo, int* copies, void* bins, hipStream_t s) {
     hipLaunchKernelGGL(zero_ints, dim3(grid_for(n, 256, 8192)), dim3(256), 0, s, indeg,
                        (long long)n);
     if (m > 0) {
-        if (copies)
-            hipLaunchKernelGGL(zero_ints, dim3(grid_for((long long)n * kXcdCopies, 256, 16384)),
-                               dim3(256), 0, s, copies, (long long)n * kXcdCopies);
-        hipLaunchKernelGGL(in_degrees_xcd, dim3(grid_for(m, 256, 16384)), dim3(256), 0, s, col,
-                           m, n, copies, indeg);
-        if (copies)
-            hipLaunchKernelGGL(sum_copies, dim3(grid_for(n, 256, 16384)), dim3(256), 0, s, copies,
-                               n, indeg);
+        if (!copies && bin_degrees_ok(n, m)) {
+            in_degrees_binned(col, n, m, indeg, bins, s);
+        } else {
+            if (copies)
+                hipLaunchKernelGGL(zero_ints, dim3(grid_for((long long)n * kXcdCopies, 256, 16384)),
+                                   dim3(256), 0, s, copies, (long long)n * kXcdCopies);
+            hipLaunchKernelGGL(in_degrees_xcd, dim3(grid_for(m, 256, 16384)), dim3(256), 0, s, col,
+                               m, n, copies, indeg);
+            if (copies)
+                hipLaunchKernelGGL(sum_copies, dim3(grid_for(n, 256, 16384)), dim3(256), 0, s,
+                                   copies, n, indeg);
+        }
         hipLaunchKernelGGL(tile_first, dim3(grid_for(n, 256, 16384)), dim3(256), 0, s, row_off, n,
                            tinfo);
         hipLaunchKernelGGL(tile_sources, dim3(tile_grid(m)), dim3(kTileT), 0, s, row_off, n, m,

@@ -36,9 +36,11 @@ struct trim_ctx {
     // tile tables of the preprocessing and reordering kernels
     int* tiles = nullptr;
     long long cap_tiles = 0;
-    // per-XCD in-degree copies of trim_mlp_prepare
+    // per-XCD in-degree copies of trim_mlp_prepare, or its binned targets
     int* copies = nullptr;
     long long cap_copies = 0;
+    void* bins = nullptr;
+    size_t cap_bins = 0;
     // per-vertex features of trim_mlp_score (float2 per vertex)
     float* vf = nullptr;
     long long cap_vf = 0;
@@ -438,6 +440,7 @@ int trim_ctx_destroy(trim_ctx* c) {
     dfree(c, c->w.part);
     dfree(c, c->tiles);
     dfree(c, c->copies);
+    dfree(c, c->bins);
     dfree(c, c->vf);
     delete c;
     return TRIM_OK;
@@ -771,7 +774,23 @@ int trim_mlp_prepare(trim_ctx* c, const trim_csr_t* g, int32_t* indeg, int32_t* 
     if (!indeg || (g->m > 0 && !src)) return fail(TRIM_E_INVAL, "trim_mlp_prepare: NULL output");
     if ((rc = ensure_tiles(c, g->m))) return rc;
     int* copies = nullptr;
-    if (g->n <= trim::kXcdCopiesMaxN) {
+    bool binned = trim::bin_degrees_ok(g->n, g->m);
+    if (binned) {
+        const size_t need = trim::bin_scratch_bytes(g->n, g->m);
+        if (need > c->cap_bins) {
+            dfree(c, c->bins);
+            c->bins = nullptr;
+            c->cap_bins = 0;
+            if (dmalloc(c, &c->bins, need) == hipSuccess) {
+                c->cap_bins = need;
+            } else {   // no room under the cap: the copies may need less
+                (void)hipGetLastError();
+                c->bins = nullptr;
+                binned = false;
+            }
+        }
+    }
+    if (!binned && g->n <= trim::kXcdCopiesMaxN) {
         const long long need = (long long)trim::kXcdCopies * (g->n > 0 ? g->n : 1);
         if (need > c->cap_copies) {
             dfree(c, c->copies);
@@ -788,7 +807,7 @@ int trim_mlp_prepare(trim_ctx* c, const trim_csr_t* g, int32_t* indeg, int32_t* 
         copies = c->copies;
     }
     return launched(trim::mlp_prepare(g->row_off, g->col, g->n, g->m, indeg, src, c->tiles,
-                                      copies, (hipStream_t)stream));
+                                      copies, c->bins, (hipStream_t)stream));
 }
 
 int trim_mlp_grad(trim_ctx* c, const trim_csr_t* g, const int32_t* indeg, const int32_t* src,

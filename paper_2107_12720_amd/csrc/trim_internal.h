@@ -232,8 +232,12 @@ inline long long tile_scratch_ints(long long m) {
 // Per-XCD in-degree copies (kXcdCopies * n ints) are used up to this n.
 constexpr int kXcdCopies = 8;
 constexpr int kXcdCopiesMaxN = 1 << 26;
+// In-degrees by binning (bin_degrees_ok: scratch of bin_scratch_bytes, copies
+// NULL), else with copies, else (both NULL) with device-wide atomics.
+bool bin_degrees_ok(long long n, long long m);
+size_t bin_scratch_bytes(long long n, long long m);
 hipError_t mlp_prepare(const int* row_off, const int* col, int n, long long m, int* indeg,
-                       int* src, int* tinfo, int* copies, hipStream_t s);
+                       int* src, int* tinfo, int* copies, void* bins, hipStream_t s);
 hipError_t mlp_grad_launch(const int* row_off, const int* col, const int* indeg, const int* src,
                            long long m, const uint32_t* live, const short* pbf,
                            const long long* ids, long long count, uint64_t seed, int step,

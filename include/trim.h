@@ -497,7 +497,8 @@ int trim_mlp_adam(trim_ctx *ctx, float *params, uint16_t *params_bf16, float *ad
 
 /* scores[e] = the network's logit that the target of edge e stays live (its
  * probability is 1 / (1 + exp(-logit))) (m entries, CSR order).  Per-vertex features are first
- * tabulated in context memory (8 bytes per vertex, kept for later calls). */
+ * tabulated in context memory (12 bytes per vertex, 4 where the cap leaves no
+ * room for them, kept for later calls). */
 int trim_mlp_score(trim_ctx *ctx, const trim_csr_t *g, const int32_t *indeg, const int32_t *src,
                    const uint16_t *params_bf16, float *scores, void *stream);
 

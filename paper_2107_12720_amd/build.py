@@ -14,6 +14,9 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-Wall",
          # no packed-fp32 instruction selection (hazard on these parts)
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+# the network kernels' MFMAs take and leave plain registers, which the vector
+# instructions around them use (a move per accumulator word otherwise)
+FILE_FLAGS = {"mlp.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 
 def build(jobs: int = 4, verbose: bool = False) -> str:
@@ -23,7 +26,7 @@ def build(jobs: int = 4, verbose: bool = False) -> str:
     for src in SOURCES:
         obj = os.path.join(objdir, src.replace(".hip", ".o"))
         objs.append(obj)
-        cmd = [HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = [HIPCC, *FLAGS, *FILE_FLAGS.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)))

@@ -72,36 +72,17 @@ struct Graph {
     const int* indeg;
     const int* src;
     long long m;
-    // per-vertex (log1p(outdeg), log1p(indeg)) when precomputed, else NULL
-    const float2* vf;
 };
-
-// (log1p(outdeg v), log1p(indeg v)) in FP32, the same expressions the edge
-// features use.
-__global__ void vertex_features(const int* row_off, const int* indeg, int n, float2* vf) {
-    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x)
-        vf[v] = make_float2(log1pf((float)(row_off[v + 1] - row_off[v])),
-                            log1pf((float)indeg[v]));
-}
 
 // This lane's four features (half 0: features 0-3, half 1: 4-7) of edge e.
 __device__ __forceinline__ void features(const Graph& g, long long e, int half, float f[4],
                                          int& u, int& w) {
     u = g.src[e];
     w = g.col[e];
-    float lu, lw, iu, iw;
-    if (g.vf) {   // one 8-byte gather per endpoint
-        const float2 a = g.vf[u], b = g.vf[w];
-        lu = a.x;
-        iu = a.y;
-        lw = b.x;
-        iw = b.y;
-    } else {
-        lu = log1pf((float)(g.row_off[u + 1] - g.row_off[u]));
-        lw = log1pf((float)(g.row_off[w + 1] - g.row_off[w]));
-        iu = log1pf((float)g.indeg[u]);
-        iw = log1pf((float)g.indeg[w]);
-    }
+    const float lu = log1pf((float)(g.row_off[u + 1] - g.row_off[u]));
+    const float lw = log1pf((float)(g.row_off[w + 1] - g.row_off[w]));
+    const float iu = log1pf((float)g.indeg[u]);
+    const float iw = log1pf((float)g.indeg[w]);
     if (half == 0) {
         f[0] = lu;
         f[1] = iu;
@@ -339,29 +320,154 @@ __global__ void mlp_adam(float* p32, short* pbf, float* m1, float* m2, float* gr
     if (threadIdx.x == 0) grad[1377] = 0.f;
 }
 
+// Two floats as BF16 bits, nearest even, the first in the low half.
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
+    typedef __bf16 v2 __attribute__((ext_vector_type(2)));
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{lo, hi}, v2));
+}
+// max(x, 0) of two packed BF16 values: negative ones have the sign of a
+// negative 16-bit integer.
+__device__ __forceinline__ uint32_t relu_bf16x2(uint32_t x) {
+    typedef short s2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t,
+                              __builtin_elementwise_max(__builtin_bit_cast(s2, x), s2{0, 0}));
+}
+
+// What scoring needs of a vertex, in the four bytes that a gather of targets at
+// random places should cost at most: the out-degree (kOutMax: that or more)
+// above a ten-bit code of the in-degree's feature, log1p of an integer below
+// 2^31 as BF16, which is 0 or between bf16(log 2) and bf16(log 2^31).
+constexpr uint32_t kOutMax = (1u << 22) - 1;
+constexpr uint32_t kInBase = 0x3F00;
+// The edges' sources come in order, so theirs may be wider: both features as
+// BF16 (out-degree in the low half) and the out-degree's in FP32.
+struct ScoreSource {
+    uint32_t bf;
+    float out;
+};
+// sv: an entry per vertex; su, if given, the sources' entries.
+__global__ void score_vertices(const int* row_off, const int* indeg, int n, uint32_t* sv,
+                               ScoreSource* su) {
+    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x) {
+        const uint32_t d = (uint32_t)(row_off[v + 1] - row_off[v]);
+        const uint32_t in = (uint32_t)(uint16_t)f2bf(log1pf((float)indeg[v]));
+        sv[v] = (min(d, kOutMax) << 10) | (in ? in - kInBase : 0);
+        if (su) {
+            const float out = log1pf((float)(int)d);
+            su[v] = ScoreSource{(pack_bf16(out, 0.f) & 0xFFFFu) | (in << 16), out};
+        }
+    }
+}
+// Both features of vertex v with entry x as BF16, the out-degree's in the low
+// half, and that one in FP32 (`out`), for the difference.
+__device__ __forceinline__ uint32_t score_features(uint32_t x, int v, const int* row_off,
+                                                   float& out) {
+    uint32_t d = x >> 10;
+    if (d == kOutMax) d = (uint32_t)(row_off[v + 1] - row_off[v]);
+    out = log1pf((float)(int)d);
+    const uint32_t c = x & 0x3FFu;
+    return (pack_bf16(out, 0.f) & 0xFFFFu) | ((min(c, 1u) * kInBase + c) << 16);
+}
+
 // The network's logit that the target of every edge stays live, in CSR
 // order.  The logit, not the probability, is what the lists are ordered by:
 // the logistic function saturates to exactly 1 in FP32 for logits above about
 // 17, which would tie most live targets.
-__global__ __launch_bounds__(256) void mlp_score(Graph g, const short* p, float* score) {
-    const int l = lane_id(), half = l >> 5, col = l & 31;
+//
+// Two things bound it on R-MAT 24 (2.7 * 10^8 edges, 8.4 * 10^6 tiles of 32,
+// 3.73 ms at first): the targets' gathers, a fresh line for every one that the
+// L2s miss, and, at four cycles an instruction, the 220 instructions of a tile
+// (3 ms by themselves).  So what is gathered takes four bytes a vertex; a
+// wavefront takes two tiles at a time, one edge per lane for the loads and the
+// features (both halves used to make the same ones), and swaps halves of
+// registers to get the tiles' operands; conversions and the first ReLU go two
+// values an instruction; the second layer's biases enter as the MFMA's addend;
+// and the position's hash bits, two 64-bit products, come from a table for the
+// first kHashed positions of a list.
+// The sources' features come from their own table (kWide) unless the context
+// has no room for it: made from the four-byte entries, 3.05 instead of 2.64 ms.
+constexpr int kHashed = 4096;
+
+template <bool kWide>
+__global__ __launch_bounds__(256) void mlp_score(const int* row_off, const int* col,
+                                                 const int* src, long long m,
+                                                 const uint32_t* sv, const ScoreSource* su,
+                                                 const short* p, float* score) {
+    __shared__ uint8_t hashed[kHashed];
+    for (int i = threadIdx.x; i < kHashed; i += blockDim.x) hashed[i] = (uint8_t)(mix64(i) & 7);
+    __syncthreads();
+    const int l = lane_id();
     Weights W;
     load_weights(p, W);
-    const long long tiles_total = (g.m + 31) / 32;
+    f32x16 b2;
+    for (int r = 0; r < 16; ++r) b2[r] = W.b2[r];
+    const f32x16 zero = {};
+    const bf16x8 w2a = cat(W.w2[0], W.w2[1]), w2b = cat(W.w2[2], W.w2[3]);
+    auto logit = [&](uint32_t x0, uint32_t x1) {
+        const uint64_t x = ((uint64_t)x1 << 32) | x0;
+        const f32x16 z1 = mfma(W.w1, __builtin_bit_cast(bf16x4, x), zero);
+        uint32_t h[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+            h[r] = relu_bf16x2(pack_bf16(z1[2 * r] + W.b1[2 * r], z1[2 * r + 1] + W.b1[2 * r + 1]));
+        typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+        f32x16 z2 = mfma16(w2a, __builtin_bit_cast(bf16x8, u4{h[0], h[1], h[2], h[3]}), b2);
+        z2 = mfma16(w2b, __builtin_bit_cast(bf16x8, u4{h[4], h[5], h[6], h[7]}), z2);
+        float s = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s += W.w3[r] * fmaxf(z2[r], 0.f);
+        s += __shfl_xor(s, 32);   // the other half of the hidden units
+        return s + W.b3;
+    };
+    const long long pairs = (m + 63) / 64;
     const long long wave = (blockIdx.x * (long long)blockDim.x + threadIdx.x) / kWave;
     const long long nwaves = (gridDim.x * (long long)blockDim.x) / kWave;
-    for (long long t = wave; t < tiles_total; t += nwaves) {
-        const long long e = t * 32 + col;
-        float f[4] = {0.f, 0.f, 0.f, 0.f};
-        if (e < g.m) {
-            int u, w;
-            features(g, e, half, f, u, w);
-        }
-        f32x16 z1, z2;
-        bf16x4 h1[4];
-        float h2[16];
-        const float s = forward(W, f, z1, z2, h1, h2);
-        if (half == 0 && e < g.m) score[e] = s;
+    // ids two tile pairs ahead, what they lead to one ahead
+    struct Ids {
+        int u, w;
+        long long e;
+    };
+    struct Ends {
+        ScoreSource a;     // !kWide: u's four-byte entry in `bf`
+        uint32_t b, pos;   // w's entry
+        int u, w;
+    };
+    auto ids_of = [&](long long t) {
+        const long long e = t * 64 + l, ec = e < m ? e : m - 1;
+        return Ids{__builtin_nontemporal_load(src + ec), __builtin_nontemporal_load(col + ec), ec};
+    };
+    auto ends_of = [&](const Ids& i) {
+        return Ends{kWide ? su[i.u] : ScoreSource{sv[i.u], 0.f}, sv[i.w],
+                    (uint32_t)(i.e - row_off[i.u]), i.u, i.w};
+    };
+    if (wave >= pairs) return;
+    Ids ids = ids_of(wave);
+    Ends next = ends_of(ids);
+    ids = ids_of(wave + nwaves);
+    for (long long t = wave; t < pairs; t += nwaves) {
+        const Ends now = next;
+        next = ends_of(ids);
+        ids = ids_of(t + 2 * nwaves);
+        const long long e = t * 64 + l;
+        float a_out = now.a.out, b_out;
+        const uint32_t a_bf =
+            kWide ? now.a.bf : score_features(now.a.bf, now.u, row_off, a_out);
+        const uint32_t b_bf = score_features(now.b, now.w, row_off, b_out);
+        const uint32_t pos = now.pos;
+        uint32_t h = hashed[pos & (kHashed - 1)];
+        if (pos >= kHashed) h = (uint32_t)mix64(pos);
+        // features 4-7: the difference and the signs of the three bits
+        const uint32_t f45 = (pack_bf16(a_out - b_out, 0.f) & 0xFFFFu) |
+                             (0xBF800000u ^ ((h & 1u) << 31));
+        const uint32_t f67 = 0xBF80BF80u ^ ((h & 2u) << 14) ^ ((h & 4u) << 29);
+        // lanes 0-31 hold edges 0-31: after the swaps, x0 x1 are the first
+        // tile's operand (features 0-3 in the lower half, 4-7 in the upper)
+        // and y0 y1 the second's
+        const auto s0 = __builtin_amdgcn_permlane32_swap(a_bf, f45, false, false);
+        const auto s1 = __builtin_amdgcn_permlane32_swap(b_bf, f67, false, false);
+        const float first = logit(s0[0], s1[0]), second = logit(s0[1], s1[1]);
+        if (e < m) score[e] = l < 32 ? first : second;
     }
 }
 
@@ -378,7 +484,7 @@ hipError_t mlp_grad_launch(const int* row_off, const int* col, const int* indeg,
                            long long m, const uint32_t* live, const short* pbf,
                            const long long* ids, long long count, uint64_t seed, int step,
                            float* grad, int cus, hipStream_t s) {
-    Graph g{row_off, col, indeg, src, m, nullptr};
+    Graph g{row_off, col, indeg, src, m};
     const int blocks = grid_for((count + 31) / 32, kGradWaves, cus);
     hipLaunchKernelGGL(mlp_grad, dim3(blocks), dim3(kGradWaves * kWave), 0, s, g, live, pbf, ids,
                        count, seed, step, grad);
@@ -397,14 +503,20 @@ hipError_t mlp_adam_launch(float* p32, short* pbf, float* m1, float* m2, float* 
 }
 
 hipError_t mlp_score_launch(const int* row_off, const int* col, const int* indeg, const int* src,
-                            int n, long long m, const short* pbf, float* score, float2* vf,
-                            int cus, hipStream_t s) {
-    Graph g{row_off, col, indeg, src, m, vf};
+                            int n, long long m, const short* pbf, float* score, uint32_t* sv,
+                            bool wide, int cus, hipStream_t s) {
     if (m > 0) {
-        hipLaunchKernelGGL(vertex_features, dim3(grid_for(n, 256, 16384)), dim3(256), 0, s,
-                           row_off, indeg, n, vf);
-        hipLaunchKernelGGL(mlp_score, dim3(grid_for((m + 31) / 32, 4, cus * 16)), dim3(256), 0, s,
-                           g, pbf, score);
+        ScoreSource* su = wide ? reinterpret_cast<ScoreSource*>(sv) : nullptr;
+        if (wide) sv += 2 * (long long)n;
+        hipLaunchKernelGGL(score_vertices, dim3(grid_for(n, 256, 16384)), dim3(256), 0, s,
+                           row_off, indeg, n, sv, su);
+        const dim3 grid(grid_for((m + 63) / 64, 4, cus * 16));
+        if (wide)
+            hipLaunchKernelGGL(mlp_score<true>, grid, dim3(256), 0, s, row_off, col, src, m, sv,
+                               su, pbf, score);
+        else
+            hipLaunchKernelGGL(mlp_score<false>, grid, dim3(256), 0, s, row_off, col, src, m, sv,
+                               su, pbf, score);
     }
     return hipGetLastError();
 }

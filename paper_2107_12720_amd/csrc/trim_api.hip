@@ -41,8 +41,8 @@ struct trim_ctx {
     long long cap_copies = 0;
     void* bins = nullptr;
     size_t cap_bins = 0;
-    // per-vertex features of trim_mlp_score (float2 per vertex)
-    float* vf = nullptr;
+    // per-vertex features of trim_mlp_score (kScoreWords words per vertex, or one)
+    uint32_t* vf = nullptr;
     long long cap_vf = 0;
 };
 
@@ -844,21 +844,26 @@ int trim_mlp_score(trim_ctx* c, const trim_csr_t* g, const int32_t* indeg, const
     if (rc) return rc;
     if (!indeg || (g->m > 0 && (!src || !scores)) || !params_bf16)
         return fail(TRIM_E_INVAL, "trim_mlp_score: NULL argument");
-    const long long need = 2LL * (g->n > 0 ? g->n : 1);   // float2 per vertex
-    if (need > c->cap_vf) {
+    const long long n1 = g->n > 0 ? g->n : 1;
+    for (long long need : {trim::kScoreWords * n1, n1}) {   // the second without much room
+        if (need <= c->cap_vf) break;
+        const uint64_t others = c->mem_used - (uint64_t)c->cap_vf * 4;
+        if (need != n1 && c->mem_budget && others + (uint64_t)need * 4 > c->mem_budget) continue;
         dfree(c, c->vf);
         c->vf = nullptr;
         c->cap_vf = 0;
-        if (dmalloc(c, &c->vf, (size_t)need * 4) != hipSuccess) {
-            (void)hipGetLastError();
-            c->vf = nullptr;
-            return fail(TRIM_E_NOMEM, "cannot allocate vertex features for %d vertices", g->n);
+        if (dmalloc(c, &c->vf, (size_t)need * 4) == hipSuccess) {
+            c->cap_vf = need;
+            break;
         }
-        c->cap_vf = need;
+        (void)hipGetLastError();
+        c->vf = nullptr;
+        if (need == n1)
+            return fail(TRIM_E_NOMEM, "cannot allocate vertex features for %d vertices", g->n);
     }
     return launched(trim::mlp_score_launch(g->row_off, g->col, indeg, src, g->n, g->m,
-                                           (const short*)params_bf16, scores,
-                                           reinterpret_cast<float2*>(c->vf), c->cus,
+                                           (const short*)params_bf16, scores, c->vf,
+                                           c->cap_vf >= trim::kScoreWords * n1, c->cus,
                                            (hipStream_t)stream));
 }
 

@@ -74,3 +74,35 @@ def test_memory_cap():
         assert c.mem_used() <= 4 << 20
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("m", [1, 63, 64, 65, 1000, 70001])
+def test_score_forms(m):
+    """Scoring with the wide and the narrow vertex table agrees to the bit, over
+    partial tile pairs and a list longer than the table of hashed positions."""
+    import torch
+    import paper_2107_12720_amd as T
+    from paper_2107_12720_amd import learned
+    n = 900
+    rng = np.random.default_rng(m)
+    s = np.where(rng.random(m) < 0.5, 7, rng.integers(0, n, m)).astype(np.int32)   # one long list
+    g = gg.from_edges(n, s, rng.integers(0, n, m).astype(np.int32))
+    dg = T.DeviceGraph.upload(g)
+    p = learned.init_params(3) + rng.normal(0, 0.05, T.MLP_PARAMS).astype(np.float32)
+    pbf = T.to_device(learned.to_bf16_bits(p).view(np.int16))
+    wide = T.Context(0)
+    used = wide.mem_used()
+    narrow = T.Context(0, mem_budget=used + n * 8)   # room for one word per vertex only
+    try:
+        indeg, src = learned.prepare(wide, dg)
+        got = []
+        for c in (wide, narrow):
+            scores = torch.zeros(g.m, dtype=torch.float32, device="cuda")
+            c.mlp_score(dg, indeg, src, pbf, scores)
+            torch.cuda.synchronize()
+            got.append(scores.cpu().numpy())
+        assert narrow.mem_used() == used + n * 4
+        assert np.array_equal(got[0], got[1])
+    finally:
+        wide.close()
+        narrow.close()

@@ -409,17 +409,43 @@ __global__ void zero_ints(int* a, long long k) {
         a[i] = 0;
 }
 
+// Out-degrees in two bytes (kDegMax: that or more), for edge_keys.
+constexpr uint32_t kDegMax = 65535;
+__global__ void short_degrees(const int* row_off, int n, uint16_t* deg) {
+    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x)
+        deg[v] = (uint16_t)min((uint32_t)(row_off[v + 1] - row_off[v]), kDegMax);
+}
+
 // Keys for the reference orders: 0 = log1p(outdeg w) (larger first), 1 = a hash
-// of (seed, e) (a random order).
-__global__ void edge_keys(const int* row_off, const int* col, long long m, int kind, uint64_t seed,
-                          float* key) {
-    for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < m;
-         e += (long long)gridDim.x * blockDim.x) {
+// of (seed, e) (a random order).  The gather of the targets' degrees bounds
+// kind 0 (a line from beyond the L2 for every one they miss): with the two
+// offsets of every target it took 1.96 ms on R-MAT 24, from the table of two
+// bytes a vertex, of which the L2s hold more, 1.75 ms with the table's making.
+__global__ void edge_keys(const int* row_off, const int* col, const uint16_t* deg, long long m,
+                          int kind, uint64_t seed, float* key) {
+    constexpr int U = 4;
+    const long long stride = gridDim.x * (long long)blockDim.x;
+    for (long long e0 = blockIdx.x * (long long)blockDim.x + threadIdx.x; e0 < m;
+         e0 += U * stride) {
         if (kind == 0) {
-            const int w = col[e];
-            key[e] = log1pf((float)(row_off[w + 1] - row_off[w]));
+            int w[U], d[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k)
+                w[k] = __builtin_nontemporal_load(col + min(e0 + k * stride, m - 1));
+#pragma unroll
+            for (int k = 0; k < U; ++k)
+                d[k] = deg ? (int)deg[w[k]] : row_off[w[k] + 1] - row_off[w[k]];
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                if (deg && d[k] == (int)kDegMax) d[k] = row_off[w[k] + 1] - row_off[w[k]];
+                if (e0 + k * stride < m)
+                    __builtin_nontemporal_store(log1pf((float)d[k]), key + e0 + k * stride);
+            }
         } else {
-            key[e] = (float)(mix64(seed ^ (uint64_t)e) >> 40) * (1.f / 16777216.f);
+            for (int k = 0; k < U; ++k) {
+                const long long e = e0 + k * stride;
+                if (e < m) key[e] = (float)(mix64(seed ^ (uint64_t)e) >> 40) * (1.f / 16777216.f);
+            }
         }
     }
 }
@@ -751,11 +777,15 @@ hipError_t mlp_prepare(const int* row_off, const int* col, int n, long long m, i
     return hipGetLastError();
 }
 
-hipError_t edge_keys_launch(const int* row_off, const int* col, long long m, int kind,
-                            uint64_t seed, float* key, hipStream_t s) {
-    if (m > 0)
-        hipLaunchKernelGGL(edge_keys, dim3(grid_for(m, 256, 16384)), dim3(256), 0, s, row_off,
-                           col, m, kind, seed, key);
+hipError_t edge_keys_launch(const int* row_off, const int* col, int n, long long m, int kind,
+                            uint64_t seed, float* key, uint16_t* deg, hipStream_t s) {
+    if (m > 0) {
+        if (kind == 0 && deg)
+            hipLaunchKernelGGL(short_degrees, dim3(grid_for(n, 256, 16384)), dim3(256), 0, s,
+                               row_off, n, deg);
+        hipLaunchKernelGGL(edge_keys, dim3(grid_for((m + 3) / 4, 256, 16384)), dim3(256), 0, s,
+                           row_off, col, deg, m, kind, seed, key);
+    }
     return hipGetLastError();
 }
 

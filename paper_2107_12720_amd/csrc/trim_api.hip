@@ -873,8 +873,23 @@ int trim_edge_keys(trim_ctx* c, const trim_csr_t* g, int32_t kind, uint64_t seed
     if (rc) return rc;
     if (kind != 0 && kind != 1) return fail(TRIM_E_INVAL, "trim_edge_keys: kind must be 0 or 1");
     if (g->m > 0 && !keys) return fail(TRIM_E_INVAL, "trim_edge_keys: NULL keys");
-    return launched(
-        trim::edge_keys_launch(g->row_off, g->col, g->m, kind, seed, keys, (hipStream_t)stream));
+    // the table of degrees is worth its pass over the vertices from a few edges
+    // a vertex on; without room for it the keys come from the offsets
+    const long long words = ((long long)g->n + 1) / 2;
+    if (kind == 0 && g->m >= 2LL * g->n && words > c->cap_vf) {
+        uint32_t* more = nullptr;
+        if (dmalloc(c, &more, (size_t)words * 4) == hipSuccess) {
+            dfree(c, c->vf);
+            c->vf = more;
+            c->cap_vf = words;
+        } else {
+            (void)hipGetLastError();
+        }
+    }
+    const bool table = kind == 0 && g->m >= 2LL * g->n && words <= c->cap_vf;
+    return launched(trim::edge_keys_launch(g->row_off, g->col, g->n, g->m, kind, seed, keys,
+                                           table ? reinterpret_cast<uint16_t*>(c->vf) : nullptr,
+                                           (hipStream_t)stream));
 }
 
 int trim_order_by_key(trim_ctx* c, const trim_csr_t* g, const float* keys, float lo, float hi,

@@ -249,8 +249,9 @@ hipError_t mlp_score_launch(const int* row_off, const int* col, const int* indeg
                             uint32_t* sv, bool wide, int cus, hipStream_t s);
 // sv: kScoreWords words per vertex when wide (the faster form), else one.
 constexpr int kScoreWords = 3;
-hipError_t edge_keys_launch(const int* row_off, const int* col, long long m, int kind,
-                            uint64_t seed, float* key, hipStream_t s);
+// deg: n 16-bit words of scratch for kind 0, or NULL (slower).
+hipError_t edge_keys_launch(const int* row_off, const int* col, int n, long long m, int kind,
+                            uint64_t seed, float* key, uint16_t* deg, hipStream_t s);
 hipError_t order_launch(const int* row_off, const int* col, int n, long long m, const float* key,
                         float lo, float hi, int* col_out, int* tinfo, int* tcnt,
                         hipStream_t s);

@@ -33,12 +33,16 @@
 // that own them in LDS and finds each entry's owner by binary search, so a hub
 // and a thousand short lists cost the same per entry.  A neighbour is taken
 // once per direction, by the lane whose fetch-or sets its mark first, and
-// appended to the next frontier.
+// appended to the next frontier.  A level of the pivot's search whose frontier
+// holds a large part of all edges is taken the other way round (scc_pull):
+// every unassigned vertex not reached yet looks for a reached neighbour in its
+// own list and stops at the first.
 #include <chrono>
 
 #include "trim_device.h"
 #include "trim_internal.h"
 #include "scc_internal.h"
+#include "block_append.h"
 
 namespace trim {
 
@@ -132,8 +136,17 @@ __global__ void scc_pivot(int n, const int* row_off, const int* rrow_off, const 
         const unsigned long long o = ((unsigned long long)hi << 32) | lo;
         best = o > best ? o : best;
     }
-    if (lane_id() == 0 && best)
-        __hip_atomic_fetch_max(misc + kSccPivot, best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // one update per workgroup: a few thousand of one word take longer than
+    // the pass over the vertices
+    __shared__ unsigned long long s_best[16];
+    if (lane_id() == 0) s_best[threadIdx.x / kWave] = best;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < (int)(blockDim.x / kWave); ++w) best = max(best, s_best[w]);
+        if (best)
+            __hip_atomic_fetch_max(misc + kSccPivot, best, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+    }
 }
 
 // Search items: bit 30 = backward, low 30 bits = vertex.
@@ -265,8 +278,9 @@ __global__ __launch_bounds__(256) void scc_scan_chunks(const uint32_t* front, co
 }
 
 // Step 2 (one block): exclusive scan of the chunk sums, and the frontier's
-// total entries into misc[kSccTotal].
-__global__ void scc_scan_sums(uint32_t* bsum, unsigned long long* misc) {
+// total entries into misc[kSccTotal].  From `pull` entries on the level is
+// scc_pull's.
+__global__ void scc_scan_sums(uint32_t* bsum, unsigned long long* misc, unsigned long long pull) {
     __shared__ uint32_t s_w[16];
     __shared__ uint32_t s_carry;
     const long long F = (long long)misc[kSccFront];
@@ -292,13 +306,15 @@ __global__ void scc_scan_sums(uint32_t* bsum, unsigned long long* misc) {
     }
     if (threadIdx.x == 0) {
         misc[kSccTotal] = s_carry;
-        misc[kSccEdges] += s_carry;
+        if (s_carry < pull) misc[kSccEdges] += s_carry;
         misc[kSccNext] = 0;
     }
 }
 
 // Step 3: add the chunk offsets.
-__global__ void scc_scan_add(uint32_t* pre, const uint32_t* bsum, const unsigned long long* misc) {
+__global__ void scc_scan_add(uint32_t* pre, const uint32_t* bsum, const unsigned long long* misc,
+                             unsigned long long pull) {
+    if (misc[kSccTotal] >= pull) return;
     const long long F = (long long)misc[kSccFront];
     for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < F;
          i += (long long)gridDim.x * blockDim.x)
@@ -335,7 +351,9 @@ __global__ __launch_bounds__(256) void scc_expand(const uint32_t* front, const u
                                                   const int* rrow_off, const int* rcol,
                                                   const uint32_t* live, const int* color,
                                                   int* flags, uint32_t* next,
-                                                  unsigned long long* misc) {
+                                                  unsigned long long* misc,
+                                                  unsigned long long pull) {
+    if (misc[kSccTotal] >= pull) return;
     __shared__ uint32_t s_pre[kLBS + 1];
     __shared__ int s_start[kLBS + 1];
     __shared__ uint32_t s_item[kLBS + 1];
@@ -398,6 +416,80 @@ __global__ __launch_bounds__(256) void scc_expand(const uint32_t* front, const u
     }
     ors = wave_sum(ors);
     if (lane_id() == 0 && ors) add_misc(misc + kSccOrs, ors);
+}
+
+// One level the other way round: every unassigned vertex without a mark scans
+// its list on that direction's far side (predecessors for the forward search)
+// for a vertex with the mark, and takes the mark and joins the next frontier
+// at the first.  Every mark of the levels before is seen, so what this finds
+// includes all that the frontier's own lists lead to; marks set by this level
+// may be seen, too, which only finds vertices a level early.  Only v's lane
+// writes v's marks here.  A list's first kPullLane entries are scanned by its
+// lane, the rest by the whole wavefront.
+//
+// Why: the frontier's lists hold nearly all edges twice over in two or three
+// levels of a power-law graph (R-MAT 22: 1.3 * 10^8 entries, 2.2 ms), while a
+// vertex of the large component finds a marked neighbour among its first few.
+constexpr int kPullLane = 32, kPullStep = 4;
+
+__global__ __launch_bounds__(256) void scc_pull(int n, const int* row_off, const int* col,
+                                                const int* rrow_off, const int* rcol,
+                                                const uint32_t* live, int* flags, uint32_t* next,
+                                                unsigned long long* misc,
+                                                unsigned long long pull) {
+    __shared__ int s_wave[256 / kWave], s_base;
+    __shared__ unsigned long long red[16];
+    if (misc[kSccTotal] < pull) return;
+    unsigned long long seen = 0;
+    for (int base = blockIdx.x * blockDim.x; base < n; base += gridDim.x * blockDim.x) {
+        const int v = base + threadIdx.x;
+        const bool in = v < n && has_bit(live, v);
+        const int f = in ? flags[v] : 3;
+        int got = 0;
+#pragma unroll
+        for (int dir = 0; dir < 2; ++dir) {
+            const int mark = 1 << dir;
+            const int* off = dir ? row_off : rrow_off;
+            const int* adj = dir ? col : rcol;
+            int p = 0, e = 0;
+            if (!(f & mark)) {
+                p = off[v];
+                e = off[v + 1];
+            }
+            bool hit = false;
+            for (int stop = min(e, p + kPullLane); p < stop && !hit; p += kPullStep) {
+                int w[kPullStep], m[kPullStep];
+#pragma unroll
+                for (int j = 0; j < kPullStep; ++j) w[j] = adj[min(p + j, e - 1)];
+#pragma unroll
+                for (int j = 0; j < kPullStep; ++j) m[j] = ld_cached(flags + w[j]);
+#pragma unroll
+                for (int j = 0; j < kPullStep; ++j) hit |= (m[j] & mark) != 0;
+                seen += min(kPullStep, e - p);
+            }
+            for (uint64_t rest = ballot(!hit && p < e); rest; rest &= rest - 1) {
+                const int owner = __ffsll((unsigned long long)rest) - 1;
+                const int eb = __shfl(e, owner);
+                bool found = false;
+                for (int q = __shfl(p, owner); q < eb && !found; q += kWave) {
+                    const int at = q + lane_id();
+                    const bool m = at < eb && (ld_cached(flags + adj[at]) & mark);
+                    found = ballot(m) != 0;
+                    seen += at < eb;
+                }
+                if (lane_id() == owner) hit = found;
+            }
+            if (hit) got |= mark;
+        }
+        if (got) flags[v] = f | got;
+        const int c = (got & 1) + (got >> 1);
+        int* tail = reinterpret_cast<int*>(misc + kSccNext);   // the low half: at most 2n items
+        int slot = block_append_base(c, tail, nullptr, s_wave, &s_base);
+        if (got & 1) next[slot++] = ritem(0, v);
+        if (got & 2) next[slot] = ritem(1, v);
+    }
+    seen = block_total(seen, red);
+    if (threadIdx.x == 0 && seen) add_misc(misc + kSccEdges, seen);
 }
 
 // Size-2 check (the pattern after size-1 trimming): the only remaining
@@ -554,14 +646,26 @@ hipError_t scc_run(const trim_csr_t& g, const Work& w, const Work2& x, const Scc
     // them); ends when a level takes nothing
     auto search = [&](const int* color) -> hipError_t {
         const int ge = lc.cus * 8;
+        // A pull costs a pass over the vertices and the lists of those not
+        // reached, whatever the frontier; from an eighth of all list entries
+        // (each edge is in two) it is the better one.  Not with colours, where
+        // a neighbour counts only in the vertex's own colour.
+        const unsigned long long pull =
+            color ? ~0ull : (unsigned long long)(g.m / 4 > 1 ? g.m / 4 : 1);
         for (int cur = 0;; cur ^= 1) {
             hipLaunchKernelGGL(scc_scan_chunks, dim3(ge), dim3(256), 0, st, s.front[cur],
                                g.row_off, g.rrow_off, s.pre, s.bsum, s.misc);
-            hipLaunchKernelGGL(scc_scan_sums, dim3(1), dim3(1024), 0, st, s.bsum, s.misc);
-            hipLaunchKernelGGL(scc_scan_add, dim3(ge), dim3(256), 0, st, s.pre, s.bsum, s.misc);
+            hipLaunchKernelGGL(scc_scan_sums, dim3(1), dim3(1024), 0, st, s.bsum, s.misc,
+                               pull);
+            hipLaunchKernelGGL(scc_scan_add, dim3(ge), dim3(256), 0, st, s.pre, s.bsum, s.misc,
+                               pull);
             hipLaunchKernelGGL(scc_expand, dim3(ge), dim3(256), 0, st, s.front[cur], s.pre,
                                g.row_off, g.col, g.rrow_off, g.rcol, s.live, color, s.flags,
-                               s.front[cur ^ 1], s.misc);
+                               s.front[cur ^ 1], s.misc, pull);
+            if (!color)
+                hipLaunchKernelGGL(scc_pull, dim3(gv), dim3(256), 0, st, n, g.row_off, g.col,
+                                   g.rrow_off, g.rcol, s.live, s.flags, s.front[cur ^ 1], s.misc,
+                                   pull);
             hipLaunchKernelGGL(scc_level_done, dim3(1), dim3(64), 0, st, s.misc);
             hipError_t r = hipGetLastError();
             if (r == hipSuccess) r = read_misc();

@@ -15,8 +15,9 @@
 // zero removes it only if its exchange of dead[v] is the first one.  Every
 // removed vertex walks both of its lists once.
 //
-// Kernels: ac4_init (counters), ac4_seed (out-degree-0 vertices queued),
-// ac4_propagate (persistent workers on per-wavefront LDS rings, WaveQueue;
+// Kernels: ac4_init (counters), ac4_first (the vertices removed from the start,
+// spread evenly over the device; those that their removal takes down are
+// queued), ac4_propagate (persistent workers on per-wavefront LDS rings, WaveQueue;
 // a lane walks a short predecessor list of its removed vertex eight at a
 // time, with the eight decrements in flight together, and then goes on with
 // one of the vertices it removed itself, depth first; long lists are walked
@@ -24,7 +25,6 @@
 #include "trim_device.h"
 #include "trim_stats.h"
 #include "trim_internal.h"
-#include "block_append.h"
 
 namespace trim {
 
@@ -52,27 +52,6 @@ __global__ void ac4_init(const int* row_off, const int* rrow_off, const uint32_t
     }
 }
 
-// Four vertices per thread, one shared-queue reservation per block and step.
-template <bool kTwo>
-__global__ void ac4_seed(const int* cnt, const int* dead, int n, uint32_t* q, int* ctr) {
-    __shared__ int s_wave[1024 / kWave], s_base;
-    const int step = gridDim.x * blockDim.x * 4;
-    for (int base = blockIdx.x * blockDim.x * 4; base < n; base += step) {
-        int v[4], c = 0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int x = base + j * blockDim.x + threadIdx.x;
-            const bool d = x < n && (kTwo ? dead[x] != 0 : cnt[x] == 0);
-            v[j] = d ? x : -1;
-            c += d;
-        }
-        int slot = block_append_base(c, ctr + kQTail, ctr + kPending, s_wave, &s_base);
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (v[j] >= 0) q[slot++] = make_item(0, v[j]);
-    }
-}
-
 // The lane whose decrement brought a counter of u to zero: u's remover?
 template <bool kTwo>
 __device__ __forceinline__ bool removes(int* dead, int u) {
@@ -86,6 +65,103 @@ constexpr int kCoop = 16;   // predecessor lists longer than this are walked by 
 // core+tail graph 35 % and R-MAT 22 with half of its vertices preset 12 %
 // faster than with 64, the R-MAT 22 chain workload unchanged).
 constexpr int kShareEvery4 = 16;
+
+// The removals of the vertices removed from the start (no successors, with kTwo
+// no predecessors either way, or preset; read off the offsets, since counters
+// reach zero while this runs).  On a power-law graph they are most of all
+// removals and nearly all have short lists or none: through the shared queue
+// the 9.4 * 10^6 of R-MAT 24, 2.1 * 10^6 reverse edges in all, took 3.4 of
+// 3.7 ms.  A wavefront takes 64 consecutive vertices at a time; lists of up to
+// kCoop entries are walked by their lanes, longer ones by the wavefront.
+constexpr int kFirstBuf = 2048;   // removed vertices kept in LDS before one reservation
+
+template <bool kTwo>
+__global__ __launch_bounds__(256) void ac4_first(const int* rrow_off, const int* rcol,
+                                                 const int* row_off, const int* col,
+                                                 const uint32_t* preset, int n, int* cnt,
+                                                 int* dead, uint32_t* q, int* ctr,
+                                                 uint64_t* worker_edges, int P, int sched) {
+    __shared__ uint32_t buf[kFirstBuf];
+    __shared__ int s_n, s_base;
+    __shared__ uint64_t red[16];
+    if (threadIdx.x == 0) s_n = 0;
+    __syncthreads();
+    auto push = [&](bool has, int u) {
+        const uint64_t m = ballot(has);
+        if (!m) return;
+        int base = 0;
+        if (lane_id() == 0) base = atomicAdd(&s_n, popc(m));
+        base = __shfl(base, 0) + popc(m & lanes_below());
+        if (has && base < kFirstBuf) buf[base] = make_item(0, u);
+        const int slot = wave_append_slot(has && base >= kFirstBuf, ctr + kQTail, ctr + kPending);
+        if (slot >= 0) q[slot] = make_item(0, u);
+    };
+    uint64_t edges = 0;
+    const int waves = (gridDim.x * blockDim.x) / kWave;
+    const int wid = (blockIdx.x * blockDim.x + threadIdx.x) / kWave;
+    for (long long base = (long long)wid * kWave; base < n; base += (long long)waves * kWave) {
+        const int v = (int)base + lane_id();
+        const int x = v < n ? v : n - 1;
+        const int b = row_off[x], be = row_off[x + 1], rb = rrow_off[x], re = rrow_off[x + 1];
+        const bool gone = v < n && (b == be || (kTwo && rb == re) ||
+                                    (preset && ((preset[x >> 5] >> (x & 31)) & 1u)));
+        if (!ballot(gone)) continue;
+#pragma unroll
+        for (int ph = 0; ph < (kTwo ? 2 : 1); ++ph) {
+            const int* adj = ph ? col : rcol;
+            int* ctr_of = ph ? cnt + n : cnt;
+            int k = gone ? (ph ? b : rb) : 0;
+            const int e = gone ? (ph ? be : re) : 0;
+            edges += (uint64_t)(e - k);
+            for (uint64_t big = ballot(e - k > kCoop); big; big &= big - 1) {
+                const int owner = __ffsll((unsigned long long)big) - 1;
+                const int kb = __shfl(k, owner), eb = __shfl(e, owner);
+                for (int at = kb; at < eb; at += kWave * kBatch) {
+                    int u[kBatch], old[kBatch];
+#pragma unroll
+                    for (int j = 0; j < kBatch; ++j) {
+                        const int p = at + j * kWave + lane_id();
+                        if (p < eb) u[j] = adj[p];
+                    }
+                    if (sched & TRIM_SCHED_JITTER) jitter_nap(((uint64_t)kb << 20) ^ at);
+#pragma unroll
+                    for (int j = 0; j < kBatch; ++j)
+                        if (at + j * kWave + lane_id() < eb) old[j] = add_dev(ctr_of + u[j], -1);
+#pragma unroll
+                    for (int j = 0; j < kBatch; ++j)
+                        push(at + j * kWave + lane_id() < eb && old[j] == 1 &&
+                                 removes<kTwo>(dead, u[j]), u[j]);
+                }
+                if (lane_id() == owner) k = e;
+            }
+            while (ballot(k < e)) {
+                const int nb = min(kBatch, e - k);
+                int u[kBatch], old[kBatch];
+#pragma unroll
+                for (int j = 0; j < kBatch; ++j)
+                    if (j < nb) u[j] = adj[k + j];
+                if (sched & TRIM_SCHED_JITTER) jitter_nap(((uint64_t)k << 16) ^ v);
+#pragma unroll
+                for (int j = 0; j < kBatch; ++j)
+                    if (j < nb) old[j] = add_dev(ctr_of + u[j], -1);
+#pragma unroll
+                for (int j = 0; j < kBatch; ++j)
+                    push(j < nb && old[j] == 1 && removes<kTwo>(dead, u[j]), u[j]);
+                if (nb > 0) k += nb;
+            }
+        }
+    }
+    __syncthreads();
+    const int k = min(s_n, kFirstBuf);
+    if (threadIdx.x == 0 && k > 0) {
+        add_dev(ctr + kPending, k);
+        s_base = add_dev(ctr + kQTail, k);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < k; i += blockDim.x) q[s_base + i] = buf[i];
+    edges = block_sum(edges, red);
+    if (threadIdx.x == 0 && edges) add_dev(worker_edges + (blockIdx.x % P), edges);
+}
 
 // Phase 0 walks pre(w) over G^T and decrements out-counters (cnt[u]); with
 // kTwo, phase 1 then walks post(w) over G and decrements in-counters
@@ -227,7 +303,7 @@ inline int grid_for(long long n, int block, int max_blocks = 1 << 20) {
 template <bool kTwo>
 hipError_t ac4_run(const trim_csr_t& g, const Work& w, const LaunchCfg& lc, uint32_t* bitmap,
                    uint64_t* worker_edges, trim_stats_t* stats, const uint32_t* preset) {
-    const int n = g.n, P = lc.workers, B = lc.block;
+    const int n = g.n, P = lc.workers;
     int pack_blocks = 0;
     {
         Timed t(lc, kTwo ? "ac4t_init" : "ac4_init");
@@ -237,9 +313,10 @@ hipError_t ac4_run(const trim_csr_t& g, const Work& w, const LaunchCfg& lc, uint
     }
     if (n > 0) {
         {
-            Timed t(lc, kTwo ? "ac4t_seed" : "ac4_seed");
-            hipLaunchKernelGGL(ac4_seed<kTwo>, dim3(grid_for(n, 4 * B, lc.cus * 8)), dim3(B), 0,
-                               lc.stream, w.a, w.d, n, w.q, w.ctr);
+            Timed t(lc, kTwo ? "ac4t_first" : "ac4_first");
+            hipLaunchKernelGGL(ac4_first<kTwo>, dim3(grid_for(n, 256, lc.cus * 8)), dim3(256), 0,
+                               lc.stream, g.rrow_off, g.rcol, g.row_off, g.col, preset, n, w.a,
+                               w.d, w.q, w.ctr, worker_edges, P, lc.schedule);
         }
         {
             Timed t(lc, kTwo ? "ac4t_propagate" : "ac4_propagate");

@@ -83,24 +83,32 @@ template <class View>
 __global__ void ac3_list_preset(View g, int n, const uint32_t* preset, int* list1, int* ctr) {
     __shared__ uint64_t lds[Stage3<View>::kWords];
     __shared__ int s_wave[1024 / kWave], s_base;
+    // the offsets and targets of U vertices per thread in flight, then one
+    // reservation: with four, their loads after it, 66 us at 2^22 vertices
+    constexpr int U = 8;
     Stage3<View>::apply(g, lds);
-    const int step = gridDim.x * blockDim.x * 4;
-    for (int base = blockIdx.x * blockDim.x * 4; base < n; base += step) {
-        int v[4], c = 0;
+    const int step = gridDim.x * blockDim.x * U;
+    for (int base = blockIdx.x * blockDim.x * U; base < n; base += step) {
+        int v[U], b[U], w[U], c = 0;
+        bool keep[U];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int x = base + j * blockDim.x + threadIdx.x;
-            const bool keep = x < n && !((preset[x >> 5] >> (x & 31)) & 1u);
-            v[j] = keep ? x : -1;
-            c += keep;
+        for (int j = 0; j < U; ++j) {
+            v[j] = base + j * blockDim.x + threadIdx.x;
+            const int x = v[j] < n ? v[j] : n - 1;
+            keep[j] = v[j] < n && !((preset[x >> 5] >> (x & 31)) & 1u);
+            b[j] = g.begin(x);
+            w[j] = g.end(x);
+            c += keep[j];
         }
+#pragma unroll
+        for (int j = 0; j < U; ++j)
+            w[j] = keep[j] && b[j] < w[j] ? g.target(v[j], b[j], g.vctx(v[j])) : kNoTarget;
         int slot = block_append_base(c, ctr + kCnt0 + 1, nullptr, s_wave, &s_base);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (v[j] < 0) continue;
-            const int b = g.begin(v[j]), e = g.end(v[j]);
+        for (int j = 0; j < U; ++j) {
+            if (!keep[j]) continue;
             list1[slot] = v[j];
-            list1[n + slot] = b < e ? g.target(v[j], b, g.vctx(v[j])) : kNoTarget;
+            list1[n + slot] = w[j];
             ++slot;
         }
     }
@@ -113,14 +121,24 @@ __global__ void ac3_list_preset(View g, int n, const uint32_t* preset, int* list
 // is still live costs one random access (the target's removal round); only
 // when it has died are the cursor, the offsets and further successors read.
 constexpr int kUnroll = 4;
+// Threads of a rounds workgroup: a round over many entries is bound by the
+// accesses in flight, so one workgroup per CU has 1,024; a round of a small
+// graph, or with two workgroups per CU (opts.workers), has 256, so that the
+// launch never asks for all of a CU's wavefront slots (every workgroup has to
+// be resident).
+constexpr int kAc3Threads = 1024;
+constexpr int kAc3LargeN = 1 << 18;
+inline int ac3_block(long long n, int P, int cus) {
+    return n >= kAc3LargeN && P <= cus ? kAc3Threads : 256;
+}
 
 template <class View>
-__global__ __launch_bounds__(256) void ac3_rounds(View g, int n, int* ptr, int* dround,
+__global__ __launch_bounds__(kAc3Threads) void ac3_rounds(View g, int n, int* ptr, int* dround,
                                                   int* list0, int* list1, int* ctr,
                                                   uint64_t* worker_edges, trim_stats_t* stats,
                                                   int budget) {
     __shared__ uint64_t lds[Stage3<View>::kWords];
-    __shared__ int s_wave[256 / kWave], s_base;
+    __shared__ int s_wave[kAc3Threads / kWave], s_base;
     Stage3<View>::apply(g, lds);
     uint64_t edges = 0;
     int r = 1;
@@ -244,11 +262,11 @@ __device__ __forceinline__ int scan_on(const ExplicitView& g, int v, int p0, int
     return p;
 }
 
-__global__ __launch_bounds__(256) void ac3_rounds2(ExplicitView out, ExplicitView in, int n,
-                                                   int* ptr, int* ptr_in, int* dround, List3 l0,
+__global__ __launch_bounds__(kAc3Threads) void ac3_rounds2(ExplicitView out, ExplicitView in,
+                                                   int n, int* ptr, int* ptr_in, int* dround, List3 l0,
                                                    List3 l1, int* ctr, uint64_t* worker_edges,
                                                    trim_stats_t* stats, int budget) {
-    __shared__ int s_wave[256 / kWave], s_base;
+    __shared__ int s_wave[kAc3Threads / kWave], s_base;
     uint64_t edges = 0;
     int r = 1;
     const int stride = gridDim.x * blockDim.x;
@@ -370,7 +388,7 @@ hipError_t ac3_run(View g, int n, const Work& w, const LaunchCfg& lc, uint32_t* 
     }
     if (preset && n > 0) {
         Timed t(lc, "ac3_list_preset");
-        hipLaunchKernelGGL(ac3_list_preset<View>, dim3(grid_for(n, 1024, lc.cus * 8)), dim3(256), 0,
+        hipLaunchKernelGGL(ac3_list_preset<View>, dim3(grid_for(n, 2048, lc.cus * 8)), dim3(256), 0,
                            lc.stream, g, n, preset, list1, w.ctr);
     }
     if (n > 0) {
@@ -381,7 +399,8 @@ hipError_t ac3_run(View g, int n, const Work& w, const LaunchCfg& lc, uint32_t* 
         {
             Timed t(lc, "ac3_rounds");
             hipError_t e = hipLaunchCooperativeKernel((const void*)ac3_rounds<View>, dim3(P),
-                                                      dim3(256), args, 0, lc.stream);
+                                                      dim3(ac3_block(n, P, lc.cus)), args, 0,
+                                                      lc.stream);
             if (e != hipSuccess) return e;
         }
         Timed t(lc, "ac3_pack");
@@ -426,8 +445,9 @@ hipError_t ac3_two_csr(const trim_csr_t& g, const Work& w, const Work2& x, const
                         &worker_edges, &stats, &budget};
         {
             Timed t(lc, "ac3t_rounds");
-            hipError_t e = hipLaunchCooperativeKernel((const void*)ac3_rounds2, dim3(P), dim3(256),
-                                                      args, 0, lc.stream);
+            hipError_t e = hipLaunchCooperativeKernel((const void*)ac3_rounds2, dim3(P),
+                                                      dim3(ac3_block(n, P, lc.cus)), args, 0,
+                                                      lc.stream);
             if (e != hipSuccess) return e;
         }
         Timed t(lc, "ac3t_pack");

@@ -50,7 +50,6 @@ __device__ __forceinline__ short f2bf(float f) {   // round to nearest even
 __device__ __forceinline__ float bf2f(short h) {
     return __uint_as_float(((uint32_t)(uint16_t)h) << 16);
 }
-__device__ __forceinline__ float rbf(float f) { return bf2f(f2bf(f)); }
 // row of D register r held by lane l
 __device__ __forceinline__ int drow(int r, int l) { return 8 * (r >> 2) + 4 * (l >> 5) + (r & 3); }
 __device__ __forceinline__ f32x16 mfma(bf16x4 a, bf16x4 b, f32x16 c) {

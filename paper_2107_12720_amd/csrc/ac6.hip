@@ -61,6 +61,12 @@
 //                  (WaveQueue); a lane follows an S_last chain for up to
 //                  kHops removals in a row.  Exits when no item is pending.
 //   ac6_pack       live bitmap by wavefront ballot, live/dead counts.
+//
+// These serve the implicit graph, batches of graphs too large for a workgroup,
+// explicit graphs with late registration and the fixed-memory entry point.
+// Other explicit graphs go to one workgroup (small.hip) or to the rounds over
+// watched supports (ac6_watch.h), which end in the kernels above when a graph
+// is too deep for them.
 #include "trim_device.h"
 #include "trim_stats.h"
 #include "trim_internal.h"
@@ -68,6 +74,7 @@
 #include "block_append.h"
 #include "grid_barrier.h"
 #include "forest_jump.h"
+#include "ac6_watch.h"
 
 namespace trim {
 
@@ -1265,12 +1272,108 @@ hipError_t ac6_run(View g, int n, const Work& w, const LaunchCfg& lc, uint32_t* 
     return hipGetLastError();
 }
 
+// Watched supports serve every explicit graph that one workgroup does not take
+// (small.hip): against lists from the first sweep on, core+tail graphs of 10^5
+// vertices take 266 / 402 us, of 2^21 762 / 764, R-MAT of edge factor 16 and
+// 2^22 vertices 190 / 350, 2^24 480 / 890, uniform ones of mean degree 1.1 and
+// 2^20 vertices 828 / 850.  Below this size (graphs of too many edges for one
+// workgroup) the lists stay: their place must hold the filters.
+constexpr int kWatchMinN = 4096;
+static_assert(2LL * kWatchMinN >= 3 * WatchFilter::kWords, "the filters fit");
+
+// The device-wide path for explicit graphs: supports watched, lists only for a
+// deep remainder (ac6_watch.h).
+hipError_t ac6_watch_run(const trim_csr_t& g, const Work& w, const LaunchCfg& lc, uint32_t* bitmap,
+                         uint64_t* worker_edges, trim_stats_t* stats, const uint32_t* preset) {
+    const int n = g.n, P = lc.workers, B = lc.block;
+    hipStream_t st = lc.stream;
+    int* ext = (w.ext && n <= kSplitMaxN) ? w.ext : nullptr;
+    uint32_t* y1 = reinterpret_cast<uint32_t*>(w.c);
+    uint32_t* dead = y1 + round_bitmap_offset(n);
+    // the filters lie where the heads will, which are made last if at all
+    const WatchFilter flt{reinterpret_cast<uint32_t*>(w.a)};
+    const WatchState a{g.row_off, g.col, n, w.d, w.b, dead, flt, w.ctr, worker_edges, P,
+                       lc.schedule};
+    const ExplicitView v{g.row_off, g.col};
+    const int level_blocks = phase_blocks(n, lc.cus);
+    const int sweep_blocks = grid_for(n, (long long)B * kSweepFlight, lc.cus * 8);
+    {
+        Timed t(lc, "ac6_init");
+        hipLaunchKernelGGL(watch_init, dim3(grid_for((n + 3) / 4, 256, 16384)), dim3(256), 0, st,
+                           g.row_off, n, ((uintptr_t)g.row_off & 15) == 0, preset, y1, dead, flt,
+                           w.ctr, worker_edges, P, stats);
+    }
+    {
+        Timed t(lc, "ac6_sweep");
+        if (lc.forest)
+            hipLaunchKernelGGL(watch_sweep<true>, dim3(sweep_blocks), dim3(B), 0, st, a,
+                               (long long)g.m, y1, w.jp, w.e, w.part);
+        else
+            hipLaunchKernelGGL(watch_sweep<false>, dim3(sweep_blocks), dim3(B), 0, st, a,
+                               (long long)g.m, y1, (int*)nullptr, (uint32_t*)nullptr, w.part);
+    }
+    if (lc.forest) {
+        Timed t(lc, "ac6_jump");
+        hipLaunchKernelGGL(ac6_jump<WatchKill>, dim3(level_blocks), dim3(256), 0, st,
+                           WatchKill{w.d, dead}, w.jp, w.e, w.e + n, w.q, w.ctr,
+                           jump_rounds(n), lc.budget);
+    }
+    {
+        Timed t(lc, "ac6_rounds");
+        const int rb = grid_for(n, 256LL * kRoundFlight, lc.cus * 8);
+        // a launch starts with clean caches, so the statuses themselves are
+        // probed as long as the L2s hold most of them
+        for (int r = 1; r <= kRoundLaunches; ++r)
+            if (r > 1 && n > kSplitMaxN)
+                hipLaunchKernelGGL(watch_round<true>, dim3(rb), dim3(256), 0, st, a, r);
+            else
+                hipLaunchKernelGGL(watch_round<false>, dim3(rb), dim3(256), 0, st, a, r);
+        hipLaunchKernelGGL(watch_tail,
+                           dim3(grid_for(n, (long long)kTailThreads * kTailPer, lc.cus)),
+                           dim3(kTailThreads), 0, st, a, kRoundLaunches + 1, watch_rounds(n),
+                           lc.budget);
+    }
+    {
+        Timed t(lc, "ac6_register");
+        hipLaunchKernelGGL(watch_heads, dim3(grid_for(n, 1024, lc.cus * 8)), dim3(256), 0, st, dead,
+                           n, w.a, ext, w.ctr);
+        hipLaunchKernelGGL(watch_register, dim3(grid_for(n, 1024, lc.cus * 8)), dim3(256), 0, st, a,
+                           w.a, ext, w.q);
+    }
+    {
+        Timed t(lc, "ac6_levels");
+        hipLaunchKernelGGL(ac6_levels<ExplicitView>, dim3(level_blocks), dim3(256), 0, st, v, w.a,
+                           ext, w.b, w.q, w.e, w.e + n, w.ctr, worker_edges, P, w.part,
+                           lc.schedule, lc.budget);
+    }
+    {
+        Timed t(lc, "ac6_propagate");
+        hipLaunchKernelGGL(ac6_propagate<ExplicitView>, dim3(P), dim3(256), 0, st, v, w.a, ext,
+                           w.b, w.q, w.ctr, worker_edges, w.part, lc.schedule, lc.budget);
+    }
+    const int pack_blocks = grid_for(n, 256, lc.cus * 4);
+    {
+        Timed t(lc, "ac6_pack");
+        hipLaunchKernelGGL(ac6_pack_deferred, dim3(pack_blocks), dim3(256), 0, st, w.a, dead, n,
+                           bitmap, w.part, w.ctr, w.q, w.qwords);
+    }
+    if (stats) {
+        Timed t(lc, "finalize");
+        hipLaunchKernelGGL(finalize_stats, dim3(1), dim3(1024), 0, st, n, P, sweep_blocks, P,
+                           pack_blocks, P, worker_edges, w.part, w.ctr, stats, 0, 0, level_blocks);
+    }
+    return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t ac6_csr(const trim_csr_t& g, const Work& w, const LaunchCfg& lc, uint32_t* bitmap,
                    uint64_t* worker_edges, trim_stats_t* stats, const uint32_t* preset) {
     if (ac6_small_ok(g.n, g.m, lc.rounds))
         return ac6_small_csr(g, w, lc, bitmap, worker_edges, stats, preset);
+    // (w.d: the fixed array of trim_csr_noalloc has no place for the supports)
+    if (lc.rounds < 2 && w.d && g.n > kWatchMinN)
+        return ac6_watch_run(g, w, lc, bitmap, worker_edges, stats, preset);
     ExplicitView v{g.row_off, g.col};
     return ac6_run(v, g.n, w, lc, bitmap, worker_edges, stats, nullptr, nullptr, 0, preset);
 }

@@ -1,0 +1,488 @@
+// ac6_watch.h -- AC-6 of a large explicit graph by watching supports
+// (Section 6.2; included by ac6.hip).
+//
+// As in watch.h, a vertex is handed back when a pass over the vertices finds
+// its support removed, not by a walk over the support's list; the support
+// searches and their counts are the same.  Joining a list costs a device-wide
+// exchange at a random place for every vertex that keeps a successor: on
+// R-MAT 22, 1.6 of 2.0 * 10^6 of them in a sweep of 0.2 ms, to hand back 53
+// vertices; a round over all supports reads them in order and probes a bitmap
+// that the L2s hold.
+//
+//   watch_init    statuses (two bitmaps: the sweep reads y1, everything later
+//                 reads and sets `dead`), counters, filters;
+//   watch_sweep   DoPost of every vertex; supports in sup[], positions in the
+//                 high halves of rec[] where they are not the first, links and
+//                 members for the forest collapse;
+//   ac6_jump      the forest collapse (forest_jump.h), setting statuses;
+//   watch_round   one round: vertices whose support was removed resume their
+//                 scans.  kRoundLaunches launches; a round that removes nothing
+//                 is the last, and what follows returns at once;
+//   watch_tail    further rounds in one launch with grid barriers, up to
+//                 watch_rounds(n) rounds in all;
+//   watch_heads, watch_register
+//                 if that did not end it (a deep, narrow remainder): list heads
+//                 from the statuses, every vertex left joins its support's
+//                 list, and the propagation over lists finishes.
+//
+// What bounds it: the sweep by its gathers of row_off, col and statuses (67 us
+// for R-MAT 22, edge factor 16, 200 with the exchanges), a round of all vertices
+// by reading sup (12 us at 2^22) and by the latency of four dependent loads,
+// about 5 us, plus 2 for the barrier in the tail.  R-MAT 22 with a chain of
+// 2*10^5: 524 -> 314 us in all; 24 without: 910 -> 480; core+tail of 10^5
+// vertices 402 -> 266, of 2^20 564 -> 473.
+//
+// Filters: a support that was live before round r - 1 is removed before round
+// r iff round r - 1 removed it.  While those removals are few, a round tests a
+// hashed filter of them in LDS and looks at the statuses only on a hit: in
+// watch_tail, where a status has to be read past the L2 (it may have changed
+// since the line was cached), and, from round 2 on, for graphs whose bitmap the
+// L2s don't hold.
+#pragma once
+#include "trim_device.h"
+#include "block_append.h"
+#include "grid_barrier.h"
+#include "ac6_support.h"
+#include "forest_jump.h"
+
+namespace trim {
+
+namespace {
+
+constexpr int kSupFirst = 1 << 29;      // sup[]: the support is the first successor
+constexpr int kSupMask = kSupFirst - 1;
+constexpr int kRoundLaunches = 4;
+constexpr int kWatchRounds = 64;
+// Rounds before the vertices left are registered in lists.  A round of the tail
+// takes 6 to 9 us up to 2^20 vertices and 19 at 2^22, a phase over lists 5 (one
+// removal) to 60 (thousands), registering 50 and 170.  Core+tail graphs of mean
+// degree 30 and 2^20 vertices (some 60 rounds) take 2.5 ms with 64 rounds, 3.1
+// with 40; with lists alone 3.8.  66 rounds of one removal each, the worst case,
+// take 0.68 ms, with lists alone 0.46.
+constexpr int watch_rounds(int n) {
+    const int r = n <= (1 << 21) ? kWatchRounds : (int)(((long long)kWatchRounds << 21) / n);
+    return r > 8 ? r : 8;
+}
+constexpr int kSweepFlight = 8;         // vertices per lane in flight
+constexpr int kRoundFlight = 8;
+constexpr int kTailThreads = 512;       // one workgroup per CU
+constexpr int kTailPer = 2;
+
+// Removals of three rounds in rotation, hashed into 2^kLog bits each.  (Small
+// enough for every workgroup to stage a round's in a microsecond or two, and
+// large enough that setting its bits does not queue at a few lines: with a
+// second one of 2^12 bits, 30,000 removals a round cost 20 us.)
+struct WatchFilter {
+    static constexpr int kLog = 16;
+    static constexpr int kWords = 1 << (kLog - 5);
+    uint32_t* f;
+    __device__ __forceinline__ uint32_t* slot(int r) const { return f + (r % 3) * kWords; }
+    __device__ static __forceinline__ uint32_t hash(int v) {
+        return ((uint32_t)v * 0x9E3779B1u) >> (32 - kLog);
+    }
+    __device__ __forceinline__ void add(int r, int v) const {
+        const uint32_t h = hash(v);
+        atomicOr(slot(r) + (h >> 5), 1u << (h & 31));
+    }
+    // whether a filter of that many removals answers most tests
+    __device__ static __forceinline__ bool useful(int removed) { return removed <= kWords * 8; }
+};
+
+struct WatchState {
+    const int* row_off;
+    const int* col;
+    int n;
+    int* sup;         // support and kSupFirst, or -1: removed
+    uint64_t* rec;
+    uint32_t* dead;
+    WatchFilter flt;
+    int* ctr;
+    uint64_t* worker_edges;
+    int P;
+    int sched;
+};
+
+__device__ __forceinline__ int* rec_pos(uint64_t* rec, int v) {
+    return reinterpret_cast<int*>(rec + v) + 1;
+}
+__device__ __forceinline__ bool status_bit(const uint32_t* bm, int v) {
+    return __builtin_amdgcn_ubfe(bm[v >> 5], (unsigned)v, 1) != 0;
+}
+
+// A lane takes four vertices from one 16-byte load of the offsets when they
+// are aligned (`wide`), a wavefront 256, whose eight words it assembles.
+__global__ void watch_init(const int* row_off, int n, bool wide, const uint32_t* preset,
+                           uint32_t* y1, uint32_t* dead, WatchFilter flt, int* ctr,
+                           uint64_t* worker_edges, int P, trim_stats_t* stats) {
+    const int tid = blockIdx.x * blockDim.x + threadIdx.x;
+    const int stride = gridDim.x * blockDim.x;
+    if (tid < kCtrInts) ctr[tid] = 0;
+    for (int p = tid; p < P; p += stride) worker_edges[p] = 0;
+    if (stats && tid < (int)(sizeof(trim_stats_t) / 8)) ((uint64_t*)stats)[tid] = 0;
+    for (int i = tid; i < 3 * WatchFilter::kWords; i += stride) flt.f[i] = 0;
+    const int ngroups = (n + 3) >> 2, nwords = (n + 31) >> 5;
+    const int lane = lane_id(), waves = stride / kWave;
+    for (int g0 = (tid / kWave) * kWave; g0 < ngroups; g0 += waves * kWave) {
+        const int gi = g0 + lane, v = gi << 2;
+        uint32_t nib = 0;
+        if (wide && v + 4 <= n) {
+            typedef int v4i __attribute__((ext_vector_type(4)));
+            const v4i a = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(row_off) + gi);
+            const int e4 = __builtin_nontemporal_load(row_off + v + 4);
+            nib = (uint32_t)(a.x == a.y) | ((uint32_t)(a.y == a.z) << 1) |
+                  ((uint32_t)(a.z == a.w) << 2) | ((uint32_t)(a.w == e4) << 3);
+        } else {
+            for (int j = 0; j < 4 && v + j < n; ++j)
+                nib |= (uint32_t)(row_off[v + j] == row_off[v + j + 1]) << j;
+        }
+        uint32_t word = nib << (4 * (lane & 7));
+        word |= __shfl_xor(word, 1);
+        word |= __shfl_xor(word, 2);
+        word |= __shfl_xor(word, 4);
+        const int wi = (g0 >> 3) + (lane >> 3);
+        if ((lane & 7) == 0 && wi < nwords) {
+            if (preset) word |= preset[wi];
+            y1[wi] = word;
+            dead[wi] = word;
+        }
+    }
+}
+
+// kForest: jp and jlist as in ac6_sweep.  Otherwise the vertices without a
+// live successor are removed here (round 0).
+template <bool kForest>
+__global__ __launch_bounds__(1024) void watch_sweep(WatchState a, long long m, const uint32_t* y1,
+                                                    int* jp, uint32_t* jlist, uint64_t* part) {
+    constexpr int U = kSweepFlight;
+    __shared__ int s_wave[1024 / kWave], s_base;
+    __shared__ uint64_t red[16];
+    uint64_t edges = 0, removed = 0;
+    const int n = a.n, per = U * blockDim.x;
+    const int steps = (n + per - 1) / per;
+    for (int st = blockIdx.x; st < steps; st += gridDim.x) {
+        const int base = ((a.sched & TRIM_SCHED_REVERSE) ? steps - 1 - st : st) * per;
+        int b[U], e[U], p[U], w[U];
+        bool ok[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int v = base + k * blockDim.x + threadIdx.x, x = min(v, n - 1);
+            b[k] = __builtin_nontemporal_load(a.row_off + x);
+            e[k] = __builtin_nontemporal_load(a.row_off + x + 1);
+            ok[k] = v < n && !status_bit(y1, x);
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            if (!ok[k]) e[k] = b[k];   // removed already, or past the end
+            p[k] = b[k];
+            w[k] = ok[k] ? __builtin_nontemporal_load(a.col + b[k]) : 0;
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) ok[k] = !status_bit(y1, w[k]) && b[k] < e[k];
+        int c = 0;
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int v = base + k * blockDim.x + threadIdx.x;
+            if (b[k] < e[k] && !ok[k]) {   // the rare scan past removed vertices
+                for (++p[k]; p[k] < e[k]; ++p[k]) {
+                    w[k] = __builtin_nontemporal_load(a.col + p[k]);
+                    if (!status_bit(y1, w[k])) break;
+                }
+                ok[k] = p[k] < e[k];
+            }
+            if (ok[k]) {
+                edges += (uint64_t)(p[k] - b[k] + 1);
+                if (p[k] != b[k]) *rec_pos(a.rec, v) = p[k];
+            } else {
+                edges += (uint64_t)(e[k] - b[k]);
+            }
+            if (v < n) {
+                a.sup[v] = ok[k] ? (w[k] | (p[k] == b[k] ? kSupFirst : 0)) : -1;
+                if (kForest && b[k] < e[k])
+                    jp[v] = !ok[k] ? ~v : p[k] + 1 == e[k] ? w[k] : v;
+            }
+            if (kForest) {
+                c += b[k] < e[k] && (!ok[k] || p[k] + 1 == e[k]);
+            } else if (b[k] < e[k] && !ok[k]) {
+                atomicOr(a.dead + (v >> 5), 1u << (v & 31));
+                removed += 1;
+            }
+        }
+        if constexpr (kForest) {
+            int slot = block_append_base(c, a.ctr + kJCnt0, nullptr, s_wave, &s_base);
+#pragma unroll
+            for (int k = 0; k < U; ++k)
+                if (b[k] < e[k] && (!ok[k] || p[k] + 1 == e[k]))
+                    jlist[slot++] = (uint32_t)(base + k * (int)blockDim.x + (int)threadIdx.x) |
+                                    (ok[k] ? 0u : kRootBit);
+        }
+    }
+    edges = block_sum(edges, red);
+    if (!kForest) removed = block_sum(removed, red);
+    if (threadIdx.x == 0) {
+        if (edges) add_dev(a.worker_edges + (blockIdx.x % a.P), edges);
+        part[kPartSweep * kPartStride + blockIdx.x] = edges;
+        part[kPartDeg * kPartStride + blockIdx.x] = blockIdx.x == 0 ? (uint64_t)m : 0;
+        if (!kForest && removed) {
+            add_dev(a.ctr + kHyDead0, (int)removed);
+            add_dev(reinterpret_cast<uint64_t*>(a.ctr + kWatchCloses), removed);
+        }
+    }
+}
+
+// The forest collapse's removal of v (round 0).  No list is handed back.
+struct WatchKill {
+    int* sup;
+    uint32_t* dead;
+    __device__ __forceinline__ void operator()(int v, uint32_t (&)[kJumpItems]) const {
+        sup[v] = -1;
+        atomicOr(dead + (v >> 5), 1u << (v & 31));
+    }
+};
+
+// Removals of the round before round r (round 0: the sweep's and the forest's).
+__device__ __forceinline__ int removed_before(const int* ctr, int r) {
+    return ld_dev(ctr + kHyDead0 + (r - 1) % 3) + (r == 1 ? ld_dev(ctr + kJKilled) : 0);
+}
+
+struct WatchSums {
+    uint64_t edges = 0;
+    uint32_t closes = 0, joins = 0, visited = 0;
+};
+
+// The scan of v resumed after its removed support s: true with the position
+// and the target, or false.  kFresh: statuses are read past the L2.
+template <bool kFresh>
+__device__ __forceinline__ bool watch_scan(const WatchState& a, int v, int s, int& pos, int& to,
+                                           uint64_t& edges) {
+    constexpr int K = 4;
+    const int e = a.row_off[v + 1];
+    const int p0 = ((s & kSupFirst) ? a.row_off[v] : *rec_pos(a.rec, v)) + 1;
+    if (a.sched & TRIM_SCHED_JITTER) jitter_nap((uint64_t)v);
+    for (int p = p0; p < e; p += K) {
+        int w[K];
+        uint32_t x[K];
+#pragma unroll
+        for (int j = 0; j < K; ++j) w[j] = a.col[min(p + j, e - 1)];
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+            x[j] = kFresh ? ld_dev(a.dead + (w[j] >> 5)) : a.dead[w[j] >> 5];
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            if (p + j >= e || ((x[j] >> (w[j] & 31)) & 1u)) continue;
+            edges += (uint64_t)(p + j - p0 + 1);
+            pos = p + j;
+            to = w[j];
+            return true;
+        }
+    }
+    edges += (uint64_t)(e - p0);
+    return false;
+}
+
+// Round r over the thread's vertices; returns the removals.  sflt: the filter of
+// round r - 1 in LDS, or NULL.
+template <bool kFresh>
+__device__ __forceinline__ uint32_t watch_vertices(const WatchState& a, int r,
+                                                   const uint32_t* sflt, WatchSums& t) {
+    constexpr int U = kRoundFlight;
+    uint32_t removed = 0;
+    const int n = a.n, stride = gridDim.x * blockDim.x;
+    for (int base = blockIdx.x * blockDim.x + threadIdx.x; base < n; base += U * stride) {
+        int s[U];
+        bool back[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int v = base + k * stride;
+            s[k] = a.sup[v < n ? v : n - 1];
+            back[k] = v < n && s[k] >= 0;
+        }
+        if (sflt) {
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const uint32_t h = WatchFilter::hash(s[k] & kSupMask);
+                back[k] = back[k] && ((sflt[h >> 5] >> (h & 31)) & 1u);
+            }
+        }
+        uint32_t x[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int w = s[k] & kSupMask;
+            x[k] = 0;
+            if (back[k]) x[k] = kFresh ? ld_dev(a.dead + (w >> 5)) : a.dead[w >> 5];
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) back[k] = back[k] && ((x[k] >> (s[k] & 31)) & 1u);
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            if (!back[k]) continue;
+            const int v = base + k * stride;
+            int pos, to;
+            t.visited += 1;
+            if (watch_scan<kFresh>(a, v, s[k], pos, to, t.edges)) {
+                a.sup[v] = to;
+                *rec_pos(a.rec, v) = pos;
+                t.joins += 1;
+            } else {
+                a.sup[v] = -1;
+                atomicOr(a.dead + (v >> 5), 1u << (v & 31));
+                a.flt.add(r, v);
+                t.closes += 1;
+                removed += 1;
+            }
+        }
+    }
+    return removed;
+}
+
+// What a round leaves for the next: the filter slot of round r + 1 cleared (it
+// was last read by round r - 1), the counter after it, the round's removals.
+__device__ __forceinline__ void watch_round_end(const WatchState& a, int r, uint32_t removed,
+                                                uint64_t* red) {
+    uint32_t* f = a.flt.slot(r + 1);
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < WatchFilter::kWords;
+         i += gridDim.x * blockDim.x)
+        st_dev(f + i, 0u);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        st_dev(a.ctr + kHyDead0 + (r + 1) % 3, 0);
+        add_dev(a.ctr + kLvPhases, 1);
+    }
+    const uint64_t sum = block_sum(removed, red);
+    if (threadIdx.x == 0 && sum) add_dev(a.ctr + kHyDead0 + r % 3, (int)sum);
+}
+
+__device__ __forceinline__ void watch_sums(const WatchState& a, WatchSums& t, uint64_t* red) {
+    const uint64_t e = block_sum(t.edges, red);
+    const uint64_t x[3] = {block_sum(t.closes, red), block_sum(t.joins, red),
+                           block_sum(t.visited, red)};
+    if (threadIdx.x != 0) return;
+    if (e) add_dev(a.worker_edges + (blockIdx.x % a.P), e);
+    for (int i = 0; i < 3; ++i)
+        if (x[i]) add_dev(reinterpret_cast<uint64_t*>(a.ctr + kWatchCloses) + i, x[i]);
+}
+
+// The filter of round r - 1, which removed `removed`, into LDS; NULL when it is
+// of no use.
+template <int kThreads>
+__device__ __forceinline__ const uint32_t* watch_stage(const WatchState& a, int r, int removed,
+                                                       uint32_t* sflt) {
+    const bool use = WatchFilter::useful(removed);
+    if (use) {
+        constexpr int K = WatchFilter::kWords / 2 / kThreads;
+        static_assert(K * 2 * kThreads == WatchFilter::kWords, "");
+        const uint64_t* f = reinterpret_cast<const uint64_t*>(a.flt.slot(r - 1));
+        uint64_t x[K];   // all in flight at once: a load past the L2 takes 1 us
+#pragma unroll
+        for (int i = 0; i < K; ++i) x[i] = ld_dev(f + i * kThreads + threadIdx.x);
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+            reinterpret_cast<uint64_t*>(sflt)[i * kThreads + threadIdx.x] = x[i];
+    }
+    __syncthreads();
+    return use ? sflt : nullptr;
+}
+
+template <bool kFilter>
+__global__ __launch_bounds__(256) void watch_round(WatchState a, int r) {
+    __shared__ __align__(8) uint32_t sflt[kFilter ? WatchFilter::kWords : 2];
+    __shared__ uint64_t red[16];
+    if (ld_dev(a.ctr + kHyStop)) return;
+    const int before = removed_before(a.ctr, r);
+    if (before == 0) {   // the fixed point; workgroup 0 tells the later launches
+        if (blockIdx.x == 0 && threadIdx.x == 0) st_dev(a.ctr + kHyStop, 1);
+        return;
+    }
+    WatchSums t;
+    const uint32_t removed =
+        watch_vertices<false>(a, r, kFilter ? watch_stage<256>(a, r, before, sflt) : nullptr, t);
+    watch_round_end(a, r, removed, red);
+    watch_sums(a, t, red);
+}
+
+// Rounds r0 .. watch_rounds(n) in one launch of at most one workgroup per CU, all
+// resident at once.  A vertex is the same thread's in every round.
+__global__ __launch_bounds__(kTailThreads) void watch_tail(WatchState a, int r0, int last,
+                                                          int budget) {
+    __shared__ __align__(8) uint32_t sflt[WatchFilter::kWords];
+    __shared__ uint64_t red[16];
+    if (ld_dev(a.ctr + kHyStop)) return;
+    WatchSums t;
+    int r = r0;
+    for (;; ++r) {
+        const int before = removed_before(a.ctr, r);
+        if (before == 0) {
+            if (blockIdx.x == 0 && threadIdx.x == 0) st_dev(a.ctr + kHyStop, 1);
+            break;
+        }
+        if (r > last) break;
+        const uint32_t removed =
+            watch_vertices<true>(a, r, watch_stage<kTailThreads>(a, r, before, sflt), t);
+        watch_round_end(a, r, removed, red);
+        if (!grid_barrier(a.ctr + kBarCount, a.ctr + kBarGen, a.ctr + kStall, budget)) break;
+    }
+    watch_sums(a, t, red);
+}
+
+// Without a fixed point after watch_rounds(n) rounds: the lists' heads.
+__global__ void watch_heads(const uint32_t* dead, int n, int* head, int* ext, const int* ctr) {
+    if (ld_dev(ctr + kHyStop)) return;
+    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x) {
+        const int h = status_bit(dead, v) ? kDead : kEmpty;
+        reinterpret_cast<int2*>(head)[v] = make_int2(h, h);
+        if (ext)
+            for (int j = 0; j < kMoreLists - 1; ++j) ext[(kMoreLists - 1) * (long long)v + j] = h;
+    }
+}
+
+// Every vertex left joins the list of its support, those whose support the last
+// round removed that of the next live successor; those without one become close
+// items.  Nothing is closed while this runs, so joining is a plain exchange.
+__global__ __launch_bounds__(256) void watch_register(WatchState a, int* head, int* ext,
+                                                      uint32_t* q) {
+    constexpr int U = 4;
+    __shared__ int s_wave[256 / kWave], s_base;
+    __shared__ uint64_t red[16];
+    if (ld_dev(a.ctr + kHyStop)) return;
+    WatchSums t;
+    const int n = a.n, step = gridDim.x * blockDim.x * U;
+    for (int base = blockIdx.x * blockDim.x * U; base < n; base += step) {
+        int s[U], p[U], w[U], old[U], c = 0;
+        bool lost[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int v = base + k * blockDim.x + threadIdx.x;
+            s[k] = v < n ? a.sup[v] : -1;
+            lost[k] = false;
+            if (s[k] < 0) continue;
+            w[k] = s[k] & kSupMask;
+            p[k] = (s[k] & kSupFirst) ? a.row_off[v] : *rec_pos(a.rec, v);
+            if (status_bit(a.dead, w[k])) {
+                t.visited += 1;
+                if (watch_scan<false>(a, v, s[k], p[k], w[k], t.edges)) {
+                    t.joins += 1;
+                } else {
+                    lost[k] = true;
+                    s[k] = -1;
+                    c += 1;
+                }
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int v = base + k * blockDim.x + threadIdx.x;
+            if (s[k] >= 0)
+                old[k] = xchg_dev(join_slot(head, ext, w[k], p[k] + 1 == a.row_off[v + 1], v), v);
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+            if (s[k] >= 0) a.rec[base + k * blockDim.x + threadIdx.x] = pack_rec(old[k], p[k]);
+        int slot = block_append_base(c, a.ctr + kQTail, a.ctr + kPending, s_wave, &s_base);
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+            if (lost[k]) q[slot++] = make_item(0, base + k * blockDim.x + threadIdx.x);
+    }
+    watch_sums(a, t, red);
+}
+
+}  // namespace
+
+}  // namespace trim

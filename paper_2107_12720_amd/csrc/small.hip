@@ -293,12 +293,12 @@ int small_block(int n) {
 }  // namespace
 
 // Where the line lies, one workgroup against the device-wide path, us a call:
-// core+tail of 1,000 vertices 37 / 253, 10,000 94 / 699, 32,768 172 / 379,
-// 65,536 308 / 389 (its LDS holds no more supports); R-MAT scale 12 18 / 72,
-// 16 46 / 78, with a chain 77 / 148.  The edge limit keeps graphs of long lists
-// away, whose scans one compute unit would run slowly; at it (uniform, 60,000
-// vertices, 2^21 edges) 29 / 60, and a tail of 30 successors a vertex (60,000
-// vertices, 1.26 * 10^6 edges), nearly all of them removed, 2,845 / 2,937.
+// core+tail of 17,000 vertices 125 / 223, 32,768 172 / 249, 50,000 257 / 263,
+// 65,536 312 / 272 (its LDS holds no more supports); R-MAT scale 15 29 / 57,
+// 16 47 / 58, with a chain 76 / 91; uniform of 65,536 vertices and mean degree
+// 1.1 333 / 474.  The edge limit keeps graphs of long lists away, whose scans one
+// compute unit runs slowly: tails of 30 successors a vertex, nearly all of them
+// removed, take 915 / 1,430 with 17,000 vertices, 2,958 / 1,510 with 65,536.
 bool ac6_small_ok(long long n, long long m, int rounds) {
     return rounds < 2 && n <= kWatchLdsN && m <= kSmallMaxM;
 }

@@ -38,9 +38,15 @@ enum Ctr : int {
     kHyStop = 100,
     kHyRounds = 101,
     kHyWork = 102,   // uint64 (words 102 and 103, 8-byte aligned)
+    // AC-6 by watched supports (ac6_watch.h): closes, joins and hand-backs of
+    // its rounds, uint64 each
+    kWatchCloses = 44,
+    kWatchJoins = 46,
+    kWatchVisited = 48,
     kCtrInts = 256
 };
 
+static_assert(kWatchCloses % 2 == 0, "64-bit counters need 8-byte aligned words");
 static_assert(kHyWork % 2 == 0, "the 64-bit re-check counter needs an 8-byte aligned word");
 
 // Working memory of one call, sized for n vertices (owned by trim_ctx).

@@ -1,6 +1,8 @@
 // Output and statistics kernels shared by the three propagation schemes: the
 // live bitmap and the reduction of per-block partial sums into trim_stats_t.
 #pragma once
+#include <cstddef>
+
 #include "trim_device.h"
 
 namespace trim {
@@ -8,6 +10,11 @@ namespace trim {
 // ---------------------------------------------------- outputs and statistics
 // Per-block partial sums live in `part` (kPartStride words per quantity); one
 // finalize block reduces them, so no word is updated by every block.
+
+static_assert(offsetof(trim_stats_t, rounds) == 24 && offsetof(trim_stats_t, queued) == 32 &&
+              offsetof(trim_stats_t, visited) == 64 && offsetof(trim_stats_t, edges_live) == 88 &&
+              offsetof(trim_stats_t, phases) == 128 && offsetof(trim_stats_t, rechecks) == 136 &&
+              sizeof(trim_stats_t) == 144, "finalize_stats writes the words in this order");
 
 namespace {   // kernels below get a private copy in every translation unit
 
@@ -93,31 +100,55 @@ __global__ void finalize_stats(int n, int P, int n_sweep, int n_prop, int n_pack
         if (lane_id() == 0) red[q][w] = x;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint64_t tot[kN] = {};
-        for (int q = 0; q < kN; ++q)
-            for (int i = 0; i < nw; ++i)
-                tot[q] = q == kQhw ? (red[q][i] > tot[q] ? red[q][i] : tot[q]) : tot[q] + red[q][i];
-        stats->edges_total = tot[kEdges];
-        stats->n_live = tot[kLive];
-        stats->n_dead = (uint64_t)n - tot[kLive];
-        stats->queued = (uint64_t)ctr[kQTail];
-        stats->edges_sweep = tot[kSweep];
-        stats->closes = tot[kCloses];
-        stats->joins = tot[kJoins];
-        stats->visited = tot[kVisited];
-        stats->graph_edges = tot[kDeg];
-        stats->q_highwater = tot[kQhw];
-        stats->edges_live = tot[kLiveE];
-        stats->stalled = ld_dev(ctr + kStall) != 0;
-        stats->forest = (uint64_t)ld_dev(ctr + kJKilled);
-        stats->jump_rounds = (uint64_t)ld_dev(ctr + kJRounds);
-        stats->work_items = (uint64_t)(uint32_t)ld_dev(ctr + kJWork) +
-                            (uint64_t)(uint32_t)ld_dev(ctr + kAcWork);
-        stats->phases = (uint64_t)ld_dev(ctr + kLvPhases);
-        stats->rechecks = ld_dev(reinterpret_cast<const uint64_t*>(ctr + kHyWork));
-        if (ld_dev(ctr + kHyRounds)) stats->rounds = (uint64_t)ld_dev(ctr + kHyRounds);
-        if (n == 0 && empty_rounds) stats->rounds = (uint64_t)empty_rounds;
+    // one lane per quantity, then one per word of the result: a single thread
+    // took 9 us for the same
+    __shared__ uint64_t tot[kN];
+    if (threadIdx.x < kN) {
+        const int q = threadIdx.x;
+        uint64_t t = 0;
+        for (int i = 0; i < nw; ++i) {
+            const uint64_t x = red[q][i];
+            t = q == kQhw ? (x > t ? x : t) : t + x;
+        }
+        tot[q] = t;
+    }
+    __syncthreads();
+    constexpr int kWords = sizeof(trim_stats_t) / 8;
+    if (threadIdx.x < kWords) {
+        // each lane picks its sum and its counters, then all load at once
+        int q = -1, c0 = -1, c1 = -1;
+        bool wide = false;
+        switch (threadIdx.x) {   // in the order of trim_stats_t
+            case 0: q = kEdges; break;
+            case 1: case 2: q = kLive; break;
+            case 3: c0 = kHyRounds; break;
+            case 4: c0 = kQTail; break;
+            case 5: q = kSweep; break;
+            // with what the rounds over watched supports counted
+            case 6: q = kCloses; c0 = kWatchCloses; wide = true; break;
+            case 7: q = kJoins; c0 = kWatchJoins; wide = true; break;
+            case 8: q = kVisited; c0 = kWatchVisited; wide = true; break;
+            case 9: q = kDeg; break;
+            case 10: q = kQhw; break;
+            case 11: q = kLiveE; break;
+            case 12: c0 = kStall; break;
+            case 13: c0 = kJKilled; break;
+            case 14: c0 = kJRounds; break;
+            case 15: c0 = kJWork; c1 = kAcWork; break;
+            case 16: c0 = kLvPhases; break;
+            default: c0 = kHyWork; wide = true; break;
+        }
+        const uint32_t lo = (uint32_t)ld_dev(ctr + (c0 < 0 ? 0 : c0));
+        const uint32_t hi = (uint32_t)ld_dev(ctr + (c0 < 0 ? 0 : c0 + 1));
+        const uint32_t lo1 = (uint32_t)ld_dev(ctr + (c1 < 0 ? 0 : c1));
+        const uint64_t had = stats->rounds;   // as the rounds kernels left it
+        uint64_t x = q < 0 ? 0 : tot[q];
+        if (c0 >= 0) x += ((uint64_t)(wide ? hi : 0u) << 32) | lo;
+        if (c1 >= 0) x += lo1;
+        if (threadIdx.x == 2) x = (uint64_t)n - x;
+        if (threadIdx.x == 3) x = n == 0 && empty_rounds ? (uint64_t)empty_rounds : x ? x : had;
+        if (threadIdx.x == 12) x = x != 0;
+        reinterpret_cast<uint64_t*>(stats)[threadIdx.x] = x;
     }
 }
 

@@ -62,9 +62,8 @@
 //                  kHops removals in a row.  Exits when no item is pending.
 //   ac6_pack       live bitmap by wavefront ballot, live/dead counts.
 //
-// These serve the implicit graph, batches of graphs too large for a workgroup,
-// explicit graphs with late registration and the fixed-memory entry point.
-// Other explicit graphs go to one workgroup (small.hip) or to the rounds over
+// These serve the implicit graph, batches of graphs too large for a workgroup
+// and the fixed-memory entry point.  Other explicit graphs go to one workgroup (small.hip) or to the rounds over
 // watched supports (ac6_watch.h), which end in the kernels above when a graph
 // is too deep for them.
 #include "trim_device.h"
@@ -170,54 +169,6 @@ __global__ void ac6_init(View g, int n, int* head, int* ext, uint32_t* sinks, ui
                 sinks2[v >> 5] = (uint32_t)m;
                 sinks2[(v >> 5) + 1] = (uint32_t)(m >> 32);
             }
-        }
-    }
-}
-
-// The init of late registration on an explicit graph: no list heads, only
-// the two round bitmaps of the sinks.  A lane takes four consecutive vertices
-// from one 16-byte load of the offsets (and the next offset), a wavefront 256
-// vertices, whose eight bitmap words it assembles by shuffles.  Offsets that
-// are not 16-byte aligned take the one-vertex-per-lane path of ac6_init.
-__global__ void ac6_init_bits(const int* row_off, int n, uint32_t* y1, uint32_t* y0, int* ctr,
-                              uint64_t* worker_edges, int P, trim_stats_t* stats,
-                              RoundFilter flt) {
-    const int tid = blockIdx.x * blockDim.x + threadIdx.x;
-    const int stride = gridDim.x * blockDim.x;
-    if (tid < kCtrInts) ctr[tid] = tid == kHyRounds ? 1 : 0;
-    for (int p = tid; p < P; p += stride) worker_edges[p] = 0;
-    if (stats && tid < (int)(sizeof(trim_stats_t) / 8)) ((uint64_t*)stats)[tid] = 0;
-    if (flt.f)
-        for (int i = tid; i < 2 * flt.words(); i += stride) flt.slot(1)[i] = 0;
-    const int ngroups = (n + 3) >> 2;   // groups of four vertices
-    const int nwords = (n + 31) >> 5;
-    const int lane = lane_id();
-    const int waves = stride / kWave;
-    for (int g0 = (tid / kWave) * kWave; g0 < ngroups; g0 += waves * kWave) {
-        const int gi = g0 + lane;
-        uint32_t nib = 0;
-        if (gi < ngroups) {
-            const int v = gi << 2;
-            if (v + 4 <= n) {
-                typedef int v4i __attribute__((ext_vector_type(4)));
-                const v4i a = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(row_off) + gi);
-                const int e4 = __builtin_nontemporal_load(row_off + v + 4);
-                nib = (uint32_t)(a.x == a.y) | ((uint32_t)(a.y == a.z) << 1) |
-                      ((uint32_t)(a.z == a.w) << 2) | ((uint32_t)(a.w == e4) << 3);
-            } else {
-                for (int j = 0; v + j < n; ++j)
-                    nib |= (uint32_t)(row_off[v + j] == row_off[v + j + 1]) << j;
-            }
-        }
-        // word (g0 / 8 + lane / 8) holds the nibbles of lanes 8k .. 8k + 7
-        uint32_t word = nib << (4 * (lane & 7));
-        word |= __shfl_xor(word, 1);
-        word |= __shfl_xor(word, 2);
-        word |= __shfl_xor(word, 4);
-        const int wi = (g0 >> 3) + (lane >> 3);
-        if ((lane & 7) == 0 && wi < nwords) {
-            y1[wi] = word;
-            y0[wi] = word;
         }
     }
 }
@@ -1122,19 +1073,6 @@ inline int grid_for(long long n, int block, int max_blocks = 1 << 20) {
     return (int)b;
 }
 
-// Which views take ac6_init_bits: explicit graphs whose offsets are 16-byte
-// aligned (the caller's pointer; torch allocations are).
-template <class View>
-struct InitBits {
-    static bool ok(const View&) { return false; }
-    static const int* row_off(const View&) { return nullptr; }
-};
-template <>
-struct InitBits<ExplicitView> {
-    static bool ok(const ExplicitView& g) { return ((uintptr_t)g.row_off & 15) == 0; }
-    static const int* row_off(const ExplicitView& g) { return g.row_off; }
-};
-
 // Words from the first round bitmap to the second (both in w.c, which holds
 // n + n / 8 + 64 ints): room for ceil(n / 32) words plus the one past the end
 // that ac6_init may write, aligned to a cache line.
@@ -1180,15 +1118,9 @@ hipError_t ac6_run(View g, int n, const Work& w, const LaunchCfg& lc, uint32_t* 
     }
     {
         Timed t(lc, "ac6_init");
-        if (defer && InitBits<View>::ok(g))
-            hipLaunchKernelGGL(ac6_init_bits, dim3(grid_for((n + 3) / 4, 256, 16384)), dim3(256),
-                               0, lc.stream, InitBits<View>::row_off(g), n, y[1], y[0], w.ctr,
-                               worker_edges, P, stats, flt);
-        else
-            hipLaunchKernelGGL(ac6_init<View>, dim3(grid_for(n, 256, 16384)), dim3(256), 0,
-                               lc.stream, g, n, defer ? nullptr : w.a, ext, y[1],
-                               defer ? y[0] : nullptr, preset, w.ctr, worker_edges, P, stats,
-                               flt);
+        hipLaunchKernelGGL(ac6_init<View>, dim3(grid_for(n, 256, 16384)), dim3(256), 0, lc.stream,
+                           g, n, defer ? nullptr : w.a, ext, y[1], defer ? y[0] : nullptr, preset,
+                           w.ctr, worker_edges, P, stats, flt);
     }
     if (n > 0) {
         const int chunk = sweep_chunk(lc, n, B);
@@ -1274,12 +1206,16 @@ hipError_t ac6_run(View g, int n, const Work& w, const LaunchCfg& lc, uint32_t* 
 
 // Watched supports serve every explicit graph that one workgroup does not take
 // (small.hip): against lists from the first sweep on, core+tail graphs of 10^5
-// vertices take 266 / 402 us, of 2^21 762 / 764, R-MAT of edge factor 16 and
-// 2^22 vertices 190 / 350, 2^24 480 / 890, uniform ones of mean degree 1.1 and
-// 2^20 vertices 828 / 850.  Below this size (graphs of too many edges for one
+// vertices take 266 / 403 us, of 2^21 653 / 765, R-MAT of edge factor 4 and 2^22
+// vertices 146 / 279, uniform ones of mean degree 1.1 and 2^20 vertices 776 / 842,
+// 2^22 1,288 / 1,414.  With late registration against a round list registered
+// after R rounds, R = 2 and 8: R-MAT 22 168 / 353 and 135 / 161 us, with a chain
+// of 2,000 234 / 404 and 325 / 562, core+tail of 2^20 482 / 585 and 484 / 666;
+// R-MAT 15 43 / 83 and 53 / 56.  Without it, below this size (graphs of too many edges for one
 // workgroup) the lists stay: their place must hold the filters.
 constexpr int kWatchMinN = 4096;
-static_assert(2LL * kWatchMinN >= 3 * WatchFilter::kWords, "the filters fit");
+static_assert(2 * kWatchMinN >= 3 << (WatchFilter::log_for(kWatchMinN) - 5) &&
+              2LL << 20 >= 3 * WatchFilter::kMaxWords, "the filters fit");
 
 // The device-wide path for explicit graphs: supports watched, lists only for a
 // deep remainder (ac6_watch.h).
@@ -1288,29 +1224,46 @@ hipError_t ac6_watch_run(const trim_csr_t& g, const Work& w, const LaunchCfg& lc
     const int n = g.n, P = lc.workers, B = lc.block;
     hipStream_t st = lc.stream;
     int* ext = (w.ext && n <= kSplitMaxN) ? w.ext : nullptr;
-    uint32_t* y1 = reinterpret_cast<uint32_t*>(w.c);
-    uint32_t* dead = y1 + round_bitmap_offset(n);
-    // the filters lie where the heads will, which are made last if at all
-    const WatchFilter flt{reinterpret_cast<uint32_t*>(w.a)};
+    // late registration: R counted rounds; round r reads y[r & 1] and builds the
+    // other bitmap (round 1 is the sweep), what follows goes on in round R's
+    const int R = lc.rounds >= 2 ? lc.rounds : 0;
+    uint32_t* y[2];
+    y[1] = reinterpret_cast<uint32_t*>(w.c);
+    y[0] = y[1] + round_bitmap_offset(n);
+    uint32_t* dead = R ? y[(R + 1) & 1] : y[0];
+    // the filters lie behind the round list or where the heads will, which are
+    // made last if at all
+    const WatchFilter flt{reinterpret_cast<uint32_t*>(R ? w.hl + 2 * w.hcap : w.a),
+                          WatchFilter::log_for(n)};
     const WatchState a{g.row_off, g.col, n, w.d, w.b, dead, flt, w.ctr, worker_edges, P,
-                       lc.schedule};
+                       lc.schedule, R + 1, lc.forest};
+    WatchState a1 = a;
+    a1.dead = y[0];
     const ExplicitView v{g.row_off, g.col};
     const int level_blocks = phase_blocks(n, lc.cus);
     const int sweep_blocks = grid_for(n, (long long)B * kSweepFlight, lc.cus * 8);
     {
         Timed t(lc, "ac6_init");
         hipLaunchKernelGGL(watch_init, dim3(grid_for((n + 3) / 4, 256, 16384)), dim3(256), 0, st,
-                           g.row_off, n, ((uintptr_t)g.row_off & 15) == 0, preset, y1, dead, flt,
-                           w.ctr, worker_edges, P, stats);
+                           g.row_off, n, ((uintptr_t)g.row_off & 15) == 0, preset, y[1], y[0],
+                           flt, w.ctr, worker_edges, P, stats, R != 0);
     }
     {
         Timed t(lc, "ac6_sweep");
+        const auto sweep = R           ? watch_sweep<kWatchCounted>
+                           : lc.forest ? watch_sweep<kWatchForest>
+                                       : watch_sweep<kWatchStep>;
+        hipLaunchKernelGGL(sweep, dim3(sweep_blocks), dim3(B), 0, st, a1, (long long)g.m, y[1],
+                           w.jp, w.e, w.part);
+    }
+    const int rb = grid_for(n, (long long)kRoundThreads * kRoundFlight, lc.cus * 2);
+    if (R) {
+        Timed t(lc, "ac6_counted");
+        for (int r = 2; r <= R; ++r)
+            hipLaunchKernelGGL(watch_counted, dim3(rb), dim3(kRoundThreads), 0, st, a, r, y[r & 1],
+                               y[(r + 1) & 1]);
         if (lc.forest)
-            hipLaunchKernelGGL(watch_sweep<true>, dim3(sweep_blocks), dim3(B), 0, st, a,
-                               (long long)g.m, y1, w.jp, w.e, w.part);
-        else
-            hipLaunchKernelGGL(watch_sweep<false>, dim3(sweep_blocks), dim3(B), 0, st, a,
-                               (long long)g.m, y1, (int*)nullptr, (uint32_t*)nullptr, w.part);
+            hipLaunchKernelGGL(watch_collect, dim3(sweep_blocks), dim3(B), 0, st, a, w.jp, w.e);
     }
     if (lc.forest) {
         Timed t(lc, "ac6_jump");
@@ -1320,23 +1273,20 @@ hipError_t ac6_watch_run(const trim_csr_t& g, const Work& w, const LaunchCfg& lc
     }
     {
         Timed t(lc, "ac6_rounds");
-        const int rb = grid_for(n, 256LL * kRoundFlight, lc.cus * 8);
         // a launch starts with clean caches, so the statuses themselves are
         // probed as long as the L2s hold most of them
-        for (int r = 1; r <= kRoundLaunches; ++r)
-            if (r > 1 && n > kSplitMaxN)
-                hipLaunchKernelGGL(watch_round<true>, dim3(rb), dim3(256), 0, st, a, r);
+        for (int r = a.r1; r < a.r1 + round_launches(n); ++r)
+            if (r > a.r1 && n > kSplitMaxN)
+                hipLaunchKernelGGL(watch_round<true>, dim3(rb), dim3(kRoundThreads), 0, st, a, r);
             else
-                hipLaunchKernelGGL(watch_round<false>, dim3(rb), dim3(256), 0, st, a, r);
+                hipLaunchKernelGGL(watch_round<false>, dim3(rb), dim3(kRoundThreads), 0, st, a, r);
         hipLaunchKernelGGL(watch_tail,
-                           dim3(grid_for(n, (long long)kTailThreads * kTailPer, lc.cus)),
-                           dim3(kTailThreads), 0, st, a, kRoundLaunches + 1, watch_rounds(n),
-                           lc.budget);
+                           dim3(grid_for(n, (long long)kRoundThreads * kTailPer, lc.cus)),
+                           dim3(kRoundThreads), 0, st, a, a.r1 + round_launches(n),
+                           R + watch_rounds(n), w.a, ext, lc.budget);
     }
     {
         Timed t(lc, "ac6_register");
-        hipLaunchKernelGGL(watch_heads, dim3(grid_for(n, 1024, lc.cus * 8)), dim3(256), 0, st, dead,
-                           n, w.a, ext, w.ctr);
         hipLaunchKernelGGL(watch_register, dim3(grid_for(n, 1024, lc.cus * 8)), dim3(256), 0, st, a,
                            w.a, ext, w.q);
     }
@@ -1372,7 +1322,7 @@ hipError_t ac6_csr(const trim_csr_t& g, const Work& w, const LaunchCfg& lc, uint
     if (ac6_small_ok(g.n, g.m, lc.rounds))
         return ac6_small_csr(g, w, lc, bitmap, worker_edges, stats, preset);
     // (w.d: the fixed array of trim_csr_noalloc has no place for the supports)
-    if (lc.rounds < 2 && w.d && g.n > kWatchMinN)
+    if (w.d && (lc.rounds >= 2 ? g.n > 0 : g.n > kWatchMinN))
         return ac6_watch_run(g, w, lc, bitmap, worker_edges, stats, preset);
     ExplicitView v{g.row_off, g.col};
     return ac6_run(v, g.n, w, lc, bitmap, worker_edges, stats, nullptr, nullptr, 0, preset);

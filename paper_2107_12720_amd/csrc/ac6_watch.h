@@ -14,23 +14,27 @@
 //   watch_sweep   DoPost of every vertex; supports in sup[], positions in the
 //                 high halves of rec[] where they are not the first, links and
 //                 members for the forest collapse;
+//   watch_counted, watch_collect
+//                 (late registration, opts.rounds >= 2) the counted rounds, then
+//                 the forest's links and members from the supports left;
 //   ac6_jump      the forest collapse (forest_jump.h), setting statuses;
 //   watch_round   one round: vertices whose support was removed resume their
-//                 scans.  kRoundLaunches launches; a round that removes nothing
-//                 is the last, and what follows returns at once;
+//                 scans.  round_launches(n) launches; a round that removes
+//                 nothing is the last, and what follows returns at once;
 //   watch_tail    further rounds in one launch with grid barriers, up to
-//                 watch_rounds(n) rounds in all;
-//   watch_heads, watch_register
-//                 if that did not end it (a deep, narrow remainder): list heads
-//                 from the statuses, every vertex left joins its support's
-//                 list, and the propagation over lists finishes.
+//                 watch_rounds(n) rounds in all; then the list heads;
+//   watch_register
+//                 if that did not end it (a deep, narrow remainder): every
+//                 vertex left joins its support's list, and the propagation
+//                 over lists finishes.
 //
 // What bounds it: the sweep by its gathers of row_off, col and statuses (67 us
 // for R-MAT 22, edge factor 16, 200 with the exchanges), a round of all vertices
 // by reading sup (12 us at 2^22) and by the latency of four dependent loads,
 // about 5 us, plus 2 for the barrier in the tail.  R-MAT 22 with a chain of
-// 2*10^5: 524 -> 314 us in all; 24 without: 910 -> 480; core+tail of 10^5
-// vertices 402 -> 266, of 2^20 564 -> 473.
+// 2*10^5: 494 -> 260 us in all; core+tail of 10^5 vertices 402 -> 266, of 2^20
+// 564 -> 455.  Late registration, R-MAT 26 with four counted rounds, whose fourth
+// removes 1 vertex: 2.85 -> 1.33 ms (5 * 10^7 list exchanges took 2.65).
 //
 // Filters: a support that was live before round r - 1 is removed before round
 // r iff round r - 1 removed it.  While those removals are few, a round tests a
@@ -51,42 +55,52 @@ namespace {
 
 constexpr int kSupFirst = 1 << 29;      // sup[]: the support is the first successor
 constexpr int kSupMask = kSupFirst - 1;
-constexpr int kRoundLaunches = 4;
+// Small graphs: one (a launch that has nothing to do takes 2 us, and the tail's
+// rounds are as fast).
+constexpr int round_launches(int n) { return n <= (1 << 18) ? 1 : 4; }
 constexpr int kWatchRounds = 64;
 // Rounds before the vertices left are registered in lists.  A round of the tail
 // takes 6 to 9 us up to 2^20 vertices and 19 at 2^22, a phase over lists 5 (one
 // removal) to 60 (thousands), registering 50 and 170.  Core+tail graphs of mean
-// degree 30 and 2^20 vertices (some 60 rounds) take 2.5 ms with 64 rounds, 3.1
-// with 40; with lists alone 3.8.  66 rounds of one removal each, the worst case,
-// take 0.68 ms, with lists alone 0.46.
+// degree 30 and 2^20 vertices (some 60 rounds) take 2.2 ms with 64 rounds, with
+// lists alone 3.8 (a limit of 40 cost 0.5 more).  66 rounds of one removal each,
+// the worst case, take 0.69 ms, with lists alone 0.46.
 constexpr int watch_rounds(int n) {
     const int r = n <= (1 << 21) ? kWatchRounds : (int)(((long long)kWatchRounds << 21) / n);
     return r > 8 ? r : 8;
 }
 constexpr int kSweepFlight = 8;         // vertices per lane in flight
 constexpr int kRoundFlight = 8;
-constexpr int kTailThreads = 512;       // one workgroup per CU
+constexpr int kRoundThreads = 512;      // the tail: one workgroup per CU
 constexpr int kTailPer = 2;
 
-// Removals of three rounds in rotation, hashed into 2^kLog bits each.  (Small
+// Removals of three rounds in rotation, hashed into 2^log bits each.  (Small
 // enough for every workgroup to stage a round's in a microsecond or two, and
 // large enough that setting its bits does not queue at a few lines: with a
 // second one of 2^12 bits, 30,000 removals a round cost 20 us.)
 struct WatchFilter {
-    static constexpr int kLog = 16;
-    static constexpr int kWords = 1 << (kLog - 5);
+    static constexpr int kMaxWords = 1 << (18 - 5);
     uint32_t* f;
-    __device__ __forceinline__ uint32_t* slot(int r) const { return f + (r % 3) * kWords; }
-    __device__ static __forceinline__ uint32_t hash(int v) {
-        return ((uint32_t)v * 0x9E3779B1u) >> (32 - kLog);
+    int log;
+    // graphs whose statuses cost more to read get a filter of more removals
+    __host__ __device__ static constexpr int log_for(int n) { return n <= (1 << 20) ? 16 : 18; }
+    __device__ __forceinline__ int words() const { return 1 << (log - 5); }
+    __device__ __forceinline__ uint32_t* slot(int r) const { return f + (r % 3) * words(); }
+    __device__ __forceinline__ uint32_t hash(int v) const {
+        return ((uint32_t)v * 0x9E3779B1u) >> (32 - log);
     }
     __device__ __forceinline__ void add(int r, int v) const {
         const uint32_t h = hash(v);
         atomicOr(slot(r) + (h >> 5), 1u << (h & 31));
     }
     // whether a filter of that many removals answers most tests
-    __device__ static __forceinline__ bool useful(int removed) { return removed <= kWords * 8; }
+    __device__ __forceinline__ bool useful(int removed) const { return removed <= words() * 8; }
 };
+
+// How the first sweep records a vertex without a live successor: it is removed
+// by the propagation (round 0), by the forest collapse, or by the first of the
+// counted rounds of late registration.
+enum WatchMode { kWatchStep, kWatchForest, kWatchCounted };
 
 struct WatchState {
     const int* row_off;
@@ -100,6 +114,8 @@ struct WatchState {
     uint64_t* worker_edges;
     int P;
     int sched;
+    int r1;           // the first round of the propagation: 1, after R counted ones R + 1
+    bool forest;
 };
 
 __device__ __forceinline__ int* rec_pos(uint64_t* rec, int v) {
@@ -113,13 +129,13 @@ __device__ __forceinline__ bool status_bit(const uint32_t* bm, int v) {
 // are aligned (`wide`), a wavefront 256, whose eight words it assembles.
 __global__ void watch_init(const int* row_off, int n, bool wide, const uint32_t* preset,
                            uint32_t* y1, uint32_t* dead, WatchFilter flt, int* ctr,
-                           uint64_t* worker_edges, int P, trim_stats_t* stats) {
+                           uint64_t* worker_edges, int P, trim_stats_t* stats, bool counted) {
     const int tid = blockIdx.x * blockDim.x + threadIdx.x;
     const int stride = gridDim.x * blockDim.x;
-    if (tid < kCtrInts) ctr[tid] = 0;
+    if (tid < kCtrInts) ctr[tid] = counted && tid == kHyRounds ? 1 : 0;
     for (int p = tid; p < P; p += stride) worker_edges[p] = 0;
     if (stats && tid < (int)(sizeof(trim_stats_t) / 8)) ((uint64_t*)stats)[tid] = 0;
-    for (int i = tid; i < 3 * WatchFilter::kWords; i += stride) flt.f[i] = 0;
+    for (int i = tid; i < 3 * flt.words(); i += stride) flt.f[i] = 0;
     const int ngroups = (n + 3) >> 2, nwords = (n + 31) >> 5;
     const int lane = lane_id(), waves = stride / kWave;
     for (int g0 = (tid / kWave) * kWave; g0 < ngroups; g0 += waves * kWave) {
@@ -148,12 +164,13 @@ __global__ void watch_init(const int* row_off, int n, bool wide, const uint32_t*
     }
 }
 
-// kForest: jp and jlist as in ac6_sweep.  Otherwise the vertices without a
-// live successor are removed here (round 0).
-template <bool kForest>
+// kWatchForest: jp and jlist as in ac6_sweep.  Otherwise the vertices without a
+// live successor are removed here.
+template <WatchMode kMode>
 __global__ __launch_bounds__(1024) void watch_sweep(WatchState a, long long m, const uint32_t* y1,
                                                     int* jp, uint32_t* jlist, uint64_t* part) {
     constexpr int U = kSweepFlight;
+    constexpr bool kForest = kMode == kWatchForest;
     __shared__ int s_wave[1024 / kWave], s_base;
     __shared__ uint64_t red[16];
     uint64_t edges = 0, removed = 0;
@@ -204,6 +221,7 @@ __global__ __launch_bounds__(1024) void watch_sweep(WatchState a, long long m, c
                 c += b[k] < e[k] && (!ok[k] || p[k] + 1 == e[k]);
             } else if (b[k] < e[k] && !ok[k]) {
                 atomicOr(a.dead + (v >> 5), 1u << (v & 31));
+                if (kMode == kWatchCounted) a.flt.add(1, v);
                 removed += 1;
             }
         }
@@ -223,8 +241,9 @@ __global__ __launch_bounds__(1024) void watch_sweep(WatchState a, long long m, c
         part[kPartSweep * kPartStride + blockIdx.x] = edges;
         part[kPartDeg * kPartStride + blockIdx.x] = blockIdx.x == 0 ? (uint64_t)m : 0;
         if (!kForest && removed) {
-            add_dev(a.ctr + kHyDead0, (int)removed);
-            add_dev(reinterpret_cast<uint64_t*>(a.ctr + kWatchCloses), removed);
+            add_dev(a.ctr + kHyDead0 + (kMode == kWatchCounted), (int)removed);
+            if (kMode == kWatchStep)
+                add_dev(reinterpret_cast<uint64_t*>(a.ctr + kWatchCloses), removed);
         }
     }
 }
@@ -239,9 +258,12 @@ struct WatchKill {
     }
 };
 
-// Removals of the round before round r (round 0: the sweep's and the forest's).
-__device__ __forceinline__ int removed_before(const int* ctr, int r) {
-    return ld_dev(ctr + kHyDead0 + (r - 1) % 3) + (r == 1 ? ld_dev(ctr + kJKilled) : 0);
+// Removals whose supporters round r has to find: the round's before, and in
+// front of the first those of the forest collapse or, without it, of the sweep
+// or the last counted round.
+__device__ __forceinline__ int removed_before(const WatchState& a, int r) {
+    return r == a.r1 && a.forest ? ld_dev(a.ctr + kJKilled)
+                                 : ld_dev(a.ctr + kHyDead0 + (r - 1) % 3);
 }
 
 struct WatchSums {
@@ -279,12 +301,31 @@ __device__ __forceinline__ bool watch_scan(const WatchState& a, int v, int s, in
     return false;
 }
 
+// The wavefront's hand-backs among the U vertices of each lane, put side by side
+// in its part of `found` (U * 64 entries): their scans, chains of four dependent
+// loads, then run 64 at a time instead of a few lanes' at a time, U times.
+template <int U>
+__device__ __forceinline__ int watch_found(const bool (&back)[U], const int (&s)[U], int v0,
+                                           int stride, int2* found) {
+    int cnt = 0;
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+        const uint64_t mask = ballot(back[k]);
+        if (back[k]) found[cnt + popc(mask & lanes_below())] = make_int2(v0 + k * stride, s[k]);
+        cnt += popc(mask);
+    }
+    __builtin_amdgcn_wave_barrier();
+    return cnt;
+}
+
 // Round r over the thread's vertices; returns the removals.  sflt: the filter of
 // round r - 1 in LDS, or NULL.
 template <bool kFresh>
 __device__ __forceinline__ uint32_t watch_vertices(const WatchState& a, int r,
-                                                   const uint32_t* sflt, WatchSums& t) {
+                                                   const uint32_t* sflt, int2* found,
+                                                   WatchSums& t) {
     constexpr int U = kRoundFlight;
+    found += threadIdx.x / kWave * (U * kWave);
     uint32_t removed = 0;
     const int n = a.n, stride = gridDim.x * blockDim.x;
     for (int base = blockIdx.x * blockDim.x + threadIdx.x; base < n; base += U * stride) {
@@ -299,7 +340,7 @@ __device__ __forceinline__ uint32_t watch_vertices(const WatchState& a, int r,
         if (sflt) {
 #pragma unroll
             for (int k = 0; k < U; ++k) {
-                const uint32_t h = WatchFilter::hash(s[k] & kSupMask);
+                const uint32_t h = a.flt.hash(s[k] & kSupMask);
                 back[k] = back[k] && ((sflt[h >> 5] >> (h & 31)) & 1u);
             }
         }
@@ -312,13 +353,12 @@ __device__ __forceinline__ uint32_t watch_vertices(const WatchState& a, int r,
         }
 #pragma unroll
         for (int k = 0; k < U; ++k) back[k] = back[k] && ((x[k] >> (s[k] & 31)) & 1u);
-#pragma unroll
-        for (int k = 0; k < U; ++k) {
-            if (!back[k]) continue;
-            const int v = base + k * stride;
+        const int cnt = watch_found(back, s, base, stride, found);
+        for (int i = lane_id(); i < cnt; i += kWave) {
+            const int v = found[i].x;
             int pos, to;
             t.visited += 1;
-            if (watch_scan<kFresh>(a, v, s[k], pos, to, t.edges)) {
+            if (watch_scan<kFresh>(a, v, found[i].y, pos, to, t.edges)) {
                 a.sup[v] = to;
                 *rec_pos(a.rec, v) = pos;
                 t.joins += 1;
@@ -330,6 +370,7 @@ __device__ __forceinline__ uint32_t watch_vertices(const WatchState& a, int r,
                 removed += 1;
             }
         }
+        __builtin_amdgcn_wave_barrier();
     }
     return removed;
 }
@@ -339,7 +380,7 @@ __device__ __forceinline__ uint32_t watch_vertices(const WatchState& a, int r,
 __device__ __forceinline__ void watch_round_end(const WatchState& a, int r, uint32_t removed,
                                                 uint64_t* red) {
     uint32_t* f = a.flt.slot(r + 1);
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < WatchFilter::kWords;
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < a.flt.words();
          i += gridDim.x * blockDim.x)
         st_dev(f + i, 0u);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -362,75 +403,232 @@ __device__ __forceinline__ void watch_sums(const WatchState& a, WatchSums& t, ui
 
 // The filter of round r - 1, which removed `removed`, into LDS; NULL when it is
 // of no use.
-template <int kThreads>
+template <int kThreads, bool kFresh>
 __device__ __forceinline__ const uint32_t* watch_stage(const WatchState& a, int r, int removed,
                                                        uint32_t* sflt) {
-    const bool use = WatchFilter::useful(removed);
+    const bool use = a.flt.useful(removed);
     if (use) {
-        constexpr int K = WatchFilter::kWords / 2 / kThreads;
-        static_assert(K * 2 * kThreads == WatchFilter::kWords, "");
+        // 8-byte pieces, four in flight: a load past the L2 takes 1 us
+        constexpr int K = 4;
         const uint64_t* f = reinterpret_cast<const uint64_t*>(a.flt.slot(r - 1));
-        uint64_t x[K];   // all in flight at once: a load past the L2 takes 1 us
+        uint64_t* to = reinterpret_cast<uint64_t*>(sflt);
+        const int words = a.flt.words() / 2;
+        for (int base = threadIdx.x; base < words; base += K * kThreads) {
+            uint64_t x[K];
 #pragma unroll
-        for (int i = 0; i < K; ++i) x[i] = ld_dev(f + i * kThreads + threadIdx.x);
+            for (int i = 0; i < K; ++i) {
+                const uint64_t* p = f + min(base + i * kThreads, words - 1);
+                x[i] = kFresh ? ld_dev(p) : *p;
+            }
 #pragma unroll
-        for (int i = 0; i < K; ++i)
-            reinterpret_cast<uint64_t*>(sflt)[i * kThreads + threadIdx.x] = x[i];
+            for (int i = 0; i < K; ++i)
+                if (base + i * kThreads < words) to[base + i * kThreads] = x[i];
+        }
     }
     __syncthreads();
     return use ? sflt : nullptr;
 }
 
+// Late registration (opts.rounds = R): counted rounds 2 .. R, a vertex's support
+// checked again in each.  Round r reads ycur, which holds the removals before
+// it, and builds ynext from the bitmap of the round before last: the words of
+// ycur and its own removals.  (The rounds and their counts are the sequential
+// ones whatever the order of the lanes.)  True if round r need not run: a round
+// before it removed nothing.
+__device__ __forceinline__ bool counted_done(int* ctr, int r) {
+    if (ld_dev(ctr + kHyStop)) return true;
+    if (ld_dev(ctr + kHyDead0 + (r - 1) % 3) == 0) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) st_dev(ctr + kHyStop, 1);
+        return true;
+    }
+    return false;
+}
+
+__global__ __launch_bounds__(kRoundThreads) void watch_counted(WatchState a, int r,
+                                                               const uint32_t* ycur,
+                                                               uint32_t* ynext) {
+    constexpr int U = kRoundFlight;
+    __shared__ __align__(8) uint32_t s_flt[WatchFilter::kMaxWords];
+    __shared__ int2 s_found[kRoundThreads * U];
+    __shared__ uint64_t red[16];
+    if (counted_done(a.ctr, r)) return;
+    const int before = ld_dev(a.ctr + kHyDead0 + (r - 1) % 3);
+    const uint32_t* sflt = watch_stage<kRoundThreads, false>(a, r, before, s_flt);
+    const int n = a.n, stride = gridDim.x * blockDim.x;
+    const int tid = blockIdx.x * blockDim.x + threadIdx.x;
+    int2* found = s_found + threadIdx.x / kWave * (U * kWave);
+    for (int i = tid; i < (n + 31) >> 5; i += stride) {
+        const uint32_t b = ycur[i];
+        if (b & ~ynext[i]) atomicOr(ynext + i, b);
+    }
+    WatchState now = a;
+    now.dead = const_cast<uint32_t*>(ycur);
+    uint64_t edges = 0;
+    uint32_t removed = 0, entries = 0;
+    for (int base = tid; base < n; base += U * stride) {
+        int s[U];
+        uint32_t x[U];
+        bool back[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int v = base + k * stride;
+            s[k] = a.sup[v < n ? v : n - 1];
+            back[k] = v < n && s[k] >= 0;
+            entries += back[k];
+        }
+        if (sflt) {
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const uint32_t h = a.flt.hash(s[k] & kSupMask);
+                back[k] = back[k] && ((sflt[h >> 5] >> (h & 31)) & 1u);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) x[k] = back[k] ? ycur[(s[k] & kSupMask) >> 5] : 0;
+#pragma unroll
+        for (int k = 0; k < U; ++k) back[k] = back[k] && ((x[k] >> (s[k] & 31)) & 1u);
+        const int cnt = watch_found(back, s, base, stride, found);
+        for (int i = lane_id(); i < cnt; i += kWave) {
+            const int v = found[i].x;
+            int pos, to;
+            if (watch_scan<false>(now, v, found[i].y, pos, to, edges)) {
+                a.sup[v] = to;
+                *rec_pos(a.rec, v) = pos;
+            } else {
+                a.sup[v] = -1;
+                atomicOr(ynext + (v >> 5), 1u << (v & 31));
+                a.flt.add(r, v);
+                removed += 1;
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+    uint32_t* f = a.flt.slot(r + 1);
+    for (int i = tid; i < a.flt.words(); i += stride) f[i] = 0;
+    if (tid == 0) {
+        st_dev(a.ctr + kHyDead0 + (r + 1) % 3, 0);
+        st_dev(a.ctr + kHyRounds, r);
+    }
+    const uint64_t rem = block_sum(removed, red), ent = block_sum(entries, red);
+    edges = block_sum(edges, red);
+    if (threadIdx.x == 0) {
+        add_dev(a.worker_edges + (blockIdx.x % a.P), edges + ent);
+        if (ent) add_dev(reinterpret_cast<uint64_t*>(a.ctr + kHyWork), ent);
+        if (rem) add_dev(a.ctr + kHyDead0 + r % 3, (int)rem);
+    }
+}
+
+// After counted round R, which removed something: what watch_sweep leaves for the
+// forest collapse, from the supports as they are now; vertices whose support
+// round R removed resume their scans.  It reads a.dead only.
+__global__ __launch_bounds__(1024) void watch_collect(WatchState a, int* jp, uint32_t* jlist) {
+    constexpr int U = kSweepFlight;
+    __shared__ int s_wave[1024 / kWave], s_base;
+    __shared__ uint64_t red[16];
+    if (counted_done(a.ctr, a.r1)) return;
+    WatchSums t;
+    const int n = a.n, per = U * blockDim.x;
+    for (int base = blockIdx.x * per; base < n; base += gridDim.x * per) {
+        int s[U], e[U], p[U];
+        uint32_t x[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int v = base + k * blockDim.x + threadIdx.x, c = min(v, n - 1);
+            s[k] = v < n ? a.sup[c] : -1;
+            p[k] = __builtin_nontemporal_load(a.row_off + c);
+            e[k] = __builtin_nontemporal_load(a.row_off + c + 1);
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int v = base + k * blockDim.x + threadIdx.x;
+            x[k] = a.dead[(s[k] & kSupMask) >> 5 & (s[k] < 0 ? 0 : -1)];
+            if (s[k] >= 0 && !(s[k] & kSupFirst)) p[k] = *rec_pos(a.rec, v);
+        }
+        int c = 0;
+        uint32_t put = 0, root = 0;
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            if (s[k] < 0) continue;
+            const int v = base + k * blockDim.x + threadIdx.x;
+            int w = s[k] & kSupMask;
+            bool lost = false;
+            if ((x[k] >> (w & 31)) & 1u) {
+                t.visited += 1;
+                lost = !watch_scan<false>(a, v, s[k], p[k], w, t.edges);
+                if (!lost) {
+                    *rec_pos(a.rec, v) = p[k];
+                    t.joins += 1;
+                }
+                a.sup[v] = lost ? -1 : w;
+            }
+            const bool member = !lost && p[k] + 1 == e[k];
+            jp[v] = lost ? ~v : member ? w : v;
+            put |= (uint32_t)(lost || member) << k;
+            root |= (uint32_t)lost << k;
+        }
+        c = __popc(put);
+        int slot = block_append_base(c, a.ctr + kJCnt0, nullptr, s_wave, &s_base);
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+            if ((put >> k) & 1u)
+                jlist[slot++] = (uint32_t)(base + k * (int)blockDim.x + (int)threadIdx.x) |
+                                ((root >> k) & 1u ? kRootBit : 0u);
+    }
+    watch_sums(a, t, red);
+}
+
 template <bool kFilter>
-__global__ __launch_bounds__(256) void watch_round(WatchState a, int r) {
-    __shared__ __align__(8) uint32_t sflt[kFilter ? WatchFilter::kWords : 2];
+__global__ __launch_bounds__(kRoundThreads) void watch_round(WatchState a, int r) {
+    __shared__ __align__(8) uint32_t sflt[kFilter ? WatchFilter::kMaxWords : 2];
+    __shared__ int2 found[kRoundThreads * kRoundFlight];
     __shared__ uint64_t red[16];
     if (ld_dev(a.ctr + kHyStop)) return;
-    const int before = removed_before(a.ctr, r);
+    const int before = removed_before(a, r);
     if (before == 0) {   // the fixed point; workgroup 0 tells the later launches
         if (blockIdx.x == 0 && threadIdx.x == 0) st_dev(a.ctr + kHyStop, 1);
         return;
     }
     WatchSums t;
     const uint32_t removed =
-        watch_vertices<false>(a, r, kFilter ? watch_stage<256>(a, r, before, sflt) : nullptr, t);
+        watch_vertices<false>(
+        a, r, kFilter ? watch_stage<kRoundThreads, false>(a, r, before, sflt) : nullptr, found, t);
     watch_round_end(a, r, removed, red);
     watch_sums(a, t, red);
 }
 
 // Rounds r0 .. watch_rounds(n) in one launch of at most one workgroup per CU, all
 // resident at once.  A vertex is the same thread's in every round.
-__global__ __launch_bounds__(kTailThreads) void watch_tail(WatchState a, int r0, int last,
-                                                          int budget) {
-    __shared__ __align__(8) uint32_t sflt[WatchFilter::kWords];
+__global__ __launch_bounds__(kRoundThreads) void watch_tail(WatchState a, int r0, int last,
+                                                          int* head, int* ext, int budget) {
+    __shared__ __align__(8) uint32_t sflt[WatchFilter::kMaxWords];
+    __shared__ int2 found[kRoundThreads * kRoundFlight];
     __shared__ uint64_t red[16];
     if (ld_dev(a.ctr + kHyStop)) return;
     WatchSums t;
     int r = r0;
     for (;; ++r) {
-        const int before = removed_before(a.ctr, r);
+        const int before = removed_before(a, r);
         if (before == 0) {
             if (blockIdx.x == 0 && threadIdx.x == 0) st_dev(a.ctr + kHyStop, 1);
             break;
         }
-        if (r > last) break;
-        const uint32_t removed =
-            watch_vertices<true>(a, r, watch_stage<kTailThreads>(a, r, before, sflt), t);
+        if (r > last) {   // the lists' heads; nothing reads the filters there any more
+            for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < a.n;
+                 v += gridDim.x * blockDim.x) {
+                const int h = (ld_dev(a.dead + (v >> 5)) >> (v & 31)) & 1u ? kDead : kEmpty;
+                reinterpret_cast<int2*>(head)[v] = make_int2(h, h);
+                if (ext)
+                    for (int j = 0; j < kMoreLists - 1; ++j)
+                        ext[(kMoreLists - 1) * (long long)v + j] = h;
+            }
+            break;
+        }
+        const uint32_t* f = watch_stage<kRoundThreads, true>(a, r, before, sflt);
+        const uint32_t removed = watch_vertices<true>(a, r, f, found, t);
         watch_round_end(a, r, removed, red);
         if (!grid_barrier(a.ctr + kBarCount, a.ctr + kBarGen, a.ctr + kStall, budget)) break;
     }
     watch_sums(a, t, red);
-}
-
-// Without a fixed point after watch_rounds(n) rounds: the lists' heads.
-__global__ void watch_heads(const uint32_t* dead, int n, int* head, int* ext, const int* ctr) {
-    if (ld_dev(ctr + kHyStop)) return;
-    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x) {
-        const int h = status_bit(dead, v) ? kDead : kEmpty;
-        reinterpret_cast<int2*>(head)[v] = make_int2(h, h);
-        if (ext)
-            for (int j = 0; j < kMoreLists - 1; ++j) ext[(kMoreLists - 1) * (long long)v + j] = h;
-    }
 }
 
 // Every vertex left joins the list of its support, those whose support the last
@@ -441,7 +639,8 @@ __global__ __launch_bounds__(256) void watch_register(WatchState a, int* head, i
     constexpr int U = 4;
     __shared__ int s_wave[256 / kWave], s_base;
     __shared__ uint64_t red[16];
-    if (ld_dev(a.ctr + kHyStop)) return;
+    // (after a stall the heads may not be there)
+    if (ld_dev(a.ctr + kHyStop) || ld_dev(a.ctr + kStall)) return;
     WatchSums t;
     const int n = a.n, step = gridDim.x * blockDim.x * U;
     for (int base = blockIdx.x * blockDim.x * U; base < n; base += step) {

@@ -76,6 +76,26 @@ def test_depths(ctx, depth, width):
     check_all(ctx, g, algos=(6,), name=f"{width} paths of {depth}")
 
 
+@pytest.mark.parametrize("R,n,depth,width", [(2, 200003, 5, 15000), (3, 70016, 40, 100),
+                                             (2, (1 << 20) + 5, 6, 30000), (8, 4097, 300, 3),
+                                             (64, 80000, 66, 2), (2, 33, 5, 2)])
+def test_counted_rounds(ctx, R, n, depth, width):
+    """Late registration: the rounds' counts, then the propagation."""
+    import torch
+    import paper_2107_12720_amd as T
+    for g in (doubled_paths(n, depth, width, seed=R), gg.uniform(n, n + n // 4, seed=R)):
+        r, c, bm = expected(g)
+        total, rounds, re = oracle.counts_deferred(g, r, R)
+        ro, col = T.to_device(g.row_off), T.to_device(g.col)
+        for flags in (0, T.FLAG_STEPWISE):
+            say(f"  R={R} n={n} flags={flags}")
+            res = ctx.trim_csr(6, n, ro, col, opts=T.make_opts(rounds=R, flags=flags))
+            torch.cuda.synchronize()
+            st = res.stats_dict()
+            assert np.array_equal(res.bitmap_numpy()[:(n + 31) // 32], bm)
+            assert (st["edges_total"], st["rounds"], st["rechecks"]) == (total, rounds, re)
+
+
 @pytest.mark.parametrize("depth", [40, 500])
 def test_rescued(ctx, depth):
     check_all(ctx, rescued(80000, depth, seed=depth), algos=(6,), name=f"rescued {depth}")

@@ -183,7 +183,11 @@ constexpr int kBinPer = 32;                 // targets per thread of a tile
 constexpr int kBinTile = kBinThreads * kBinPer;
 constexpr int kBinSlices = 1024;
 constexpr long long kBinChunk = 1 << 21;    // targets one workgroup counts at most
-constexpr long long kBinMinM = 1 << 16;     // fewer edges: the plain counters
+// Fewer edges (in one bin, in several): the plain counters.  Scores of R-MAT
+// graphs, plain / binned, us: 30,000 vertices of edge factor 4 36 / 37, 16 79 / 47;
+// 60,000 of 4 54 / 76, 8 82 / 81, 16 123 / 89; 2^18 of 4 168 / 101.
+constexpr long long kBinMinM = 1 << 16;
+constexpr long long kBinsMinM = 1 << 19;
 constexpr int kBinCountThreads = 1024;
 static_assert(kBinMax == 2 * kBinThreads && kBinMax == kBinCountThreads, "scans of the bins' totals");
 
@@ -417,35 +421,43 @@ __global__ void short_degrees(const int* row_off, int n, uint16_t* deg) {
 }
 
 // Keys for the reference orders: 0 = log1p(outdeg w) (larger first), 1 = a hash
-// of (seed, e) (a random order).  The gather of the targets' degrees bounds
-// kind 0 (a line from beyond the L2 for every one they miss): with the two
-// offsets of every target it took 1.96 ms on R-MAT 24, from the table of two
-// bytes a vertex, of which the L2s hold more, 1.75 ms with the table's making.
-__global__ void edge_keys(const int* row_off, const int* col, const uint16_t* deg, long long m,
-                          int kind, uint64_t seed, float* key) {
+// of (seed, e) (a random order).
+__global__ void edge_keys(const int* row_off, const int* col, long long m, int kind, uint64_t seed,
+                          float* key) {
+    for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < m;
+         e += gridDim.x * (long long)blockDim.x) {
+        if (kind == 0) {
+            const int w = col[e];
+            key[e] = log1pf((float)(row_off[w + 1] - row_off[w]));
+        } else {
+            key[e] = (float)(mix64(seed ^ (uint64_t)e) >> 40) * (1.f / 16777216.f);
+        }
+    }
+}
+
+// Kind 0 for many edges.  The gather of the targets' degrees bounds it (a line
+// from beyond the L2 for every one they miss): with the two offsets of every
+// target it took 1.96 ms on R-MAT 24, from the table of two bytes a vertex, of
+// which the L2s hold more, 1.75 ms with the table's making.  Targets and keys
+// pass by the caches, which the table needs; graphs whose keys the ordering
+// would find there still are taken by edge_keys.
+__global__ void edge_keys_table(const int* row_off, const int* col, const uint16_t* deg,
+                                long long m, float* key) {
     constexpr int U = 4;
     const long long stride = gridDim.x * (long long)blockDim.x;
     for (long long e0 = blockIdx.x * (long long)blockDim.x + threadIdx.x; e0 < m;
          e0 += U * stride) {
-        if (kind == 0) {
-            int w[U], d[U];
+        int w[U], d[U];
 #pragma unroll
-            for (int k = 0; k < U; ++k)
-                w[k] = __builtin_nontemporal_load(col + min(e0 + k * stride, m - 1));
+        for (int k = 0; k < U; ++k)
+            w[k] = __builtin_nontemporal_load(col + min(e0 + k * stride, m - 1));
 #pragma unroll
-            for (int k = 0; k < U; ++k)
-                d[k] = deg ? (int)deg[w[k]] : row_off[w[k] + 1] - row_off[w[k]];
+        for (int k = 0; k < U; ++k) d[k] = (int)deg[w[k]];
 #pragma unroll
-            for (int k = 0; k < U; ++k) {
-                if (deg && d[k] == (int)kDegMax) d[k] = row_off[w[k] + 1] - row_off[w[k]];
-                if (e0 + k * stride < m)
-                    __builtin_nontemporal_store(log1pf((float)d[k]), key + e0 + k * stride);
-            }
-        } else {
-            for (int k = 0; k < U; ++k) {
-                const long long e = e0 + k * stride;
-                if (e < m) key[e] = (float)(mix64(seed ^ (uint64_t)e) >> 40) * (1.f / 16777216.f);
-            }
+        for (int k = 0; k < U; ++k) {
+            if (d[k] == (int)kDegMax) d[k] = row_off[w[k] + 1] - row_off[w[k]];
+            if (e0 + k * stride < m)
+                __builtin_nontemporal_store(log1pf((float)d[k]), key + e0 + k * stride);
         }
     }
 }
@@ -716,7 +728,7 @@ inline int tile_grid(long long m) {
 }  // namespace
 
 bool bin_degrees_ok(long long n, long long m) {
-    return n <= (long long)kBinMax * kBinV && m >= kBinMinM;
+    return n <= (long long)kBinMax * kBinV && m >= (n <= kBinV ? kBinMinM : kBinsMinM);
 }
 
 // Bytes of scratch: the binned targets (whole 16-byte words) and the counts.
@@ -780,11 +792,15 @@ hipError_t mlp_prepare(const int* row_off, const int* col, int n, long long m, i
 hipError_t edge_keys_launch(const int* row_off, const int* col, int n, long long m, int kind,
                             uint64_t seed, float* key, uint16_t* deg, hipStream_t s) {
     if (m > 0) {
-        if (kind == 0 && deg)
+        if (kind == 0 && deg) {
             hipLaunchKernelGGL(short_degrees, dim3(grid_for(n, 256, 16384)), dim3(256), 0, s,
                                row_off, n, deg);
-        hipLaunchKernelGGL(edge_keys, dim3(grid_for((m + 3) / 4, 256, 16384)), dim3(256), 0, s,
-                           row_off, col, deg, m, kind, seed, key);
+            hipLaunchKernelGGL(edge_keys_table, dim3(grid_for((m + 3) / 4, 256, 16384)), dim3(256),
+                               0, s, row_off, col, deg, m, key);
+        } else {
+            hipLaunchKernelGGL(edge_keys, dim3(grid_for(m, 256, 16384)), dim3(256), 0, s, row_off,
+                               col, m, kind, seed, key);
+        }
     }
     return hipGetLastError();
 }

@@ -873,10 +873,14 @@ int trim_edge_keys(trim_ctx* c, const trim_csr_t* g, int32_t kind, uint64_t seed
     if (rc) return rc;
     if (kind != 0 && kind != 1) return fail(TRIM_E_INVAL, "trim_edge_keys: kind must be 0 or 1");
     if (g->m > 0 && !keys) return fail(TRIM_E_INVAL, "trim_edge_keys: NULL keys");
-    // the table of degrees is worth its pass over the vertices from a few edges
-    // a vertex on; without room for it the keys come from the offsets
+    // the table of degrees is worth its pass over the vertices when the offsets
+    // are too many for the L2s and the edges many to a vertex (with their
+    // ordering, offsets / table, us: R-MAT 20 of edge factor 16 276 / 295, 21 of 8
+    // 314 / 335 and of 16 592 / 574, 22 of 4 376 / 406 and of 16 1,216 / 1,158);
+    // without room for it the keys come from the offsets
     const long long words = ((long long)g->n + 1) / 2;
-    if (kind == 0 && g->m >= 2LL * g->n && words > c->cap_vf) {
+    const bool many = kind == 0 && g->m >= 1LL << 25 && g->m >= 8LL * g->n;
+    if (many && words > c->cap_vf) {
         uint32_t* more = nullptr;
         if (dmalloc(c, &more, (size_t)words * 4) == hipSuccess) {
             dfree(c, c->vf);
@@ -886,7 +890,7 @@ int trim_edge_keys(trim_ctx* c, const trim_csr_t* g, int32_t kind, uint64_t seed
             (void)hipGetLastError();
         }
     }
-    const bool table = kind == 0 && g->m >= 2LL * g->n && words <= c->cap_vf;
+    const bool table = many && words <= c->cap_vf;
     return launched(trim::edge_keys_launch(g->row_off, g->col, g->n, g->m, kind, seed, keys,
                                            table ? reinterpret_cast<uint16_t*>(c->vf) : nullptr,
                                            (hipStream_t)stream));

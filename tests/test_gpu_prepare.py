@@ -106,3 +106,30 @@ def test_score_forms(m):
     finally:
         wide.close()
         narrow.close()
+
+
+@pytest.mark.parametrize("n,m", [((1 << 22), 1 << 25), ((1 << 22) - 1, (1 << 25) + 3),
+                                 (70001, 1 << 25), (1000, (1 << 25) - 1)])
+def test_degree_keys(n, m):
+    """The keys of the degree order: from the table of two-byte degrees (many
+    edges) and from the offsets, degrees of 65,534 to 65,536 and more included.
+    The table's degrees are exact, so the keys are those of the offsets."""
+    import torch
+    import paper_2107_12720_amd as T
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    deg = torch.bincount(torch.randint(0, n, (m - 327674,), device="cuda", generator=gen),
+                         minlength=n)
+    deg[:5] += torch.tensor([65534, 65535, 65536, 131069, 0], device="cuda")
+    m = int(deg.sum())
+    row_off = torch.zeros(n + 1, dtype=torch.int32, device="cuda")
+    row_off[1:] = deg.cumsum(0).to(torch.int32)
+    col = torch.randint(0, n, (m,), device="cuda", generator=gen).to(torch.int32)
+    col[:5000] = torch.arange(5000, device="cuda", dtype=torch.int32) % 5
+    ctx = T.Context(0)
+    keys = torch.empty(m, dtype=torch.float32, device="cuda")
+    ctx.edge_keys(T.DeviceGraph(n, row_off, col), 0, keys)
+    torch.cuda.synchronize()
+    want = torch.log1p(deg[col.long()].double())
+    ctx.close()
+    # log1pf is within 2 ulp
+    assert float(((keys.double() - want).abs() / want.clamp(min=1.0)).max()) <= 2 ** -22

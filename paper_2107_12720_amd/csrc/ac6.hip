@@ -1073,10 +1073,6 @@ inline int grid_for(long long n, int block, int max_blocks = 1 << 20) {
     return (int)b;
 }
 
-// Words from the first round bitmap to the second (both in w.c, which holds
-// n + n / 8 + 64 ints): room for ceil(n / 32) words plus the one past the end
-// that ac6_init may write, aligned to a cache line.
-inline long long round_bitmap_offset(long long n) { return ((n + 31) / 32 + 2 + 31) / 32 * 32; }
 // Workgroups of a round launch: about one per 1,024 list entries (a list
 // holds at most n), at most four per CU
 // (more workgroups measured slower: every round launch after the fixed point

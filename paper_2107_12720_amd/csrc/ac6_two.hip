@@ -27,6 +27,9 @@
 // removed one checks at most its two lists once, and at least the whole list
 // of the side that removed it.
 //
+// The kernels below serve small graphs and deep remainders; other graphs are
+// trimmed by rounds over watched supports (ac6_two_watch.h).
+//
 // Kernels, in stream order: ac6t_init (list heads, the bitmap of vertices
 // without successors or predecessors, counters), ac6t_sweep (both support
 // searches per vertex; only that bitmap's vertices are removed while it runs,
@@ -41,6 +44,7 @@
 #include "ac6_support.h"
 #include "scc_internal.h"
 #include "forest_jump.h"
+#include "ac6_two_watch.h"
 
 namespace trim {
 
@@ -515,15 +519,20 @@ struct TwoSidedKill {
 // their final cursors: a live vertex's supports end at its first finally-live
 // successor and predecessor, so it checked fl_out + 1 + fl_in + 1 positions
 // whatever the schedule.  Restores the shared queue after a stalled call.
-__global__ void ac6t_pack(TwoGraph g, int n, uint32_t* bitmap, uint64_t* part, const int* ctr,
-                          uint32_t* q, long long qwords) {
+// With kWatch, after rounds over watched supports that reached the fixed point,
+// read off those.
+template <bool kWatch>
+__global__ void ac6t_pack(TwoGraph g, TwoWatch t, int n, uint32_t* bitmap, uint64_t* part,
+                          const int* ctr, uint32_t* q, long long qwords) {
     __shared__ uint64_t red[16];
     clear_queue_if_stalled(ctr, q, qwords);
     const int nwords = (n + 31) >> 5;
     const int waves = (gridDim.x * blockDim.x) / kWave;
     const int wid = (blockIdx.x * blockDim.x + threadIdx.x) / kWave;
     uint64_t live_cnt = 0, live_edges = 0;
-    for (int base = wid * kWave; base < n; base += waves * kWave) {
+    const bool watched = kWatch && ld_dev(ctr + kHyStop);
+    if (watched) two_watch_pack(t, bitmap, live_cnt, live_edges);
+    for (int base = wid * kWave; base < n && !watched; base += waves * kWave) {
         const int v = base + lane_id();
         const bool live = v < n && g.hout[2 * v] != kDead;
         if (live)
@@ -554,6 +563,85 @@ inline int grid_for(long long n, int block, int max_blocks = 1 << 20) {
 
 }  // namespace
 
+namespace {
+
+// Smaller graphs keep the lists (two launches fewer): core+tail of 4,096 vertices
+// 246 us by lists, 141 by rounds, but uniform of 4,096 164 / 173 and R-MAT 12 71 /
+// 75.  The filters need room in the heads, the in-side supports behind the bitmaps.
+constexpr int kTwoWatchMinN = 4096;
+static_assert(2 * kTwoWatchMinN >= 3 << (WatchFilter::log_for(kTwoWatchMinN) - 5), "filters fit");
+
+hipError_t two_watch_run(const TwoGraph& g, long long m, int n, const Work& w, const Work2& x,
+                         const LaunchCfg& lc, uint32_t* bitmap, uint64_t* worker_edges,
+                         trim_stats_t* stats, const uint32_t* preset) {
+    const int P = lc.workers, B = lc.block;
+    hipStream_t st = lc.stream;
+    uint32_t* y1 = reinterpret_cast<uint32_t*>(w.c);
+    uint32_t* dead = y1 + round_bitmap_offset(n);
+    int* sup_in = w.c + 2 * round_bitmap_offset(n);
+    const WatchFilter flt{reinterpret_cast<uint32_t*>(g.hout), WatchFilter::log_for(n)};
+    const TwoWatch t{{g.row_off, g.col, n, w.d, g.rec_out, dead, flt, w.ctr, worker_edges, P,
+                      lc.schedule, 1, lc.forest},
+                     {g.rrow_off, g.rcol, n, sup_in, g.rec_in, dead, flt, w.ctr, worker_edges, P,
+                      lc.schedule, 1, lc.forest}};
+    const int sweep_blocks = grid_for(n, 4LL * B, lc.cus * 8);
+    const int pack_blocks = grid_for(n, 256, lc.cus * 4);
+    {
+        Timed tm(lc, "ac6t_init");
+        hipLaunchKernelGGL(two_watch_init, dim3(grid_for(n, 256, 16384)), dim3(256), 0, st, t,
+                           preset, y1, stats);
+    }
+    {
+        Timed tm(lc, "ac6t_sweep");
+        hipLaunchKernelGGL(lc.forest ? two_watch_sweep<true> : two_watch_sweep<false>,
+                           dim3(sweep_blocks), dim3(B), 0, st, t, m, y1, w.jp, w.e, w.part);
+    }
+    if (lc.forest) {
+        Timed tm(lc, "ac6t_jump");
+        hipLaunchKernelGGL(ac6_jump<TwoWatchKill>, dim3(phase_blocks(n, lc.cus)), dim3(256), 0,
+                           st, TwoWatchKill{w.d, dead}, w.jp, w.e, w.e + n, x.q, w.ctr,
+                           jump_rounds(n), lc.budget);
+    }
+    {
+        Timed tm(lc, "ac6t_rounds");
+        const int rb = grid_for(n, (long long)kRoundThreads * kTwoFlight, lc.cus * 2);
+        for (int r = 1; r <= round_launches(n); ++r)
+            if (r > 1 && n > kSplitMaxN)
+                hipLaunchKernelGGL(two_watch_round<true>, dim3(rb), dim3(kRoundThreads), 0, st, t,
+                                   r);
+            else
+                hipLaunchKernelGGL(two_watch_round<false>, dim3(rb), dim3(kRoundThreads), 0, st,
+                                   t, r);
+        hipLaunchKernelGGL(two_watch_tail,
+                           dim3(grid_for(n, (long long)kRoundThreads * kTailPer, lc.cus)),
+                           dim3(kRoundThreads), 0, st, t, 1 + round_launches(n), watch_rounds(n),
+                           g.hout, g.ext, g.hin, lc.budget);
+    }
+    {
+        Timed tm(lc, "ac6t_register");
+        hipLaunchKernelGGL(two_watch_register, dim3(grid_for(n, 256, lc.cus * 8)), dim3(256), 0,
+                           st, t, g.hout, g.ext, g.hin, x.q);
+    }
+    {
+        Timed tm(lc, "ac6t_propagate");
+        hipLaunchKernelGGL(ac6t_propagate, dim3(P), dim3(256), 0, st, g, x.q, w.ctr, worker_edges,
+                           w.part, lc.schedule, lc.budget);
+    }
+    {
+        Timed tm(lc, "ac6t_pack");
+        hipLaunchKernelGGL(ac6t_pack<true>, dim3(pack_blocks), dim3(256), 0, st, g, t, n, bitmap,
+                           w.part, w.ctr, x.q, x.qwords);
+    }
+    if (stats) {
+        Timed tm(lc, "finalize");
+        hipLaunchKernelGGL(finalize_stats, dim3(1), dim3(1024), 0, st, n, P, sweep_blocks, P,
+                           pack_blocks, P, worker_edges, w.part, w.ctr, stats, 0, pack_blocks);
+    }
+    return hipGetLastError();
+}
+
+}  // namespace
+
 hipError_t ac6_two_csr(const trim_csr_t& gc, const Work& w, const Work2& x, const LaunchCfg& lc,
                        uint32_t* bitmap, uint64_t* worker_edges, trim_stats_t* stats) {
     return ac6_two_csr_preset(gc, w, x, lc, bitmap, worker_edges, stats, nullptr);
@@ -569,6 +657,8 @@ hipError_t ac6_two_csr_preset(const trim_csr_t& gc, const Work& w, const Work2& 
                        x.qwords >= (long long)kQueuePerVertexTwoSplit * n + kQueueSlots;
     TwoGraph g{gc.row_off, gc.col, gc.rrow_off, gc.rcol, w.a, x.hin, w.b, x.rec_in,
                split ? w.ext : nullptr};
+    if (n >= kTwoWatchMinN)
+        return two_watch_run(g, gc.m, n, w, x, lc, bitmap, worker_edges, stats, preset);
     uint32_t* dead0 = reinterpret_cast<uint32_t*>(w.c);
     int sweep_blocks = 0, pack_blocks = 0;
     {
@@ -598,8 +688,8 @@ hipError_t ac6_two_csr_preset(const trim_csr_t& gc, const Work& w, const Work2& 
         }
         Timed t(lc, "ac6t_pack");
         pack_blocks = grid_for(n, 256, lc.cus * 4);
-        hipLaunchKernelGGL(ac6t_pack, dim3(pack_blocks), dim3(256), 0, lc.stream, g, n, bitmap,
-                           w.part, w.ctr, x.q, x.qwords);
+        hipLaunchKernelGGL(ac6t_pack<false>, dim3(pack_blocks), dim3(256), 0, lc.stream, g,
+                           TwoWatch{}, n, bitmap, w.part, w.ctr, x.q, x.qwords);
     }
     if (stats) {
         Timed t(lc, "finalize");

@@ -63,8 +63,8 @@
 //   ac6_pack       live bitmap by wavefront ballot, live/dead counts.
 //
 // These serve the implicit graph, batches of graphs too large for a workgroup
-// and the fixed-memory entry point.  Other explicit graphs go to one workgroup (small.hip) or to the rounds over
-// watched supports (ac6_watch.h), which end in the kernels above when a graph
+// and the fixed-memory entry point.  Other explicit graphs go to one workgroup
+// (small.hip) or to the rounds over watched supports (ac6_watch.h), which end in the kernels above when a graph
 // is too deep for them.
 #include "trim_device.h"
 #include "trim_stats.h"
@@ -955,6 +955,8 @@ __global__ __launch_bounds__(256) void ac6_levels(View g, int* head, int* ext, u
 // heads of v exchanged with kDead, its S_more lists handed to the propagation
 // as walk items.
 struct OneSidedKill {
+    static constexpr bool kItems = true;
+    static constexpr int kThreads = 256, kUnroll = kJumpUnroll;
     int* head;
     int* ext;
     __device__ __forceinline__ void operator()(int v, uint32_t (&item)[kJumpItems]) const {
@@ -1263,7 +1265,7 @@ hipError_t ac6_watch_run(const trim_csr_t& g, const Work& w, const LaunchCfg& lc
     }
     if (lc.forest) {
         Timed t(lc, "ac6_jump");
-        hipLaunchKernelGGL(ac6_jump<WatchKill>, dim3(level_blocks), dim3(256), 0, st,
+        hipLaunchKernelGGL(ac6_jump<WatchKill>, dim3((level_blocks + 1) / 2), dim3(kRoundThreads), 0, st,
                            WatchKill{w.d, dead}, w.jp, w.e, w.e + n, w.q, w.ctr,
                            jump_rounds(n), lc.budget);
     }

@@ -501,6 +501,8 @@ __global__ __launch_bounds__(256) void ac6t_propagate(TwoGraph g, uint32_t* q, i
 static_assert(kJumpItems >= kMoreLists + 2, "a two-sided removal hands back its S_more lists "
                                             "and both in-side lists");
 struct TwoSidedKill {
+    static constexpr bool kItems = true;
+    static constexpr int kThreads = 256, kUnroll = kJumpUnroll;
     int* hout;
     int* hin;
     int* ext;
@@ -598,8 +600,8 @@ hipError_t two_watch_run(const TwoGraph& g, long long m, int n, const Work& w, c
     }
     if (lc.forest) {
         Timed tm(lc, "ac6t_jump");
-        hipLaunchKernelGGL(ac6_jump<TwoWatchKill>, dim3(phase_blocks(n, lc.cus)), dim3(256), 0,
-                           st, TwoWatchKill{w.d, dead}, w.jp, w.e, w.e + n, x.q, w.ctr,
+        hipLaunchKernelGGL(ac6_jump<TwoWatchKill>, dim3((phase_blocks(n, lc.cus) + 1) / 2),
+                           dim3(kRoundThreads), 0, st, TwoWatchKill{w.d, dead}, w.jp, w.e, w.e + n, x.q, w.ctr,
                            jump_rounds(n), lc.budget);
     }
     {

@@ -87,7 +87,8 @@ __global__ __launch_bounds__(1024) void two_watch_sweep(TwoWatch t, long long m,
             for (int s = 0; s < 2; ++s) {
                 p[s][k] = b[s][k];
                 w[s][k] = 0;
-                if (live[k]) w[s][k] = __builtin_nontemporal_load((s ? t.i.col : t.o.col) + b[s][k]);
+                const int* adj = s ? t.i.col : t.o.col;
+                if (live[k]) w[s][k] = __builtin_nontemporal_load(adj + b[s][k]);
             }
 #pragma unroll
         for (int k = 0; k < U; ++k)
@@ -151,9 +152,11 @@ __global__ __launch_bounds__(1024) void two_watch_sweep(TwoWatch t, long long m,
 
 // The forest collapse's removal of v.  No list is handed back.
 struct TwoWatchKill {
+    static constexpr bool kItems = false;
+    static constexpr int kThreads = kRoundThreads, kUnroll = 1;
     int* sup;
     uint32_t* dead;
-    __device__ __forceinline__ void operator()(int v, uint32_t (&)[kJumpItems]) const {
+    __device__ __forceinline__ void operator()(int v) const {
         sup[v] = -1;
         atomicOr(dead + (v >> 5), 1u << (v & 31));
     }
@@ -332,8 +335,10 @@ __global__ __launch_bounds__(256) void two_watch_register(TwoWatch t, int* hout,
             }
         }
         if (keep) {
-            const int oldo = xchg_dev(join_slot(hout, ext, w[0], p[0] + 1 == t.o.row_off[v + 1], v), v);
-            const int oldi = xchg_dev(hin + 2 * w[1] + (p[1] + 1 == t.i.row_off[v + 1]), v);
+            const bool lasto = p[0] + 1 == t.o.row_off[v + 1];
+            const bool lasti = p[1] + 1 == t.i.row_off[v + 1];
+            const int oldo = xchg_dev(join_slot(hout, ext, w[0], lasto, v), v);
+            const int oldi = xchg_dev(hin + 2 * w[1] + lasti, v);
             t.o.rec[v] = pack_rec(oldo, p[0]);
             t.i.rec[v] = pack_rec(oldi, p[1]);
         }

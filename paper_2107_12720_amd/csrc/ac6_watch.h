@@ -178,9 +178,11 @@ __global__ __launch_bounds__(1024) void watch_sweep(WatchState a, long long m, c
 
 // The forest collapse's removal of v (round 0).  No list is handed back.
 struct WatchKill {
+    static constexpr bool kItems = false;
+    static constexpr int kThreads = kRoundThreads, kUnroll = 1;
     int* sup;
     uint32_t* dead;
-    __device__ __forceinline__ void operator()(int v, uint32_t (&)[kJumpItems]) const {
+    __device__ __forceinline__ void operator()(int v) const {
         sup[v] = -1;
         atomicOr(dead + (v >> 5), 1u << (v & 31));
     }

@@ -21,6 +21,12 @@ namespace {
 // sweep left without a live successor (the removed roots).
 constexpr uint32_t kRootBit = 0x80000000u;
 
+// What bounds it: the latency of the links followed, kJumpHops a round, and for
+// long chains the removals' atomics.  With supports watched (no lists to hand
+// back) 256 workgroups of 512 lanes, an entry a lane, take 92 us for R-MAT 22 with
+// a chain of 2*10^5, two entries a lane 103, four 180; 512 workgroups of 256 with
+// the buffers of the lists 107.
+//
 // One launch of at most two workgroups per CU, all resident at once: round r
 // reads the list of round r (sizes rotate over three counters, like the AC-3
 // lists), resolves what it can, appends the members still without a root to
@@ -33,7 +39,7 @@ constexpr uint32_t kRootBit = 0x80000000u;
 // into a cycle.
 // Entries per thread per step: more would leave most workgroups idle when a
 // round's list is short.
-constexpr int kJumpUnroll = 2;
+constexpr int kJumpUnroll = 2;   // (with lists to hand back)
 // Links an entry follows per round (at least 2): a link that spans d levels
 // spans kJumpHops * d after the round (2 is classic pointer doubling).
 constexpr int kJumpHops = 8;
@@ -47,16 +53,20 @@ constexpr int kJumpItems = kMoreLists + 2;
 constexpr int kJumpStep = 256 * kJumpUnroll * kJumpItems;
 constexpr int kJumpBuf = kJumpStep + 4096;
 
-// Kill: `void operator()(int v, uint32_t (&item)[kJumpItems]) const` removes v
-// (closes its lists) and fills the work items that hand its lists back, kNone
-// for the unused ones.  v's out-side S_last list holds only members of v's
-// own tree, which the same rounds remove, so Kill leaves it unwalked.
+// Kill removes v.  With kItems, `void operator()(int v, uint32_t (&item)
+// [kJumpItems]) const` closes its lists and fills the work items that hand them
+// back, kNone for the unused ones (v's out-side S_last list holds only members of
+// v's own tree, which the same rounds remove, so Kill leaves it unwalked);
+// without, `void operator()(int v) const`.  kThreads: lanes per workgroup, of
+// which at most two for 256 and one for 512 fit a CU's share; kUnroll: entries per
+// lane.
 template <class Kill>
-__global__ __launch_bounds__(256) void ac6_jump(Kill kill, int* jp, uint32_t* l0, uint32_t* l1,
-                                                uint32_t* q, int* ctr, int max_rounds,
-                                                int budget) {
-    __shared__ uint32_t buf[kJumpBuf];   // hand-back items of removed vertices
-    __shared__ int s_nbuf, s_base, s_wave[256 / kWave];
+__global__ __launch_bounds__(Kill::kThreads) void ac6_jump(Kill kill, int* jp, uint32_t* l0,
+                                                uint32_t* l1, uint32_t* q, int* ctr,
+                                                int max_rounds, int budget) {
+    constexpr int U = Kill::kUnroll;
+    __shared__ uint32_t buf[Kill::kItems ? kJumpBuf : 1];   // hand-back items of removed vertices
+    __shared__ int s_nbuf, s_base, s_wave[Kill::kThreads / kWave];
     __shared__ uint64_t red[16];
     if (ld_dev(ctr + kHyStop)) return;   // AC-6 rounds reached the fixed point
     if (threadIdx.x == 0) s_nbuf = 0;
@@ -89,38 +99,41 @@ __global__ __launch_bounds__(256) void ac6_jump(Kill kill, int* jp, uint32_t* l0
             add_dev(ctr + kJWork, cnt);
         }
         uint64_t done = 0;
-        const int step = gridDim.x * blockDim.x * kJumpUnroll;
-        for (int base = blockIdx.x * blockDim.x * kJumpUnroll; base < cnt; base += step) {
+        const int step = gridDim.x * blockDim.x * U;
+        for (int base = blockIdx.x * blockDim.x * U; base < cnt; base += step) {
             // anc[k][h]: where v[k]'s link leads after h + 1 links
-            int v[kJumpUnroll], anc[kJumpUnroll][kJumpHops];
-            uint32_t ent[kJumpUnroll];
+            int v[U], anc[U][kJumpHops];
+            uint32_t ent[U];
 #pragma unroll
-            for (int k = 0; k < kJumpUnroll; ++k) {
+            for (int k = 0; k < U; ++k) {
                 const int i = base + k * blockDim.x + threadIdx.x;
                 ent[k] = i < cnt ? (uint32_t)ld_dev((const int*)lin + i) : kNone;
             }
 #pragma unroll
-            for (int k = 0; k < kJumpUnroll; ++k) {
+            for (int k = 0; k < U; ++k) {
                 v[k] = (int)(ent[k] & ~kRootBit);
                 anc[k][0] = (ent[k] != kNone && !(ent[k] & kRootBit)) ? ld_dev(jp + v[k]) : -1;
             }
-            // further links, each one more dependent load; a link is followed
-            // only from a member (a root's link is itself or < 0)
+            // further links, each one more dependent load, as long as a lane of
+            // the wavefront has one; a link is followed only from a member (a
+            // root's link is itself or < 0).  In round 0 they may come from the
+            // caches: a link this round has since replaced leads to the same root.
 #pragma unroll
             for (int h = 1; h < kJumpHops; ++h)
 #pragma unroll
-                for (int k = 0; k < kJumpUnroll; ++k) {
+                for (int k = 0; k < U; ++k) {
                     const int a = anc[k][h - 1];
                     const bool member = a >= 0 && (h < 2 || a != anc[k][h - 2]);
-                    anc[k][h] = member ? ld_dev(jp + a) : a;
+                    anc[k][h] = a;
+                    if (ballot(member)) anc[k][h] = member ? (r == 0 ? jp[a] : ld_dev(jp + a)) : a;
                 }
             int c = 0;
-            uint32_t item[kJumpUnroll][kJumpItems];
-            bool keep[kJumpUnroll];
+            uint32_t item[U][Kill::kItems ? kJumpItems : 1];
+            bool keep[U];
 #pragma unroll
-            for (int k = 0; k < kJumpUnroll; ++k) {
+            for (int k = 0; k < U; ++k) {
 #pragma unroll
-                for (int j = 0; j < kJumpItems; ++j) item[k][j] = kNone;
+                for (int j = 0; Kill::kItems && j < kJumpItems; ++j) item[k][j] = kNone;
                 keep[k] = false;
                 bool dies = false;
                 if (ent[k] == kNone) {
@@ -158,16 +171,19 @@ __global__ __launch_bounds__(256) void ac6_jump(Kill kill, int* jp, uint32_t* l0
                     }
                 }
                 if (dies) {
-                    kill(v[k], item[k]);
+                    if constexpr (Kill::kItems)
+                        kill(v[k], item[k]);
+                    else
+                        kill(v[k]);
                     killed += 1;
                 }
             }
             int slot = block_append_base(c, ctr + kJCnt0 + (r + 1) % 3, nullptr, s_wave, &s_base);
 #pragma unroll
-            for (int k = 0; k < kJumpUnroll; ++k) {
+            for (int k = 0; k < U; ++k) {
                 if (keep[k]) st_dev((int*)lout + slot++, v[k]);
 #pragma unroll
-                for (int j = 0; j < kJumpItems; ++j) {
+                for (int j = 0; Kill::kItems && j < kJumpItems; ++j) {
                     const uint64_t mask = ballot(item[k][j] != kNone);
                     if (mask) {
                         int wbase = 0;
@@ -178,14 +194,16 @@ __global__ __launch_bounds__(256) void ac6_jump(Kill kill, int* jp, uint32_t* l0
                     }
                 }
             }
-            __syncthreads();
-            if (s_nbuf > kJumpBuf - kJumpStep) flush();
+            if constexpr (Kill::kItems) {
+                __syncthreads();
+                if (s_nbuf > kJumpBuf - kJumpStep) flush();
+            }
         }
         done = block_sum(done, red);
         if (threadIdx.x == 0 && done) add_dev(ctr + kJDone0 + r % 3, (int)done);
         if (!grid_barrier(ctr + kBarCount, ctr + kBarGen, ctr + kStall, budget)) break;
     }
-    flush();
+    if constexpr (Kill::kItems) flush();
     killed = block_sum(killed, red);
     if (threadIdx.x == 0 && killed) add_dev(ctr + kJKilled, (int)killed);
 }

@@ -64,8 +64,8 @@
 //
 // These serve the implicit graph, batches of graphs too large for a workgroup
 // and the fixed-memory entry point.  Other explicit graphs go to one workgroup
-// (small.hip) or to the rounds over watched supports (ac6_watch.h), which end in the kernels above when a graph
-// is too deep for them.
+// (small.hip) or to the rounds over watched supports (ac6_watch.h), which end in
+// the kernels above when a graph is too deep for them.
 #include "trim_device.h"
 #include "trim_stats.h"
 #include "trim_internal.h"

@@ -36,10 +36,11 @@ static_assert(kPerT == 16, "in-tile prefixes assume 16 edges per thread");
 struct Levels {
     const float* key;
     float hi, scale;
-    __device__ __forceinline__ int operator()(long long p) const {
-        const int k = (int)((hi - key[p]) * scale);
+    __device__ __forceinline__ int of(float x) const {
+        const int k = (int)((hi - x) * scale);
         return k < 0 ? 0 : (k >= kBuckets ? kBuckets - 1 : k);
     }
+    __device__ __forceinline__ int operator()(long long p) const { return of(key[p]); }
 };
 
 // kBuckets counters of 16 bits in four words (a count never exceeds kTileE).
@@ -568,18 +569,22 @@ __global__ __launch_bounds__(kWave) void scan_apply(int* tcnt, long long T, cons
 // starts at row_off of the tile's first source, and the last one ends where
 // the list holding the tile's last edge ends.  A start before the tile or an
 // end after it uses counts over the part of the list outside the tile.
+//
+// What bounds it: vector instructions (196 a chunk of 64 edges, 1.34 ms for the
+// 2.7 * 10^8 edges of R-MAT 24), and waiting while few workgroups fit the LDS.
+// 1.75 ms there, 2.51 with keys and levels passed through LDS one load at a time,
+// masks stored by single lanes and every edge written to its own place.
 constexpr int kChunks = kTileE / kWave;             // 64
 constexpr int kChunksPerWave = kChunks / kTileWaves;   // 16
 static_assert(kChunks == kWave, "chunk prefixes are scanned one chunk per lane");
 
 __device__ __forceinline__ uint64_t lanes_lt(int l) { return (1ull << l) - 1ull; }
 
-__global__ __launch_bounds__(kTileT, 4) void order_place(const int* row_off, int n, long long m,
+__global__ __launch_bounds__(kTileT, 5) void order_place(const int* row_off, int n, long long m,
                                                       const int* col, Levels level,
                                                       const int* tinfo, const int* tpre,
                                                       int* col_out) {
-    __shared__ int8_t lvl[kTileE];                      // level of each edge, -1 past the end
-    __shared__ int cols[kTileE];
+    __shared__ int out[kTileE];                         // the lists that lie in the tile
     __shared__ uint64_t fm[kChunks];                    // bit = a list other than the first starts
     __shared__ uint64_t cm[kChunks][kBuckets + 1];      // lanes of the chunk with level < k
     __shared__ int cpre[kChunks + 1][kBuckets + 1];     // edges of earlier chunks with level < k
@@ -593,11 +598,14 @@ __global__ __launch_bounds__(kTileT, 4) void order_place(const int* row_off, int
         const long long t0 = t * kTileE;
         const int len = (int)(m - t0 < kTileE ? m - t0 : kTileE);
         const long long t1 = t0 + len;
-        for (int i = 0; i < kChunksPerWave; ++i) {
-            const int j = (wv * kChunksPerWave + i) * kWave + l;
-            cols[j] = j < len ? col[t0 + j] : 0;
-            lvl[j] = (int8_t)(j < len ? level(t0 + j) : -1);
-        }
+        // the wave's chunks, all their keys in flight; four bits a level
+        float key[kChunksPerWave];
+#pragma unroll
+        for (int i = 0; i < kChunksPerWave; ++i)
+            key[i] = level.key[t0 + min((wv * kChunksPerWave + i) * kWave + l, len - 1)];
+        uint64_t lvl = 0;
+#pragma unroll
+        for (int i = 0; i < kChunksPerWave; ++i) lvl |= (uint64_t)level.of(key[i]) << (4 * i);
         if (threadIdx.x < kChunks) fm[threadIdx.x] = 0;
         const int uf = clamp_vertex(tinfo[3 * t], n);
         const long long sf = tinfo[3 * t + 1];
@@ -609,16 +617,26 @@ __global__ __launch_bounds__(kTileT, 4) void order_place(const int* row_off, int
             if (x >= len) break;
             atomicOr((unsigned long long*)&fm[x >> 6], 1ull << (x & 63));
         }
+        // lane k <= 16 works out "level < k" of a chunk from the ballots of the
+        // levels' four bits (a compare, two moves and a store by one lane for
+        // every k kept the LDS and the vector units busier)
+        static_assert(kBuckets == 16, "levels of four bits");
 #pragma unroll 1
-        for (int i = 0; i < kChunksPerWave; ++i) {   // a wave reads back only its own chunks
+        for (int i = 0; i < kChunksPerWave; ++i) {
             const int c = wv * kChunksPerWave + i;
-            const int k = lvl[c * kWave + l];
-            uint64_t below = 0;
-            for (int q = 0; q < kBuckets; ++q) {
-                if (l == 0) cm[c][q] = below;
-                below |= ballot(k == q);
+            const int k = (int)(lvl >> (4 * i)) & (kBuckets - 1);
+            const int left = len - c * kWave;
+            uint64_t eq = left >= kWave ? ~0ull : left > 0 ? lanes_lt(left) : 0ull;
+            uint64_t below = l == kBuckets ? eq : 0ull;
+#pragma unroll
+            for (int b = 3; b >= 0; --b) {
+                const uint64_t plane = ballot((k >> b) & 1);
+                const uint64_t mine = (l >> b) & 1 ? ~0ull : 0ull;
+                below |= eq & mine & ~plane;
+                eq &= ~(plane ^ mine);
             }
-            if (l == 0) cm[c][kBuckets] = below;
+            if (l == kBuckets) below = left >= kWave ? ~0ull : left > 0 ? lanes_lt(left) : 0ull;
+            if (l <= kBuckets) cm[c][l] = below;
         }
         __syncthreads();
         for (int k = wv; k <= kBuckets; k += kTileWaves) {   // lane = chunk
@@ -690,25 +708,40 @@ __global__ __launch_bounds__(kTileT, 4) void order_place(const int* row_off, int
             const int c = x >> 6;
             return cpre[c][kk] + popc(cm[c][kk] & lanes_lt(x & 63));
         };
-#pragma unroll 2
+        // lists that lie in the tile are put together in LDS and written in order;
+        // the others' edges go where they belong one by one
+        const int srel = (int)(sf - t0), erel = (int)(el - t0);
+        const int from = sf < t0 ? (fm[0] ? __ffsll((unsigned long long)fm[0]) - 1 : firstst[0]) : 0;
+        const int to = el > t1 ? (fm[kChunks - 1] ? kTileE - 1 - __clzll((long long)fm[kChunks - 1])
+                                                  : lastst[kChunks - 1])
+                               : len;
+#pragma unroll 4
         for (int i = 0; i < kChunksPerWave; ++i) {
             const int c = wv * kChunksPerWave + i;
             const int j = c * kWave + l;
+            const int w = col[t0 + min(j, len - 1)];
             if (j < len) {
-                const int k = lvl[j];
+                const int k = (int)(lvl >> (4 * i)) & (kBuckets - 1);
                 const uint64_t f = fm[c];
-                const uint64_t upto = f & (lanes_lt(l) | (1ull << l));
-                const uint64_t after = f & ~(lanes_lt(l) | (1ull << l));
+                const uint64_t upto = f & (2 * (1ull << l) - 1), after = f ^ upto;
                 const int s = upto ? c * kWave + 63 - __clzll((long long)upto) : lastst[c];
                 const int e = after ? c * kWave + __ffsll((unsigned long long)after) - 1 : firstst[c];
-                const long long sg = s == 0 ? sf : t0 + s;
-                const long long eg = e == len ? el : t0 + e;
-                const int lbe = eg > t1 ? loutc[1][k] : Lb(e, k);
-                const int lbs = sg < t0 ? loutc[0][k + 1] : Lb(s, k + 1);
-                const long long pos = sg + lbe - lbs + (Lb(j, k + 1) - Lb(j, k));
-                if (pos >= sg && pos < eg) col_out[pos] = cols[j];
+                // positions from the tile's start (edges are numbered in 31 bits)
+                const int sr = s == 0 ? srel : s, er = e == len ? erel : e;
+                const int lbe = er > len ? loutc[1][k] : Lb(e, k);
+                const int lbs = sr < 0 ? loutc[0][k + 1] : Lb(s, k + 1);
+                const uint64_t same = cm[c][k + 1] & ~cm[c][k] & lanes_lt(l);
+                const int pos = sr + lbe - lbs + cpre[c][k + 1] - cpre[c][k] + popc(same);
+                if (pos >= sr && pos < er) {
+                    if (j >= from && j < to)
+                        out[pos] = w;
+                    else
+                        col_out[t0 + pos] = w;
+                }
             }
         }
+        __syncthreads();
+        for (int j = from + threadIdx.x; j < to; j += kTileT) col_out[t0 + j] = out[j];
         __syncthreads();
     }
 }

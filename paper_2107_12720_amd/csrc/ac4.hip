@@ -72,7 +72,8 @@ constexpr int kShareEvery4 = 16;
 // removals and nearly all have short lists or none: through the shared queue
 // the 9.4 * 10^6 of R-MAT 24, 2.1 * 10^6 reverse edges in all, took 3.4 of
 // 3.7 ms.  A wavefront takes 64 consecutive vertices at a time; lists of up to
-// kCoop entries are walked by their lanes, longer ones by the wavefront.
+// kCoop entries are walked by their lanes, longer ones by the wavefront.  Steps
+// go to the workgroups by step_of: in turn 340 us on R-MAT 24, so 296.
 constexpr int kFirstBuf = 2048;   // removed vertices kept in LDS before one reservation
 
 template <bool kTwo>
@@ -97,10 +98,9 @@ __global__ __launch_bounds__(256) void ac4_first(const int* rrow_off, const int*
         if (slot >= 0) q[slot] = make_item(0, u);
     };
     uint64_t edges = 0;
-    const int waves = (gridDim.x * blockDim.x) / kWave;
-    const int wid = (blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-    for (long long base = (long long)wid * kWave; base < n; base += (long long)waves * kWave) {
-        const int v = (int)base + lane_id();
+    const int steps = (int)((n + (long long)blockDim.x - 1) / blockDim.x);
+    for (int b0 = blockIdx.x; b0 < steps; b0 += gridDim.x) {
+        const int v = step_of(b0, steps) * (int)blockDim.x + (int)threadIdx.x;
         const int x = v < n ? v : n - 1;
         const int b = row_off[x], be = row_off[x + 1], rb = rrow_off[x], re = rrow_off[x + 1];
         const bool gone = v < n && (b == be || (kTwo && rb == re) ||

@@ -1239,7 +1239,10 @@ hipError_t ac6_watch_run(const trim_csr_t& g, const Work& w, const LaunchCfg& lc
     a1.dead = y[0];
     const ExplicitView v{g.row_off, g.col};
     const int level_blocks = phase_blocks(n, lc.cus);
-    const int sweep_blocks = grid_for(n, (long long)B * kSweepFlight, lc.cus * 8);
+    // vertices of many successors lie together: dealt out to eight workgroups per CU
+    // in turn the sweep of R-MAT 26 takes 818 us, to 32 657
+    const int sweep_blocks =
+        grid_for(n, (long long)B * kSweepFlight, min(lc.cus * 32, kPartStride));
     {
         Timed t(lc, "ac6_init");
         hipLaunchKernelGGL(watch_init, dim3(grid_for((n + 3) / 4, 256, 16384)), dim3(256), 0, st,
@@ -1252,7 +1255,7 @@ hipError_t ac6_watch_run(const trim_csr_t& g, const Work& w, const LaunchCfg& lc
                            : lc.forest ? watch_sweep<kWatchForest>
                                        : watch_sweep<kWatchStep>;
         hipLaunchKernelGGL(sweep, dim3(sweep_blocks), dim3(B), 0, st, a1, (long long)g.m, y[1],
-                           w.jp, w.e, w.part);
+                           preset != nullptr, w.jp, w.e, w.part);
     }
     const int rb = grid_for(n, (long long)kRoundThreads * kRoundFlight, lc.cus * 2);
     if (R) {

@@ -66,7 +66,8 @@ __global__ __launch_bounds__(1024) void two_watch_sweep(TwoWatch t, long long m,
     uint64_t edges = 0, removed = 0;
     const int n = t.o.n, per = U * blockDim.x;
     const int steps = (n + per - 1) / per;
-    for (int st = blockIdx.x; st < steps; st += gridDim.x) {
+    for (int b0 = blockIdx.x; b0 < steps; b0 += gridDim.x) {
+        const int st = step_of(b0, steps);
         const int base = ((t.o.sched & TRIM_SCHED_REVERSE) ? steps - 1 - st : st) * per;
         int b[2][U], e[2][U], p[2][U], w[2][U];
         bool live[U], ok[2][U];

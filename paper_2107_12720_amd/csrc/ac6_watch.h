@@ -29,13 +29,14 @@
 //                 vertex left joins its support's list, and the propagation
 //                 over lists finishes.
 //
-// What bounds it: the sweep by its gathers of row_off, col and statuses (67 us
-// for R-MAT 22, edge factor 16, 200 with the exchanges), a round of all vertices
+// What bounds it: the sweep by its gathers of row_off, col and statuses (50 us
+// for R-MAT 22, edge factor 16; 200 with the exchanges), a round of all vertices
 // by reading sup (12 us at 2^22) and by the latency of four dependent loads,
 // about 5 us, plus 2 for the barrier in the tail.  R-MAT 22 with a chain of
-// 2*10^5: 494 -> 260 us in all; core+tail of 10^5 vertices 402 -> 266, of 2^20
-// 564 -> 455.  Late registration, R-MAT 26 with four counted rounds, whose fourth
-// removes 1 vertex: 2.85 -> 1.33 ms (5 * 10^7 list exchanges took 2.65).
+// 2*10^5: 494 -> 210 us in all; core+tail of 10^5 vertices 402 -> 255, of 2^20
+// 564 -> 380.  Late registration, R-MAT 26 with four counted rounds: 0.90 -> 0.84
+// ms if three reach the fixed point, 2.85 -> 1.1 if not (5 * 10^7 list exchanges
+// took 2.65).
 #pragma once
 #include "trim_device.h"
 #include "block_append.h"
@@ -96,7 +97,8 @@ __global__ void watch_init(const int* row_off, int n, bool wide, const uint32_t*
 // live successor are removed here.
 template <WatchMode kMode>
 __global__ __launch_bounds__(1024) void watch_sweep(WatchState a, long long m, const uint32_t* y1,
-                                                    int* jp, uint32_t* jlist, uint64_t* part) {
+                                                    bool preset, int* jp, uint32_t* jlist,
+                                                    uint64_t* part) {
     constexpr int U = kSweepFlight;
     constexpr bool kForest = kMode == kWatchForest;
     __shared__ int s_wave[1024 / kWave], s_base;
@@ -104,7 +106,8 @@ __global__ __launch_bounds__(1024) void watch_sweep(WatchState a, long long m, c
     uint64_t edges = 0, removed = 0;
     const int n = a.n, per = U * blockDim.x;
     const int steps = (n + per - 1) / per;
-    for (int st = blockIdx.x; st < steps; st += gridDim.x) {
+    for (int b0 = blockIdx.x; b0 < steps; b0 += gridDim.x) {
+        const int st = step_of(b0, steps);
         const int base = ((a.sched & TRIM_SCHED_REVERSE) ? steps - 1 - st : st) * per;
         int b[U], e[U], p[U], w[U];
         bool ok[U];
@@ -113,13 +116,20 @@ __global__ __launch_bounds__(1024) void watch_sweep(WatchState a, long long m, c
             const int v = base + k * blockDim.x + threadIdx.x, x = min(v, n - 1);
             b[k] = __builtin_nontemporal_load(a.row_off + x);
             e[k] = __builtin_nontemporal_load(a.row_off + x + 1);
-            ok[k] = v < n && !status_bit(y1, x);
+            ok[k] = v < n;
+        }
+        if (preset) {
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const int v = base + k * blockDim.x + threadIdx.x;
+                ok[k] = ok[k] && !status_bit(y1, min(v, n - 1));
+            }
         }
 #pragma unroll
         for (int k = 0; k < U; ++k) {
-            if (!ok[k]) e[k] = b[k];   // removed already, or past the end
             p[k] = b[k];
-            w[k] = ok[k] ? __builtin_nontemporal_load(a.col + b[k]) : 0;
+            w[k] = b[k] < e[k] ? __builtin_nontemporal_load(a.col + b[k]) : 0;
+            if (!ok[k]) e[k] = b[k];   // removed already, or past the end
         }
 #pragma unroll
         for (int k = 0; k < U; ++k) ok[k] = !status_bit(y1, w[k]) && b[k] < e[k];
@@ -192,20 +202,26 @@ struct WatchKill {
 // round r - 1 in LDS, or NULL.
 template <bool kFresh>
 __device__ __forceinline__ uint32_t watch_vertices(const WatchState& a, int r,
-                                                   const uint32_t* sflt, int2* found,
+                                                   const uint32_t* sflt, int* found,
                                                    WatchSums& t) {
     constexpr int U = kRoundFlight;
     found += threadIdx.x / kWave * (U * kWave);
     uint32_t removed = 0;
-    const int n = a.n, stride = gridDim.x * blockDim.x;
-    for (int base = blockIdx.x * blockDim.x + threadIdx.x; base < n; base += U * stride) {
-        int s[U];
+    const int n = a.n, runs = (n + 3) >> 2;
+    const int blocks = (runs + (int)blockDim.x - 1) / (int)blockDim.x;
+    for (int b0 = blockIdx.x; b0 < blocks; b0 += U / 4 * gridDim.x) {
+        int s[U], q[U / 4];
         bool back[U];
 #pragma unroll
+        for (int g = 0; g < U / 4; ++g) {
+            const int b = b0 + g * (int)gridDim.x;
+            q[g] = b < blocks ? step_of(b, blocks) * (int)blockDim.x + (int)threadIdx.x : runs;
+            const int4 y = reinterpret_cast<const int4*>(a.sup)[min(q[g], runs - 1)];
+            s[4 * g] = y.x, s[4 * g + 1] = y.y, s[4 * g + 2] = y.z, s[4 * g + 3] = y.w;
+        }
+#pragma unroll
         for (int k = 0; k < U; ++k) {
-            const int v = base + k * stride;
-            s[k] = a.sup[v < n ? v : n - 1];
-            back[k] = v < n && s[k] >= 0;
+            back[k] = 4 * q[k >> 2] + (k & 3) < n && s[k] >= 0;
         }
         if (sflt) {
 #pragma unroll
@@ -223,12 +239,12 @@ __device__ __forceinline__ uint32_t watch_vertices(const WatchState& a, int r,
         }
 #pragma unroll
         for (int k = 0; k < U; ++k) back[k] = back[k] && ((x[k] >> (s[k] & 31)) & 1u);
-        const int cnt = watch_found(back, s, base, stride, found);
+        const int cnt = watch_found(back, q, found);
         for (int i = lane_id(); i < cnt; i += kWave) {
-            const int v = found[i].x;
+            const int v = found[i];
             int pos, to;
             t.visited += 1;
-            if (watch_scan<kFresh>(a, v, found[i].y, pos, to, t.edges)) {
+            if (watch_scan<kFresh>(a, v, a.sup[v], pos, to, t.edges)) {
                 a.sup[v] = to;
                 *rec_pos(a.rec, v) = pos;
                 t.joins += 1;
@@ -265,14 +281,15 @@ __global__ __launch_bounds__(kRoundThreads) void watch_counted(WatchState a, int
                                                                uint32_t* ynext) {
     constexpr int U = kRoundFlight;
     __shared__ __align__(8) uint32_t s_flt[WatchFilter::kMaxWords];
-    __shared__ int2 s_found[kRoundThreads * U];
+    __shared__ int s_found[kRoundThreads * U];
     __shared__ uint64_t red[16];
     if (counted_done(a.ctr, r)) return;
     const int before = ld_dev(a.ctr + kHyDead0 + (r - 1) % 3);
     const uint32_t* sflt = watch_stage<kRoundThreads, false>(a, r, before, s_flt);
-    const int n = a.n, stride = gridDim.x * blockDim.x;
+    const int n = a.n, stride = gridDim.x * blockDim.x, runs = (n + 3) >> 2;
+    const int blocks = (runs + (int)blockDim.x - 1) / (int)blockDim.x;
     const int tid = blockIdx.x * blockDim.x + threadIdx.x;
-    int2* found = s_found + threadIdx.x / kWave * (U * kWave);
+    int* found = s_found + threadIdx.x / kWave * (U * kWave);
     for (int i = tid; i < (n + 31) >> 5; i += stride) {
         const uint32_t b = ycur[i];
         if (b & ~ynext[i]) atomicOr(ynext + i, b);
@@ -281,15 +298,20 @@ __global__ __launch_bounds__(kRoundThreads) void watch_counted(WatchState a, int
     now.dead = const_cast<uint32_t*>(ycur);
     uint64_t edges = 0;
     uint32_t removed = 0, entries = 0;
-    for (int base = tid; base < n; base += U * stride) {
-        int s[U];
+    for (int b0 = blockIdx.x; b0 < blocks; b0 += U / 4 * gridDim.x) {
         uint32_t x[U];
+        int s[U], q[U / 4];
         bool back[U];
 #pragma unroll
+        for (int g = 0; g < U / 4; ++g) {
+            const int b = b0 + g * (int)gridDim.x;
+            q[g] = b < blocks ? step_of(b, blocks) * (int)blockDim.x + (int)threadIdx.x : runs;
+            const int4 y = reinterpret_cast<const int4*>(a.sup)[min(q[g], runs - 1)];
+            s[4 * g] = y.x, s[4 * g + 1] = y.y, s[4 * g + 2] = y.z, s[4 * g + 3] = y.w;
+        }
+#pragma unroll
         for (int k = 0; k < U; ++k) {
-            const int v = base + k * stride;
-            s[k] = a.sup[v < n ? v : n - 1];
-            back[k] = v < n && s[k] >= 0;
+            back[k] = 4 * q[k >> 2] + (k & 3) < n && s[k] >= 0;
             entries += back[k];
         }
         if (sflt) {
@@ -303,11 +325,11 @@ __global__ __launch_bounds__(kRoundThreads) void watch_counted(WatchState a, int
         for (int k = 0; k < U; ++k) x[k] = back[k] ? ycur[(s[k] & kSupMask) >> 5] : 0;
 #pragma unroll
         for (int k = 0; k < U; ++k) back[k] = back[k] && ((x[k] >> (s[k] & 31)) & 1u);
-        const int cnt = watch_found(back, s, base, stride, found);
+        const int cnt = watch_found(back, q, found);
         for (int i = lane_id(); i < cnt; i += kWave) {
-            const int v = found[i].x;
+            const int v = found[i];
             int pos, to;
-            if (watch_scan<false>(now, v, found[i].y, pos, to, edges)) {
+            if (watch_scan<false>(now, v, a.sup[v], pos, to, edges)) {
                 a.sup[v] = to;
                 *rec_pos(a.rec, v) = pos;
             } else {
@@ -343,8 +365,9 @@ __global__ __launch_bounds__(1024) void watch_collect(WatchState a, int* jp, uin
     __shared__ uint64_t red[16];
     if (counted_done(a.ctr, a.r1)) return;
     WatchSums t;
-    const int n = a.n, per = U * blockDim.x;
-    for (int base = blockIdx.x * per; base < n; base += gridDim.x * per) {
+    const int n = a.n, per = U * blockDim.x, steps = (n + per - 1) / per;
+    for (int b0 = blockIdx.x; b0 < steps; b0 += gridDim.x) {
+        const int base = step_of(b0, steps) * per;
         int s[U], e[U], p[U];
         uint32_t x[U];
 #pragma unroll
@@ -396,7 +419,7 @@ __global__ __launch_bounds__(1024) void watch_collect(WatchState a, int* jp, uin
 template <bool kFilter>
 __global__ __launch_bounds__(kRoundThreads) void watch_round(WatchState a, int r) {
     __shared__ __align__(8) uint32_t sflt[kFilter ? WatchFilter::kMaxWords : 2];
-    __shared__ int2 found[kRoundThreads * kRoundFlight];
+    __shared__ int found[kRoundThreads * kRoundFlight];
     __shared__ uint64_t red[16];
     if (ld_dev(a.ctr + kHyStop)) return;
     const int before = removed_before(a, r);
@@ -417,7 +440,7 @@ __global__ __launch_bounds__(kRoundThreads) void watch_round(WatchState a, int r
 __global__ __launch_bounds__(kRoundThreads) void watch_tail(WatchState a, int r0, int last,
                                                           int* head, int* ext, int budget) {
     __shared__ __align__(8) uint32_t sflt[WatchFilter::kMaxWords];
-    __shared__ int2 found[kRoundThreads * kRoundFlight];
+    __shared__ int found[kRoundThreads * kRoundFlight];
     __shared__ uint64_t red[16];
     if (ld_dev(a.ctr + kHyStop)) return;
     WatchSums t;

@@ -441,8 +441,9 @@ __global__ __launch_bounds__(256) void scc_pull(int n, const int* row_off, const
     __shared__ unsigned long long red[16];
     if (misc[kSccTotal] < pull) return;
     unsigned long long seen = 0;
-    for (int base = blockIdx.x * blockDim.x; base < n; base += gridDim.x * blockDim.x) {
-        const int v = base + threadIdx.x;
+    const int steps = (n + (int)blockDim.x - 1) / (int)blockDim.x;
+    for (int b0 = blockIdx.x; b0 < steps; b0 += gridDim.x) {
+        const int v = step_of(b0, steps) * (int)blockDim.x + (int)threadIdx.x;
         const bool in = v < n && has_bit(live, v);
         const int f = in ? flags[v] : 3;
         int got = 0;

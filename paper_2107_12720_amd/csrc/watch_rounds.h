@@ -134,14 +134,17 @@ __device__ __forceinline__ bool watch_scan(const WatchState& a, int v, int s, in
 // The wavefront's hand-backs among the U vertices of each lane, put side by side
 // in its part of `found` (U * 64 entries): their scans, chains of four dependent
 // loads, then run 64 at a time instead of a few lanes' at a time, U times.
+// A lane polls runs of four vertices, the supports of each from one 16-byte load;
+// vertex k is number k & 3 of run q[k >> 2].
 template <int U>
-__device__ __forceinline__ int watch_found(const bool (&back)[U], const int (&s)[U], int v0,
-                                           int stride, int2* found) {
+__device__ __forceinline__ int watch_found(const bool (&back)[U], const int (&q)[U / 4],
+                                           int* found) {
     int cnt = 0;
 #pragma unroll
     for (int k = 0; k < U; ++k) {
         const uint64_t mask = ballot(back[k]);
-        if (back[k]) found[cnt + popc(mask & lanes_below())] = make_int2(v0 + k * stride, s[k]);
+        if (back[k]) found[cnt + popc(mask & lanes_below())] =
+                4 * q[k >> 2] + (k & 3);
         cnt += popc(mask);
     }
     __builtin_amdgcn_wave_barrier();

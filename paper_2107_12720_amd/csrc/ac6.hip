@@ -1268,7 +1268,8 @@ hipError_t ac6_watch_run(const trim_csr_t& g, const Work& w, const LaunchCfg& lc
     }
     if (lc.forest) {
         Timed t(lc, "ac6_jump");
-        hipLaunchKernelGGL(ac6_jump<WatchKill>, dim3((level_blocks + 1) / 2), dim3(kRoundThreads), 0, st,
+        hipLaunchKernelGGL(ac6_jump<WatchKill>, dim3(watch_jump_blocks(n, lc.cus)),
+                           dim3(kRoundThreads), 0, st,
                            WatchKill{w.d, dead}, w.jp, w.e, w.e + n, w.q, w.ctr,
                            jump_rounds(n), lc.budget);
     }

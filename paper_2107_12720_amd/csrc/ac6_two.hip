@@ -600,7 +600,7 @@ hipError_t two_watch_run(const TwoGraph& g, long long m, int n, const Work& w, c
     }
     if (lc.forest) {
         Timed tm(lc, "ac6t_jump");
-        hipLaunchKernelGGL(ac6_jump<TwoWatchKill>, dim3((phase_blocks(n, lc.cus) + 1) / 2),
+        hipLaunchKernelGGL(ac6_jump<TwoWatchKill>, dim3(watch_jump_blocks(n, lc.cus)),
                            dim3(kRoundThreads), 0, st, TwoWatchKill{w.d, dead}, w.jp, w.e, w.e + n, x.q, w.ctr,
                            jump_rounds(n), lc.budget);
     }

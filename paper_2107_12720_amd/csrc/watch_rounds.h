@@ -37,6 +37,14 @@ constexpr int kRoundFlight = 8;
 constexpr int kRoundThreads = 512;      // the tail: one workgroup per CU
 constexpr int kTailPer = 2;
 
+// Workgroups of the forest collapse over watched supports: one per 1,024 vertices
+// (a bare path of 10^5: 121 us a call, with one per 8,192 359), at most one
+// per CU.
+inline int watch_jump_blocks(long long n, int cus) {
+    const long long b = n / 1024;
+    return (int)(b < 8 ? 8 : b > cus ? cus : b);
+}
+
 // Removals of three rounds in rotation, hashed into 2^log bits each.  (Small
 // enough for every workgroup to stage a round's in a microsecond or two, and
 // large enough that setting its bits does not queue at a few lines: with a

@@ -44,6 +44,9 @@ INT32_VALU_PEAK_OPS = 256 * 64 * 2.4e9
 # one of them stays valid while these are unchanged (other kernel files are
 # separate translation units and cannot change them).
 KERNEL_SOURCES = ("paper_2107_12720_amd/csrc/ac6.hip", "paper_2107_12720_amd/csrc/ac6_support.h",
+                  "paper_2107_12720_amd/csrc/ac6_watch.h",
+                  "paper_2107_12720_amd/csrc/watch_rounds.h",
+                  "paper_2107_12720_amd/csrc/forest_jump.h",
                   "paper_2107_12720_amd/csrc/trim_device.h",
                   "paper_2107_12720_amd/csrc/trim_stats.h",
                   "paper_2107_12720_amd/csrc/trim_internal.h", "include/trim.h")
@@ -90,43 +93,45 @@ def measured_traffic(kernel, workload, workers=None):
     return d.get("bytes_per_launch")
 
 
-def prop_bytes(st, t6):
-    """Algorithmic bytes of the propagation after the first sweep (its
-    level-synchronous phases and its asynchronous tail together): 8 B per
-    successor check (target id + target status), 16 B per close (two list-head
-    exchanges), 16 B per join (record store + head CAS), 8 B per list member
-    handed back (its record)."""
-    return (8 * (t6 - st["edges_sweep"]) + 16 * st["closes"] + 16 * st["joins"]
-            + 8 * st["visited"])
+def prop_bytes(n, st, t6):
+    """Algorithmic bytes of the propagation after the first sweep (the rounds
+    over watched supports and what lists a deep graph still needs): 4 B per
+    vertex and round (its support; its status is a bit of a cache-resident
+    bitmap), 8 B per successor check (target id + its status), 8 B per support
+    found (its id and position), 4 B per removal."""
+    return (4 * n * st["phases"] + 8 * (t6 - st["edges_sweep"]) + 8 * st["joins"]
+            + 4 * st["closes"])
 
 
 def jump_bytes(st):
     """Algorithmic bytes of the forest collapse: per list entry and round its
     entry, its link and its ancestor's link read, and one link or list entry
-    written (16 B); per removed vertex an 8-byte head exchange and a 4-byte
-    walk item."""
-    return 16 * st["work_items"] + 12 * st["forest"]
+    written (16 B); per removed vertex its support and its status (8 B)."""
+    return 16 * st["work_items"] + 8 * st["forest"]
 
 
 def kernel_bytes(n, st, sw):
-    """Algorithmic bytes of every AC-6 kernel of one trim (sw = the sweep's
-    host counts: checks, joins, casualties, last-successor members).  The
-    propagation's two kernels share one count: both get the combined bytes
-    under the name 'propagation'."""
+    """Algorithmic bytes of every AC-6 kernel of one trim of a large explicit
+    graph (sw = the sweep's host counts: checks, joins, casualties,
+    last-successor members).  The propagation's kernels share one count: all get
+    the combined bytes under the name 'propagation'."""
     checks, joins, cas, members = sw
     forest = st["forest"] > 0
-    return {"ac6_init": 4 * (n + 1) + 8 * n + n // 8,
-            "ac6_sweep": sweep_bytes(n, checks, joins, cas)
+    return {"ac6_init": 4 * (n + 1) + n // 4,
+            "ac6_sweep": sweep_bytes(n, checks)
             + (4 * (joins + cas) + 4 * (members + cas) if forest else 0),
             "ac6_jump": jump_bytes(st),
-            "propagation": prop_bytes(st, st["edges_total"]),
-            "ac6_pack": 8 * n + n // 8}
+            "propagation": prop_bytes(n, st, st["edges_total"]),
+            "ac6_pack": n // 4}
+
+
+PROPAGATION = ("ac6_rounds", "ac6_register", "ac6_levels", "ac6_propagate")
 
 
 def group_times(kavg):
-    """Per-kernel average ms, with the propagation's two kernels summed."""
-    out = {k: v for k, v in kavg.items() if k not in ("ac6_levels", "ac6_propagate")}
-    out["propagation"] = kavg.get("ac6_levels", 0.0) + kavg.get("ac6_propagate", 0.0)
+    """Per-kernel average ms, with the propagation's kernels summed."""
+    out = {k: v for k, v in kavg.items() if k not in PROPAGATION}
+    out["propagation"] = sum(kavg.get(k, 0.0) for k in PROPAGATION)
     return out
 
 
@@ -160,12 +165,11 @@ def sweep_counts(g, chunk=1 << 22):
     return tuple(tot)
 
 
-def sweep_bytes(n, checks, joins, casualties):
-    """Algorithmic bytes of one ac6_sweep launch: 4 B of offsets per vertex, 4 B
-    per successor check (its target id; the target's status is a bit of the
-    n/8-byte sinks bitmap, read once), 16 B per join (head exchange + record
-    store), 4 B per queued casualty."""
-    return 4 * (n + 1) + n // 8 + 4 * checks + 16 * joins + 4 * casualties
+def sweep_bytes(n, checks):
+    """Algorithmic bytes of one first sweep: 4 B of offsets and 4 B of support
+    per vertex, 4 B per successor check (its target id; the target's status is a
+    bit of the n/8-byte sinks bitmap, read once)."""
+    return 4 * (n + 1) + 4 * n + n // 8 + 4 * checks
 
 
 def first_ok(row_off, col, ok):
@@ -228,19 +232,17 @@ def bench_two_sided(ctx, T, g, ro, col, rro_h, rcol_h, reps, with_ac3=True):
     chain_ok = res_c.stats_dict()["n_live"] == 1
     sc, sj, scas, smem, sscan = two_sided_sweep_counts(g, rro_h, rcol_h)
     forest = st6["forest"] > 0
-    # bytes per unit: 4 B per read or write, 8 B per 4-byte atomic, 16 B per
-    # 8-byte exchange (the paper's per-edge and per-vertex terms, both sides);
-    # with the forest collapse the sweep also writes a link per scanned vertex
-    # and a list entry per member and casualty, and the collapse reads and
-    # writes 16 B per list entry and round, and exchanges both pairs (32 B)
-    # and queues an item (4 B) per removal
+    # bytes per unit: 4 B per read or write (the paper's per-edge and per-vertex
+    # terms, both sides: offsets, a support per side, a check's target); with the
+    # forest collapse the sweep also writes a link per scanned vertex and a list
+    # entry per member and casualty; a round reads both supports of every vertex
     algo = {
-        "ac6t_init": 8 * (n + 1) + 16 * n + n // 8,
-        "ac6t_sweep": 8 * (n + 1) + n // 8 + 4 * sc + 16 * sj + 4 * scas
+        "ac6t_init": 8 * (n + 1) + n // 4,
+        "ac6t_sweep": 8 * (n + 1) + n // 8 + 4 * sc + 4 * (n + sj // 2)
         + (4 * sscan + 4 * (smem + scas) if forest else 0),
-        "ac6t_jump": 16 * st6["work_items"] + 36 * st6["forest"],
-        "ac6t_propagate": (8 * (st6["edges_total"] - st6["edges_sweep"]) + 32 * st6["closes"]
-                           + 16 * st6["joins"] + 8 * st6["visited"]),
+        "ac6t_jump": jump_bytes(st6),
+        "ac6t_rounds": (8 * n * st6["phases"] + 8 * (st6["edges_total"] - st6["edges_sweep"])
+                        + 8 * st6["joins"] + 4 * st6["closes"]),
         "ac6t_pack": 8 * n + n // 8,
     }
     k6 = {k: float(np.mean(v)) for k, v in kt6.items()}
@@ -819,17 +821,14 @@ def bench_explicit26(ctx, T, gg, reps):
                                           stats=st_t, opts=o), reps, (2, 4, 8))
     log(f"explicit26: deferred AC-6 {out['deferred']['fastest_ms']:.3f} ms "
         f"(R = {out['deferred']['fastest_rounds']})")
-    # the dominant kernel of the fastest late-registration run: the first
-    # round without joins.  Algorithmic bytes: 4 B of offsets per vertex, 4 B
-    # per check (the target id; its status is a bit of the cache-resident
-    # sinks bitmap), 8 B per round-list entry written, the bitmap of removals.
+    # the dominant kernel of the fastest late-registration run: the first sweep
     fr = out["deferred"]["by_rounds"][str(out["deferred"]["fastest_rounds"])]
     dsw_ms = fr["kernels_ms"].get("ac6_sweep")
     if dsw_ms:
-        dsw = 4 * (n + 1) + 4 * sw[0] + 8 * sw[1] + n // 8
+        dsw = sweep_bytes(n, sw[0])
         dtr = measured_traffic("ac6_sweep_deferred", "rmat26")
         out["deferred"]["sweep_roofline"] = {
-            "kernel": "ac6_sweep (round 1, no joins)", "algorithmic_bytes": dsw, "avg_ms": dsw_ms,
+            "kernel": "ac6_sweep (round 1)", "algorithmic_bytes": dsw, "avg_ms": dsw_ms,
             "achieved_GBs": dsw / (dsw_ms / 1e3) / 1e9,
             "frac": dsw / (dsw_ms / 1e3) / 1e9 / HBM_PEAK_GBS, "traffic": dtr,
             "traffic_GBs": dtr / (dsw_ms / 1e3) / 1e9 if dtr else None,

@@ -98,7 +98,10 @@ typedef struct {
     int32_t chunk;      /* AC-6: vertices claimed per dynamic work chunk of the first
                            sweep (Section 8, schedule(dynamic, s)); rounded up to a
                            multiple of block; 0 = automatic: 4096, or less for graphs
-                           with fewer than 4096 * 4 vertices per CU (at least 256) */
+                           with fewer than 4096 * 4 vertices per CU (at least 256).
+                           (Explicit graphs, implicit ones up to 2^15 vertices and
+                           two-sided trimming from 4,096 on deal their vertices out in
+                           fixed steps.) */
     int32_t validate;   /* 1 = check offsets/targets on the device first (synchronises) */
     int32_t graph;      /* trim_batch only: 1 = capture the launch sequence into a HIP
                            graph on the first call and replay it while every argument
@@ -134,8 +137,10 @@ typedef struct {
  * in round l - 1.  If a round removes nothing, that is the fixed point and
  * the call ends.  Otherwise round R re-checks every cursor the same way and
  * registers each vertex still live in the supporting set of the successor it
- * stops at, and the AC-6 propagation finishes from there.  The live set is
- * the same as without it.  Traversed edges count every cursor re-check:
+ * stops at, and the AC-6 propagation finishes from there.  (An explicit graph
+ * holds its supports in an array instead and goes on from round R by rounds that
+ * check no cursor again; the counts are the same.)  The live set is the same as
+ * without it.  Traversed edges count every cursor re-check:
  *   edges_total = sum_{dead, deg > 0} (deg + min(R, level - 1) - 1)
  *               + sum_live (fl + K),   K = min(R, max(alpha, 1)),
  * and stats.rechecks (the entries of the round lists from round 2 on) is the
@@ -173,13 +178,14 @@ typedef struct {
 #define TRIM_SCHED_JITTER 2
 
 /*
- * Per-call statistics, written to device memory.  One-sided AC-6 of a graph of
- * up to 65,536 vertices (and 2^21 edges; implicit graphs up to 2^15 vertices)
- * runs in one workgroup, where a vertex finds its support removed by watching
- * its status instead of by a walk over the support's list.  The successor
- * checks are the same; a vertex that finds its support removed counts in
- * `visited`, one that finds another in `joins`, `phases` counts the passes over
- * the vertices, and nothing goes through queues.
+ * Per-call statistics, written to device memory.  AC-6 of explicit graphs, of
+ * implicit ones up to 2^15 vertices and of batches finds the vertices whose
+ * support was removed by watching their statuses instead of by walks over the
+ * supports' lists (lists are made for what a deep graph has left after 64
+ * rounds, fewer above 2^21 vertices).  The successor checks are the same; a
+ * vertex that finds its support removed counts in `visited`, one that finds
+ * another in `joins`, one that finds none in `closes`; `phases` counts the passes
+ * over the vertices, and nothing goes through queues.
  */
 typedef struct {
     uint64_t edges_total;  /* sum of worker_edges: successor checks (AC-6, AC-3) or
@@ -190,8 +196,8 @@ typedef struct {
                               rounds run (see above); 0 otherwise */
     uint64_t queued;       /* AC-6/AC-4: work items that went through the shared queue */
     uint64_t edges_sweep;  /* AC-6: successor checks made by the first sweep */
-    uint64_t closes;       /* AC-6: removed vertices whose support lists the propagation
-                              closed (the forest collapse counts in `forest`) */
+    uint64_t closes;       /* AC-6: vertices removed by the propagation (the forest
+                              collapse counts in `forest`) */
     uint64_t joins;        /* AC-6: support-list joins after the first sweep */
     uint64_t visited;      /* AC-6: support-list members handed back */
     uint64_t graph_edges;  /* AC-6: sum of out-degrees as generated or read (m) */

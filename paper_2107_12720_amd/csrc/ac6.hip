@@ -1204,13 +1204,13 @@ hipError_t ac6_run(View g, int n, const Work& w, const LaunchCfg& lc, uint32_t* 
 
 // Watched supports serve every explicit graph that one workgroup does not take
 // (small.hip): against lists from the first sweep on, core+tail graphs of 10^5
-// vertices take 266 / 403 us, of 2^21 653 / 765, R-MAT of edge factor 4 and 2^22
-// vertices 146 / 279, uniform ones of mean degree 1.1 and 2^20 vertices 776 / 842,
-// 2^22 1,288 / 1,414.  With late registration against a round list registered
-// after R rounds, R = 2 and 8: R-MAT 22 168 / 353 and 135 / 161 us, with a chain
-// of 2,000 234 / 404 and 325 / 562, core+tail of 2^20 482 / 585 and 484 / 666;
-// R-MAT 15 43 / 83 and 53 / 56.  Without it, below this size (graphs of too many edges for one
-// workgroup) the lists stay: their place must hold the filters.
+// vertices take 252 / 403 us, of 2^21 515 / 765, R-MAT of edge factor 4 and 2^22
+// vertices 128 / 279, uniform ones of mean degree 1.1 and 2^20 vertices 724 / 842,
+// 2^22 1,285 / 1,414.  With late registration against a round list registered
+// after R rounds, R = 2 and 8: R-MAT 22 148 / 353 and 119 / 161 us, with a chain
+// of 2,000 202 / 404 and 290 / 562, core+tail of 2^20 401 / 585 and 390 / 666;
+// R-MAT 15 39 / 83 and 51 / 56.  Without it, below this size (graphs of too many
+// edges for one workgroup) the lists stay: their place must hold the filters.
 constexpr int kWatchMinN = 4096;
 static_assert(2 * kWatchMinN >= 3 << (WatchFilter::log_for(kWatchMinN) - 5) &&
               2LL << 20 >= 3 * WatchFilter::kMaxWords, "the filters fit");

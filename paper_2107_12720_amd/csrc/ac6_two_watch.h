@@ -9,8 +9,8 @@
 //
 // What bounds it: the sweep by its gathers on both sides, a round by reading both
 // support arrays and four dependent loads.  R-MAT of edge factor 16 and 2^22
-// vertices 518 -> 256 us a call (exchanges for 380 in the sweep), with a chain of
-// 83,000 809 -> 346; core+tail of 32,768 vertices 418 -> 196, of 2^20 742 -> 353.
+// vertices 518 -> 225 us a call (exchanges for 380 in the sweep), with a chain of
+// 83,000 809 -> 303; core+tail of 32,768 vertices 418 -> 182, of 2^20 742 -> 350.
 #pragma once
 #include "trim_device.h"
 #include "block_append.h"

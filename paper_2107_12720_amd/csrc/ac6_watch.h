@@ -33,9 +33,9 @@
 // for R-MAT 22, edge factor 16; 200 with the exchanges), a round of all vertices
 // by reading sup (12 us at 2^22) and by the latency of four dependent loads,
 // about 5 us, plus 2 for the barrier in the tail.  R-MAT 22 with a chain of
-// 2*10^5: 494 -> 210 us in all; core+tail of 10^5 vertices 402 -> 255, of 2^20
-// 564 -> 380.  Late registration, R-MAT 26 with four counted rounds: 0.90 -> 0.84
-// ms if three reach the fixed point, 2.85 -> 1.1 if not (5 * 10^7 list exchanges
+// 2*10^5: 494 -> 210 us in all; core+tail of 10^5 vertices 402 -> 252, of 2^20
+// 564 -> 381.  Late registration, R-MAT 26 with four counted rounds: 0.90 -> 0.78
+// ms if three reach the fixed point, 3.80 -> 0.83 if not (5 * 10^7 list exchanges
 // took 2.65).
 #pragma once
 #include "trim_device.h"

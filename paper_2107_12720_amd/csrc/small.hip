@@ -292,15 +292,18 @@ int small_block(int n) {
 
 }  // namespace
 
-// Where the line lies, one workgroup against the device-wide path, us a call:
-// core+tail of 17,000 vertices 125 / 223, 32,768 172 / 249, 50,000 257 / 263,
-// 65,536 312 / 272 (its LDS holds no more supports); R-MAT scale 15 29 / 57,
-// 16 47 / 58, with a chain 76 / 91; uniform of 65,536 vertices and mean degree
-// 1.1 333 / 474.  The edge limit keeps graphs of long lists away, whose scans one
-// compute unit runs slowly: tails of 30 successors a vertex, nearly all of them
-// removed, take 915 / 1,430 with 17,000 vertices, 2,958 / 1,510 with 65,536.
+// Where the line lies, one workgroup against the device-wide rounds, us a call:
+// core+tail of 17,000 vertices 125 / 195, 32,768 173 / 242, 50,000 257 / 254,
+// 65,536 312 / 257; R-MAT of edge factor 16 and 32,768 29 / 44, 65,536 47 / 46, of
+// 4 51 / 48, with a chain 76 / 80; uniform of mean degree 2 and 50,000 90 / 100,
+// 65,536 104 / 102, of 1.1 334 / 443, of 16 30 / 37.  The edge limit keeps graphs
+// of long lists away, whose scans one compute unit runs slowly: tails of 30
+// successors a vertex, nearly all of them removed, take 908 / 1,358 with 17,000
+// vertices, 2,302 / 1,430 with 50,000.
+constexpr long long kSmallMaxN = 61440;
+static_assert(kSmallMaxN <= kWatchLdsN, "the LDS holds the supports");
 bool ac6_small_ok(long long n, long long m, int rounds) {
-    return rounds < 2 && n <= kWatchLdsN && m <= kSmallMaxM;
+    return rounds < 2 && n <= kSmallMaxN && m <= kSmallMaxM;
 }
 // A resumed scan of the implicit graph hashes its degree again: 2^14 vertices
 // 114 / 190 us, 2^16 324 / 245.

@@ -48,7 +48,7 @@ def rescued(n, depth, seed):
     return gg.from_edges(n, src.astype(np.int32), dst.astype(np.int32))
 
 
-@pytest.mark.parametrize("n", [MIN_N - 1, MIN_N, MIN_N + 30, 70016, 131071])
+@pytest.mark.parametrize("n", [61440, 61441, MIN_N - 1, MIN_N, MIN_N + 30, 70016, 131071])
 def test_sizes(ctx, n):
     check_all(ctx, gg.uniform(n, n + n // 8, seed=n), algos=(6,), name=f"uniform {n}")
     check_all(ctx, gg.core_tail(n, seed=n), algos=(6,), name=f"core+tail {n}")

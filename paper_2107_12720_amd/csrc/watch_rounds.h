@@ -25,9 +25,9 @@ constexpr int kWatchRounds = 64;
 // Rounds before the vertices left are registered in lists.  A round of the tail
 // takes 6 to 9 us up to 2^20 vertices and 19 at 2^22, a phase over lists 5 (one
 // removal) to 60 (thousands), registering 50 and 170.  Core+tail graphs of mean
-// degree 30 and 2^20 vertices (some 60 rounds) take 2.2 ms with 64 rounds, with
+// degree 30 and 2^20 vertices (some 60 rounds) take 2.4 ms with 64 rounds, with
 // lists alone 3.8 (a limit of 40 cost 0.5 more).  66 rounds of one removal each,
-// the worst case, take 0.69 ms, with lists alone 0.46.
+// the worst case, take 0.68 ms, with lists alone 0.46.
 constexpr int watch_rounds(int n) {
     const int r = n <= (1 << 21) ? kWatchRounds : (int)(((long long)kWatchRounds << 21) / n);
     return r > 8 ? r : 8;

@@ -1103,7 +1103,7 @@ hipError_t ac6_run(View g, int n, const Work& w, const LaunchCfg& lc, uint32_t* 
     const bool defer = R >= 2;
     uint32_t* y[2];
     y[1] = reinterpret_cast<uint32_t*>(w.c);
-    y[0] = y[1] + round_bitmap_offset(n);
+    y[0] = y[1] + round_bitmap_words(n);
     const int nwords = (n + 31) / 32;
     // the round filters follow the round list in w.hl: 2^flog bits each, about
     // n / 8 bits (at least 32, at most kRoundFilterMaxLog2)
@@ -1227,7 +1227,7 @@ hipError_t ac6_watch_run(const trim_csr_t& g, const Work& w, const LaunchCfg& lc
     const int R = lc.rounds >= 2 ? lc.rounds : 0;
     uint32_t* y[2];
     y[1] = reinterpret_cast<uint32_t*>(w.c);
-    y[0] = y[1] + round_bitmap_offset(n);
+    y[0] = y[1] + round_bitmap_words(n);
     uint32_t* dead = R ? y[(R + 1) & 1] : y[0];
     // the filters lie behind the round list or where the heads will, which are
     // made last if at all

@@ -569,18 +569,18 @@ namespace {
 
 // Smaller graphs keep the lists (two launches fewer): core+tail of 4,096 vertices
 // 246 us by lists, 141 by rounds, but uniform of 4,096 164 / 173 and R-MAT 12 71 /
-// 75.  The filters need room in the heads, the in-side supports behind the bitmaps.
-constexpr int kTwoWatchMinN = 4096;
-static_assert(2 * kTwoWatchMinN >= 3 << (WatchFilter::log_for(kTwoWatchMinN) - 5), "filters fit");
+// 75.  The filters need room in the heads.
+static_assert(2 * kTwoWatchMinN >= 3LL << (WatchFilter::log_for(kTwoWatchMinN) - 5), "filters fit");
 
 hipError_t two_watch_run(const TwoGraph& g, long long m, int n, const Work& w, const Work2& x,
                          const LaunchCfg& lc, uint32_t* bitmap, uint64_t* worker_edges,
                          trim_stats_t* stats, const uint32_t* preset) {
     const int P = lc.workers, B = lc.block;
     hipStream_t st = lc.stream;
+    if (two_watch_ints(n) > work_c_ints(w.cap)) return hipErrorInvalidValue;
     uint32_t* y1 = reinterpret_cast<uint32_t*>(w.c);
-    uint32_t* dead = y1 + round_bitmap_offset(n);
-    int* sup_in = w.c + 2 * round_bitmap_offset(n);
+    uint32_t* dead = y1 + round_bitmap_words(n);
+    int* sup_in = w.c + 2 * round_bitmap_words(n);
     const WatchFilter flt{reinterpret_cast<uint32_t*>(g.hout), WatchFilter::log_for(n)};
     const TwoWatch t{{g.row_off, g.col, n, w.d, g.rec_out, dead, flt, w.ctr, worker_edges, P,
                       lc.schedule, 1, lc.forest},

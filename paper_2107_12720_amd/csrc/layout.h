@@ -1,0 +1,31 @@
+// layout.h -- how many entries the per-vertex working arrays hold and how
+// they are shared out: plain arithmetic, no HIP, so that it is checked on the
+// host for every size a kept context may meet.
+#pragma once
+
+namespace trim {
+
+// Vertices a context's arrays are sized for when a call of `need` makes them:
+// an eighth more (less 1/128, which pays for the bitmaps of work_c_ints), so
+// that slightly larger graphs find room.  Any later n up to this one uses the
+// same arrays, so no kernel may count on the slack of its own n.  A multiple of
+// four: supports are read in 16-byte loads.
+constexpr long long work_capacity(long long need) {
+    return (need + need / 8 - need / 128 + 64) / 4 * 4;
+}
+
+// Words of a status bitmap of n vertices, with the one past the end that
+// ac6_init may write, up to a cache line.
+constexpr long long round_bitmap_words(long long n) { return ((n + 31) / 32 + 2 + 31) / 32 * 32; }
+
+// Two-sided trimming watches supports from this many vertices on (ac6_two.hip).
+constexpr long long kTwoWatchMinN = 4096;
+// It keeps two status bitmaps and, behind them, the in-side supports.
+constexpr long long two_watch_ints(long long n) { return 2 * round_bitmap_words(n) + n; }
+
+// Ints of the array w.c (Work) for a capacity.
+constexpr long long work_c_ints(long long cap) {
+    return cap < kTwoWatchMinN ? cap : two_watch_ints(cap);
+}
+
+}  // namespace trim

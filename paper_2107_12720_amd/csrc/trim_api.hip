@@ -118,7 +118,7 @@ int ensure(trim_ctx* c, int64_t n) {
     size_t need = (size_t)(n > 0 ? n : 1);
     if (need <= c->cap_n) return TRIM_OK;
     free_work(c);
-    size_t cap = need + need / 8 + 64;
+    const size_t cap = (size_t)trim::work_capacity((long long)need);
     // the split S_more lists (and the queue room they need) for graphs that
     // use them
     const bool split = (long long)need <= trim::kSplitMaxN;
@@ -126,7 +126,7 @@ int ensure(trim_ctx* c, int64_t n) {
         cap * (split ? trim::kQueuePerVertexSplit : 3) + (size_t)trim::kQueueSlots;
     if (dmalloc(c, &c->w.a, cap * 8) != hipSuccess ||
         dmalloc(c, &c->w.b, cap * 8) != hipSuccess ||
-        dmalloc(c, &c->w.c, cap * 4) != hipSuccess ||
+        dmalloc(c, &c->w.c, (size_t)trim::work_c_ints((long long)cap) * 4) != hipSuccess ||
         dmalloc(c, &c->w.d, cap * 4) != hipSuccess ||
         dmalloc(c, &c->w.e, cap * 12) != hipSuccess ||
         (split && dmalloc(c, &c->w.ext, cap * 4 * (trim::kMoreLists - 1)) != hipSuccess) ||

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "../../include/trim.h"
+#include "layout.h"
 
 namespace trim {
 
@@ -54,8 +55,9 @@ struct Work {
     int* a = nullptr;         // 2n int32: AC-6 (out-side) list heads / AC-4 counters /
                               //   AC-3 list
     uint64_t* b = nullptr;    // n uint64: AC-6 (out-side) records / AC-3 list
-    int* c = nullptr;         // n int32: AC-6 bitmap of vertices removed at the start /
-                              //   AC-3 removal round
+    int* c = nullptr;         // work_c_ints(cap) int32: AC-6 status bitmaps, with the in-side
+                              //   supports of the two-sided form behind them / AC-3 removal
+                              //   round
     int* d = nullptr;         // n int32: AC-3 cursor / two-sided AC-4 removal flags /
                               //   batch: first vertex of each vertex's graph (union
                               //   path) or the graphs' claim order (owned path)

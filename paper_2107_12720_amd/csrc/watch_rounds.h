@@ -68,11 +68,6 @@ struct WatchFilter {
     __device__ __forceinline__ bool useful(int removed) const { return removed <= words() * 8; }
 };
 
-// Words from the first round bitmap to the second (both in w.c, which holds
-// n + n / 8 + 64 ints): room for ceil(n / 32) words plus the one past the end
-// that ac6_init may write, aligned to a cache line.
-inline long long round_bitmap_offset(long long n) { return ((n + 31) / 32 + 2 + 31) / 32 * 32; }
-
 struct WatchState {
     const int* row_off;
     const int* col;

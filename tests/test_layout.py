@@ -1,0 +1,41 @@
+"""Plain arithmetic of the library (csrc/layout.h), compiled with the host
+compiler: the working arrays of a context hold every size that reuses them."""
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                    "paper_2107_12720_amd", "csrc")
+
+
+def run_cpp(tmp_path, body, headers):
+    src = tmp_path / "t.cpp"
+    inc = "".join(f'#include "{h}"\n' for h in headers)
+    src.write_text("#include <cstdio>\n#include <initializer_list>\n" + inc +
+                   "int main() { using namespace trim; long long bad = 0;\n" + body +
+                   '\nprintf("%lld\\n", bad); return bad != 0; }\n')
+    exe = tmp_path / "t"
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-ftrapv", "-I", CSRC, str(src),
+                           "-o", str(exe)])
+    return subprocess.run([str(exe)], capture_output=True, text=True)
+
+
+@pytest.mark.parametrize("needs", ["1, 63, 64, 65, 960, 961, 3589, 3590, 4095, 4096, 4097",
+                                   "65536, 100000, 1000000, 33554431, 33554432, 536870912"])
+def test_arrays_hold_every_size_that_reuses_them(tmp_path, needs):
+    # every n up to the capacity of every first call `need` (large ranges: the ends)
+    r = run_cpp(tmp_path, """
+        for (long long need : {%s}) {
+            const long long cap = work_capacity(need), old = need + need / 8 + 64;
+            if (cap < need || cap %% 4) ++bad;
+            // 8 + 8 + 4 + 12 bytes and more of other arrays per vertex: no more than without
+            // the room behind the bitmaps
+            if (44 * cap + 4 * work_c_ints(cap) > 48 * old) ++bad;
+            for (long long n = 1; n <= cap; n += n < cap - 4096 && n > 8192 ? cap / 4096 + 1 : 1) {
+                if (2 * round_bitmap_words(n) > work_c_ints(cap)) ++bad;
+                if (n >= kTwoWatchMinN && two_watch_ints(n) > work_c_ints(cap)) ++bad;
+                if ((n + 3) / 4 * 4 > cap) ++bad;
+            }
+        }""" % needs, ["layout.h"])
+    assert r.returncode == 0, r.stdout

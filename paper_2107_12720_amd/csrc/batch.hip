@@ -8,7 +8,8 @@
 // n + m), so the biggest graphs start early and the small ones fill in behind
 // them.  Graphs of up to kWatchMaxN vertices are trimmed as watch.h describes,
 // their statuses in LDS: by a wavefront when they are small, else by the whole
-// workgroup, with the supports in LDS, too, up to 65,536 vertices.  What bounds
+// workgroup, with the supports in LDS, too, up to 65,536 vertices (somewhat fewer
+// with opts.block no power of two).  What bounds
 // the batch of 4,096 graphs (5.9 * 10^7 vertices) is the latency of a pass's
 // resumed scans in the middling graphs; with supporting sets as lists in
 // device memory it was the dependent accesses of every phase.
@@ -63,7 +64,8 @@ constexpr int kOwnUnroll = 2;     // sweep vertices per lane in flight
 constexpr int kOwnLds = 155648;
 constexpr int kOwnWaveLds = kOwnLds / 16;
 constexpr int kOwnWaveN = 4096;
-static_assert(kOwnWaveN / 8 + kOwnWaveN * 2 + kWatchList * 2 <= kOwnWaveLds &&
+static_assert(watch_fits(kOwnWaveN, kWave, kOwnWaveN) &&
+              kOwnWaveN / 8 + kOwnWaveN * 2 + kWatchList * 2 <= kOwnWaveLds &&
               kWatchList * 2 >= kOwnWaveN / 8, "a wavefront's share");
 static_assert(kWatchLdsN / 8 + kWatchLdsN * 2 + 16 * kWatchList * 2 <= kOwnLds,
               "statuses, supports and lists of the largest graph with supports in LDS");
@@ -399,7 +401,7 @@ __global__ __launch_bounds__(kOwnMaxBlock) void ac6_owned(OwnArgs a, int G, cons
             break;
         }
         const int64_t n = a.vbase[gi + 1] - a.vbase[gi];
-        if (n <= kWatchLdsN)
+        if (watch_fits(n, (int)blockDim.x, kWatchLdsN))
             own_watch<uint16_t, uint16_t, false>(a, gi, sh.raw, kWatchLdsN, sh.cnt[0], sh, t);
         else if (n <= kWatchMaxN)
             own_watch<int, uint32_t, false>(a, gi, sh.raw, kWatchMaxN, sh.cnt[0], sh, t);

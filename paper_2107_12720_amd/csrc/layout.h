@@ -28,4 +28,19 @@ constexpr long long work_c_ints(long long cap) {
     return cap < kTwoWatchMinN ? cap : two_watch_ints(cap);
 }
 
+// Supports in LDS (watch.h): 16 bits each, for up to this many vertices.
+constexpr int kWatchLdsN = 65536;
+constexpr int kWatchReads = 4;   // 32-bit reads per lane in flight in a watch pass
+// Entries of the support array: n rounded up to whole batches of
+// 2 * kWatchReads vertices per lane.
+constexpr int watch_padded(int n, int lanes) {
+    const int batch = 2 * kWatchReads * lanes;
+    return (n + batch - 1) / batch * batch;
+}
+// Whether an array of `room` entries holds them.  (Not every n up to the room:
+// 65,536 vertices are 67,584 entries with 768 lanes.)
+constexpr bool watch_fits(long long n, int lanes, int room) {
+    return n <= room && watch_padded((int)n, lanes) <= room;
+}
+
 }  // namespace trim

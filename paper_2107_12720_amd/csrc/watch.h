@@ -40,30 +40,21 @@
 //           back, until a pass hands none back.
 #pragma once
 #include "trim_device.h"
+#include "layout.h"
 
 namespace trim {
 
 namespace {
 
-constexpr int kWatchLdsN = 65536;       // supports in LDS up to this many vertices
 constexpr int kWatchMaxN = 1 << 19;     // status bits in LDS up to this many
 constexpr int kWatchUnroll = 8;         // vertices per lane in flight in the sweep
 constexpr int kWatchScan = 4;           // successors per step of a resumed scan
 constexpr int kWatchHops = 4;           // links followed per forest round
-constexpr int kWatchReads = 4;          // 32-bit reads per lane in flight in a watch pass
 constexpr int kWatchSlots = 2 * kWatchReads;   // vertices per lane and step of a pass
 constexpr int kWatchSteps = 8;          // steps whose finds are listed in one go
 constexpr int kWatchList = 512;         // list entries of one wavefront
 static_assert(kWatchSlots * kWatchSteps == 64, "the finds of a lane are the bits of one word");
 constexpr int kWatchCnt = 4;            // LDS words of a group: flags, null vertex
-
-// Entries of the 16-bit support array: n rounded up to whole batches of
-// 2 * kWatchReads vertices per lane.
-__host__ __device__ constexpr int watch_padded(int n, int lanes) {
-    const int batch = 2 * kWatchReads * lanes;
-    return (n + batch - 1) / batch * batch;
-}
-static_assert(watch_padded(kWatchLdsN, 1024) == kWatchLdsN, "padding stays inside the array");
 
 // Graph views with plain loads: a small graph is read again from the caches.
 struct CachedView {

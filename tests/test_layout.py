@@ -39,3 +39,26 @@ def test_arrays_hold_every_size_that_reuses_them(tmp_path, needs):
             }
         }""" % needs, ["layout.h"])
     assert r.returncode == 0, r.stdout
+
+
+def test_supports_in_lds_fit_with_every_block(tmp_path):
+    # the sizes that go to an array of kWatchLdsN entries (batches, any opts.block; the one
+    # wavefront's 4,096) and the largest each block takes
+    r = run_cpp(tmp_path, """
+        for (int lanes = 64; lanes <= 1024; lanes += 64) {
+            int most = 0;
+            for (int n = 1; n <= 2 * kWatchLdsN; ++n)
+                if (watch_fits(n, lanes, kWatchLdsN)) {
+                    most = n;
+                    if (watch_padded(n, lanes) < n || watch_padded(n, lanes) > kWatchLdsN) ++bad;
+                }
+            if ((lanes & (lanes - 1)) ? most < 57344 : most != kWatchLdsN) ++bad;
+        }
+        if (watch_fits(65536, 768, kWatchLdsN) || watch_fits(61441, 768, kWatchLdsN)) ++bad;
+        if (!watch_fits(4096, 64, 4096) || watch_fits(4097, 64, 4096)) ++bad;
+        // one workgroup of a small graph (small.hip): half as many lanes as vertices, 256 to 1,024
+        for (int n = 0; n <= 8192; ++n) {
+            const int b = (n / 2 + 63) / 64 * 64;
+            if (!watch_fits(n, b < 256 ? 256 : b > 1024 ? 1024 : b, 8192)) ++bad;
+        }""", ["layout.h"])
+    assert r.returncode == 0, r.stdout

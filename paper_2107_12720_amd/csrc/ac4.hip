@@ -115,12 +115,13 @@ __global__ __launch_bounds__(256) void ac4_first(const int* rrow_off, const int*
             edges += (uint64_t)(e - k);
             for (uint64_t big = ballot(e - k > kCoop); big; big &= big - 1) {
                 const int owner = __ffsll((unsigned long long)big) - 1;
-                const int kb = __shfl(k, owner), eb = __shfl(e, owner);
-                for (int at = kb; at < eb; at += kWave * kBatch) {
+                // (unsigned: see step_index)
+                const uint32_t kb = __shfl(k, owner), eb = __shfl(e, owner);
+                for (uint32_t at = kb; at < eb; at += kWave * kBatch) {
                     int u[kBatch], old[kBatch];
 #pragma unroll
                     for (int j = 0; j < kBatch; ++j) {
-                        const int p = at + j * kWave + lane_id();
+                        const uint32_t p = at + j * kWave + lane_id();
                         if (p < eb) u[j] = adj[p];
                     }
                     if (sched & TRIM_SCHED_JITTER) jitter_nap(((uint64_t)kb << 20) ^ at);
@@ -199,27 +200,27 @@ __global__ __launch_bounds__(256) void ac4_propagate(const int* rrow_off, const 
         // a time, 64 x kBatch decrements in flight per round.
         for (uint64_t big = ballot(item != kNone && e - k > kCoop); big; big &= big - 1) {
             const int owner = __ffsll((unsigned long long)big) - 1;
-            const int kb = __shfl(k, owner), eb = __shfl(e, owner);
+            const uint32_t kb = __shfl(k, owner), eb = __shfl(e, owner);
             const int phb = kTwo ? __shfl(ph, owner) : 0;
             const int* adj = phb ? col : rcol;
             int* ctr_of = phb ? cnt + n : cnt;
-            for (int base = kb; base < eb; base += kWave * kBatch) {
+            for (uint32_t base = kb; base < eb; base += kWave * kBatch) {
                 int u[kBatch], old[kBatch];
                 uint32_t o[kBatch];
 #pragma unroll
                 for (int j = 0; j < kBatch; ++j) {
-                    const int p = base + j * kWave + lane_id();
+                    const uint32_t p = base + j * kWave + lane_id();
                     if (p < eb) u[j] = adj[p];
                 }
                 if (sched & TRIM_SCHED_JITTER) jitter_nap(((uint64_t)kb << 20) ^ base);
 #pragma unroll
                 for (int j = 0; j < kBatch; ++j) {
-                    const int p = base + j * kWave + lane_id();
+                    const uint32_t p = base + j * kWave + lane_id();
                     if (p < eb) old[j] = add_dev(ctr_of + u[j], -1);
                 }
 #pragma unroll
                 for (int j = 0; j < kBatch; ++j) {
-                    const int p = base + j * kWave + lane_id();
+                    const uint32_t p = base + j * kWave + lane_id();
                     o[j] = (p < eb && old[j] == 1 && removes<kTwo>(dead, u[j])) ? make_item(0, u[j])
                                                                                : kNone;
                 }

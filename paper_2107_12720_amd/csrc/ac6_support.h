@@ -55,21 +55,22 @@ __device__ __forceinline__ bool resume(const View& g, int u, int p0, int* head, 
     constexpr int kScan = 4;
     const int e = g.end(u);
     const int ctx = g.vctx(u);
-    for (int p = p0; p < e; p += kScan) {
+    const uint32_t end = (uint32_t)e;   // (unsigned: see step_index)
+    for (uint32_t p = p0; p < end; p += kScan) {
         int w[kScan], h[kScan];
 #pragma unroll
         for (int j = 0; j < kScan; ++j)
-            if (p + j < e) w[j] = g.target(u, p + j, ctx);
+            if (p + j < end) w[j] = g.target(u, (int)(p + j), ctx);
 #pragma unroll
         for (int j = 0; j < kScan; ++j)
-            if (p + j < e) h[j] = ld_cached(join_slot(head, ext, w[j], p + j + 1 == e, u));
+            if (p + j < end) h[j] = ld_cached(join_slot(head, ext, w[j], p + j + 1 == end, u));
 #pragma unroll
         for (int j = 0; j < kScan; ++j) {
-            if (p + j >= e) break;
-            int* slot = join_slot(head, ext, w[j], p + j + 1 == e, u);
+            if (p + j >= end) break;
+            int* slot = join_slot(head, ext, w[j], p + j + 1 == end, u);
             int hj = h[j];
             while (hj != kDead) {
-                st_s<S>(rec + u, pack_rec(hj, p + j));
+                st_s<S>(rec + u, pack_rec(hj, (int)(p + j)));
                 complete_mem();
                 if (sched & TRIM_SCHED_JITTER) jitter_nap(((uint64_t)u << 24) ^ (p + j));
                 if (cas_s<S>(slot, hj, u)) {

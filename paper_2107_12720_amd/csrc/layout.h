@@ -2,6 +2,7 @@
 // they are shared out: plain arithmetic, no HIP, so that it is checked on the
 // host for every size a kept context may meet.
 #pragma once
+#include <cstdint>
 
 namespace trim {
 
@@ -26,6 +27,13 @@ constexpr long long two_watch_ints(long long n) { return 2 * round_bitmap_words(
 // Ints of the array w.c (Work) for a capacity.
 constexpr long long work_c_ints(long long cap) {
     return cap < kTwoWatchMinN ? cap : two_watch_ints(cap);
+}
+
+// Edge positions go up to 2^31 - 1, the end of the last list, so a scan in steps
+// of several entries keeps them unsigned: a position plus a step stays below 2^32.
+// Entry j of the step at p of a list that ends at e, the last one from there on.
+constexpr uint32_t step_index(uint32_t p, int j, int e) {
+    return p + (uint32_t)j < (uint32_t)e ? p + (uint32_t)j : (uint32_t)e - 1;
 }
 
 // Supports in LDS (watch.h): 16 bits each, for up to this many vertices.

@@ -452,28 +452,30 @@ __global__ __launch_bounds__(256) void scc_pull(int n, const int* row_off, const
             const int mark = 1 << dir;
             const int* off = dir ? row_off : rrow_off;
             const int* adj = dir ? col : rcol;
-            int p = 0, e = 0;
+            uint32_t p = 0;   // (unsigned: see step_index)
+            int e = 0;
             if (!(f & mark)) {
                 p = off[v];
                 e = off[v + 1];
             }
             bool hit = false;
-            for (int stop = min(e, p + kPullLane); p < stop && !hit; p += kPullStep) {
+            for (const uint32_t stop = min((uint32_t)e, p + kPullLane); p < stop && !hit;
+                 p += kPullStep) {
                 int w[kPullStep], m[kPullStep];
 #pragma unroll
-                for (int j = 0; j < kPullStep; ++j) w[j] = adj[min(p + j, e - 1)];
+                for (int j = 0; j < kPullStep; ++j) w[j] = adj[step_index(p, j, e)];
 #pragma unroll
                 for (int j = 0; j < kPullStep; ++j) m[j] = ld_cached(flags + w[j]);
 #pragma unroll
                 for (int j = 0; j < kPullStep; ++j) hit |= (m[j] & mark) != 0;
-                seen += min(kPullStep, e - p);
+                seen += min((uint32_t)kPullStep, (uint32_t)e - p);
             }
-            for (uint64_t rest = ballot(!hit && p < e); rest; rest &= rest - 1) {
+            for (uint64_t rest = ballot(!hit && p < (uint32_t)e); rest; rest &= rest - 1) {
                 const int owner = __ffsll((unsigned long long)rest) - 1;
-                const int eb = __shfl(e, owner);
+                const uint32_t eb = __shfl(e, owner);
                 bool found = false;
-                for (int q = __shfl(p, owner); q < eb && !found; q += kWave) {
-                    const int at = q + lane_id();
+                for (uint32_t q = __shfl((int)p, owner); q < eb && !found; q += kWave) {
+                    const uint32_t at = q + lane_id();
                     const bool m = at < eb && (ld_cached(flags + adj[at]) & mark);
                     found = ballot(m) != 0;
                     seen += at < eb;

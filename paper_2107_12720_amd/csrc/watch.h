@@ -72,15 +72,15 @@ struct CachedView {
 // address a cycle, so where the array allows it they come in 16-byte loads:
 // eight 4-byte loads a step made the scans of core+tail 65,536 cost 90 us.
 template <class View>
-__device__ __forceinline__ void wt_targets(const View& g, int u, int p, int e, int ctx,
+__device__ __forceinline__ void wt_targets(const View& g, int u, uint32_t p, int e, int ctx,
                                            int (&w)[kWatchScan]) {
 #pragma unroll
-    for (int j = 0; j < kWatchScan; ++j) w[j] = g.target(u, min(p + j, e - 1), ctx);
+    for (int j = 0; j < kWatchScan; ++j) w[j] = g.target(u, (int)step_index(p, j, e), ctx);
 }
-__device__ __forceinline__ void wt_targets(const CachedView& g, int, int p, int e, int,
+__device__ __forceinline__ void wt_targets(const CachedView& g, int, uint32_t p, int e, int,
                                            int (&w)[kWatchScan]) {
     typedef int v4 __attribute__((ext_vector_type(4), aligned(4)));
-    if (p + kWatchScan <= g.m) {   // the entries past e belong to other lists
+    if (p + kWatchScan <= (uint32_t)g.m) {   // the entries past e belong to other lists
 #pragma unroll
         for (int j = 0; j < kWatchScan; j += 4) {
             const v4 x = *reinterpret_cast<const v4*>(g.col + p + j);
@@ -91,7 +91,7 @@ __device__ __forceinline__ void wt_targets(const CachedView& g, int, int p, int 
         }
     } else {
 #pragma unroll
-        for (int j = 0; j < kWatchScan; ++j) w[j] = g.col[min(p + j, e - 1)];
+        for (int j = 0; j < kWatchScan; ++j) w[j] = g.col[step_index(p, j, e)];
     }
 }
 
@@ -398,7 +398,7 @@ struct Watch {
         if (sched & TRIM_SCHED_JITTER) jitter_nap((uint64_t)u);
         t.visited += 1;
         int at = -1, to = 0;
-        for (int p = p0; p < e && at < 0; p += K) {
+        for (uint32_t p = p0; p < (uint32_t)e && at < 0; p += K) {
             int w[K];
             bool live[K];
             wt_targets(g, u, p, e, ctx, w);
@@ -406,8 +406,8 @@ struct Watch {
             for (int j = 0; j < K; ++j) live[j] = !wt_bit(bits, w[j]) && w[j] != null;
 #pragma unroll
             for (int j = 0; j < K; ++j)
-                if (at < 0 && p + j < e && live[j]) {
-                    at = p + j;
+                if (at < 0 && p + j < (uint32_t)e && live[j]) {
+                    at = (int)(p + j);
                     to = w[j];
                 }
         }

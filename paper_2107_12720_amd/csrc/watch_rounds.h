@@ -113,19 +113,19 @@ __device__ __forceinline__ bool watch_scan(const WatchState& a, int v, int s, in
     const int e = a.row_off[v + 1];
     const int p0 = ((s & kSupFirst) ? a.row_off[v] : *rec_pos(a.rec, v)) + 1;
     if (a.sched & TRIM_SCHED_JITTER) jitter_nap((uint64_t)v);
-    for (int p = p0; p < e; p += K) {
+    for (uint32_t p = p0; p < (uint32_t)e; p += K) {
         int w[K];
         uint32_t x[K];
 #pragma unroll
-        for (int j = 0; j < K; ++j) w[j] = a.col[min(p + j, e - 1)];
+        for (int j = 0; j < K; ++j) w[j] = a.col[step_index(p, j, e)];
 #pragma unroll
         for (int j = 0; j < K; ++j)
             x[j] = kFresh ? ld_dev(a.dead + (w[j] >> 5)) : a.dead[w[j] >> 5];
 #pragma unroll
         for (int j = 0; j < K; ++j) {
-            if (p + j >= e || ((x[j] >> (w[j] & 31)) & 1u)) continue;
-            edges += (uint64_t)(p + j - p0 + 1);
-            pos = p + j;
+            if (p + j >= (uint32_t)e || ((x[j] >> (w[j] & 31)) & 1u)) continue;
+            pos = (int)(p + j);
+            edges += (uint64_t)(pos - p0 + 1);
             to = w[j];
             return true;
         }

@@ -62,3 +62,23 @@ def test_supports_in_lds_fit_with_every_block(tmp_path):
             if (!watch_fits(n, b < 256 ? 256 : b > 1024 ? 1024 : b, 8192)) ++bad;
         }""", ["layout.h"])
     assert r.returncode == 0, r.stdout
+
+
+def test_scans_end_at_the_largest_edge_number(tmp_path):
+    # steps of every size over lists that end at 2^31 - 1 (signed overflow
+    # traps): each entry once, in order, nothing outside the list
+    r = run_cpp(tmp_path, """
+        for (int step : {4, 64, 512})
+            for (int len : {0, 1, 3, 4, 5, 63, 64, 65, 511, 512, 513, 1500})
+                for (int e : {2147483647, 2147483646, 1500}) {
+                    const int p0 = e - len;
+                    long long next = p0;
+                    for (uint32_t p = p0; p < (uint32_t)e; p += step)
+                        for (int j = 0; j < step; ++j) {
+                            const long long at = step_index(p, j, e);
+                            if (at < p0 || at >= e) ++bad;
+                            if (p + j < (uint32_t)e ? at != next++ : at != e - 1) ++bad;
+                        }
+                    if (next != e) ++bad;
+                }""", ["layout.h"])
+    assert r.returncode == 0, r.stdout

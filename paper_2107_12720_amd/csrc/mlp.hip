@@ -325,13 +325,6 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
     typedef float f2 __attribute__((ext_vector_type(2)));
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{lo, hi}, v2));
 }
-// max(x, 0) of two packed BF16 values: negative ones have the sign of a
-// negative 16-bit integer.
-__device__ __forceinline__ uint32_t relu_bf16x2(uint32_t x) {
-    typedef short s2 __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(uint32_t,
-                              __builtin_elementwise_max(__builtin_bit_cast(s2, x), s2{0, 0}));
-}
 
 // What scoring needs of a vertex, in the four bytes that a gather of targets at
 // random places should cost at most: the out-degree (kOutMax: that or more)
@@ -380,8 +373,9 @@ __device__ __forceinline__ uint32_t score_features(uint32_t x, int v, const int*
 // (3 ms by themselves).  So what is gathered takes four bytes a vertex; a
 // wavefront takes two tiles at a time, one edge per lane for the loads and the
 // features (both halves used to make the same ones), and swaps halves of
-// registers to get the tiles' operands; conversions and the first ReLU go two
-// values an instruction; the second layer's biases enter as the MFMA's addend;
+// registers to get the tiles' operands; conversions go two values an
+// instruction (the first ReLU does not: a maximum of packed 16-bit integers
+// would pass a NaN, which fmaxf drops as in training); the second layer's biases enter as the MFMA's addend;
 // and the position's hash bits, two 64-bit products, come from a table for the
 // first kHashed positions of a list.
 // The sources' features come from their own table (kWide) unless the context
@@ -409,7 +403,8 @@ __global__ __launch_bounds__(256) void mlp_score(const int* row_off, const int* 
         uint32_t h[8];
 #pragma unroll
         for (int r = 0; r < 8; ++r)
-            h[r] = relu_bf16x2(pack_bf16(z1[2 * r] + W.b1[2 * r], z1[2 * r + 1] + W.b1[2 * r + 1]));
+            h[r] = pack_bf16(fmaxf(z1[2 * r] + W.b1[2 * r], 0.f),
+                             fmaxf(z1[2 * r + 1] + W.b1[2 * r + 1], 0.f));
         typedef uint32_t u4 __attribute__((ext_vector_type(4)));
         f32x16 z2 = mfma16(w2a, __builtin_bit_cast(bf16x8, u4{h[0], h[1], h[2], h[3]}), b2);
         z2 = mfma16(w2b, __builtin_bit_cast(bf16x8, u4{h[4], h[5], h[6], h[7]}), z2);

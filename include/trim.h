@@ -254,7 +254,11 @@ const char *trim_last_error(void);
  */
 int trim_ctx_create(trim_ctx **out, int device, uint64_t mem_budget);
 /* Device memory the context holds now, in bytes (working memory grows to the
- * largest graph seen and is kept for later calls). */
+ * largest graph seen and is kept for later calls; a call that has to grow it
+ * allocates and frees, which waits for the device and cannot be captured into a
+ * graph, and graphs captured before it are to be captured again).  Memory that
+ * only makes calls of the learned order faster (noted there) is given back when
+ * another call needs the room. */
 int trim_ctx_mem_used(trim_ctx *ctx, uint64_t *bytes);
 /* Free a context and its working memory (NULL is ignored). */
 int trim_ctx_destroy(trim_ctx *ctx);
@@ -480,7 +484,10 @@ int trim_csr_noalloc(const trim_csr_t *g, const trim_opts_t *opts, uint32_t *liv
  */
 #define TRIM_MLP_PARAMS 1377
 
-/* indeg[v] (n entries) and src[e] (m entries: the source of edge e). */
+/* indeg[v] (n entries) and src[e] (m entries: the source of edge e).  Context
+ * memory: 2.25 bytes per edge and up to 5 MB if there is room for them (graphs
+ * of 32,769 to 2^25 vertices and many edges; given back on need), else 32 bytes per
+ * vertex up to 2^26 vertices. */
 int trim_mlp_prepare(trim_ctx *ctx, const trim_csr_t *g, int32_t *indeg, int32_t *src,
                      void *stream);
 
@@ -504,11 +511,14 @@ int trim_mlp_adam(trim_ctx *ctx, float *params, uint16_t *params_bf16, float *ad
 /* scores[e] = the network's logit that the target of edge e stays live (its
  * probability is 1 / (1 + exp(-logit))) (m entries, CSR order).  Per-vertex features are first
  * tabulated in context memory (12 bytes per vertex, 4 where the cap leaves no
- * room for them, kept for later calls). */
+ * room for them; given back on need). */
 int trim_mlp_score(trim_ctx *ctx, const trim_csr_t *g, const int32_t *indeg, const int32_t *src,
                    const uint16_t *params_bf16, float *scores, void *stream);
 
-/* Reference orders: kind 0 keys[e] = log1p(outdeg(target)), kind 1 a hash of (seed, e). */
+/* Reference orders: kind 0 keys[e] = log1p(outdeg(target)), kind 1 a hash of (seed, e).
+ * Kind 0 on many edges (2^25, and 8 per vertex) tabulates the degrees in context memory if
+ * there is room (2 bytes per vertex, given back on need) and never allocates while `stream`
+ * is being captured. */
 int trim_edge_keys(trim_ctx *ctx, const trim_csr_t *g, int32_t kind, uint64_t seed, float *keys,
                    void *stream);
 

@@ -36,12 +36,16 @@ struct trim_ctx {
     // tile tables of the preprocessing and reordering kernels
     int* tiles = nullptr;
     long long cap_tiles = 0;
-    // per-XCD in-degree copies of trim_mlp_prepare, or its binned targets
+    // per-XCD in-degree copies of trim_mlp_prepare
     int* copies = nullptr;
     long long cap_copies = 0;
+    // Spare memory: it makes calls faster that also work without it, holds
+    // nothing from one call for the next, and goes when a call has to have the
+    // room (drop_spare): the binned targets of trim_mlp_prepare, and the
+    // per-vertex features of trim_mlp_score (kScoreWords words per vertex, or
+    // one) and degrees of trim_edge_keys.
     void* bins = nullptr;
     size_t cap_bins = 0;
-    // per-vertex features of trim_mlp_score (kScoreWords words per vertex, or one)
     uint32_t* vf = nullptr;
     long long cap_vf = 0;
 };
@@ -64,9 +68,9 @@ int hip_fail(hipError_t e, const char* what) {
     return fail(TRIM_E_HIP, "%s: %s", what, hipGetErrorString(e));
 }
 
-// Every device allocation of a context goes through these two, so the context
+// Every device allocation of a context goes through these, so the context
 // knows what it holds and can refuse what would exceed its cap.
-hipError_t dmalloc(trim_ctx* c, void** p, size_t bytes) {
+hipError_t dmalloc_spare(trim_ctx* c, void** p, size_t bytes) {
     *p = nullptr;
     if (c->mem_budget && c->mem_used + bytes > c->mem_budget) return hipErrorOutOfMemory;
     hipError_t e = hipMalloc(p, bytes);
@@ -78,10 +82,6 @@ hipError_t dmalloc(trim_ctx* c, void** p, size_t bytes) {
     c->mem_used += bytes;
     return hipSuccess;
 }
-template <class T>
-hipError_t dmalloc(trim_ctx* c, T** p, size_t bytes) {
-    return dmalloc(c, reinterpret_cast<void**>(p), bytes);
-}
 void dfree(trim_ctx* c, void* p) {
     if (!p) return;
     auto it = c->sizes.find(p);
@@ -90,6 +90,38 @@ void dfree(trim_ctx* c, void* p) {
         c->sizes.erase(it);
     }
     (void)hipFree(p);
+}
+
+// Gives the spare memory back; true if there was any.
+bool drop_spare(trim_ctx* c) {
+    if (!c->bins && !c->vf) return false;
+    dfree(c, c->bins);
+    dfree(c, c->vf);
+    c->bins = nullptr;
+    c->cap_bins = 0;
+    c->vf = nullptr;
+    c->cap_vf = 0;
+    return true;
+}
+// Memory that the call cannot do without.
+template <class T>
+hipError_t dmalloc(trim_ctx* c, T** p, size_t bytes) {
+    hipError_t e = dmalloc_spare(c, reinterpret_cast<void**>(p), bytes);
+    if (e == hipErrorOutOfMemory && drop_spare(c)) {
+        (void)hipGetLastError();
+        e = dmalloc_spare(c, reinterpret_cast<void**>(p), bytes);
+    }
+    return e;
+}
+// Whether a call on `stream` may allocate spare memory: not while the stream is
+// being captured, which an allocation would end.
+bool may_allocate(void* stream) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing((hipStream_t)stream, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st == hipStreamCaptureStatusNone;
 }
 
 void free_work(trim_ctx* c) {
@@ -778,15 +810,20 @@ int trim_mlp_prepare(trim_ctx* c, const trim_csr_t* g, int32_t* indeg, int32_t* 
     if (binned) {
         const size_t need = trim::bin_scratch_bytes(g->n, g->m);
         if (need > c->cap_bins) {
-            dfree(c, c->bins);
-            c->bins = nullptr;
-            c->cap_bins = 0;
-            if (dmalloc(c, &c->bins, need) == hipSuccess) {
-                c->cap_bins = need;
-            } else {   // no room under the cap: the copies may need less
-                (void)hipGetLastError();
+            // no room, or a stream being captured: the copies may need less, or be there
+            binned = false;
+            if (may_allocate(stream)) {
+                dfree(c, c->bins);
                 c->bins = nullptr;
-                binned = false;
+                c->cap_bins = 0;
+                for (size_t cap : {need + need / 8, need}) {   // the first as the tile tables
+                    if (dmalloc_spare(c, &c->bins, cap) == hipSuccess) {
+                        c->cap_bins = cap;
+                        binned = true;
+                        break;
+                    }
+                    (void)hipGetLastError();
+                }
             }
         }
     }
@@ -845,25 +882,32 @@ int trim_mlp_score(trim_ctx* c, const trim_csr_t* g, const int32_t* indeg, const
     if (!indeg || (g->m > 0 && (!src || !scores)) || !params_bf16)
         return fail(TRIM_E_INVAL, "trim_mlp_score: NULL argument");
     const long long n1 = g->n > 0 ? g->n : 1;
-    for (long long need : {trim::kScoreWords * n1, n1}) {   // the second without much room
-        if (need <= c->cap_vf) break;
+    const long long wide = trim::kScoreWords * n1;
+    if (c->cap_vf < wide && (c->cap_vf < n1 || may_allocate(stream))) {
+        // the wide form where there is room for it, else the one that has to be
         const uint64_t others = c->mem_used - (uint64_t)c->cap_vf * 4;
-        if (need != n1 && c->mem_budget && others + (uint64_t)need * 4 > c->mem_budget) continue;
-        dfree(c, c->vf);
-        c->vf = nullptr;
-        c->cap_vf = 0;
-        if (dmalloc(c, &c->vf, (size_t)need * 4) == hipSuccess) {
-            c->cap_vf = need;
-            break;
+        if (!c->mem_budget || others + (uint64_t)wide * 4 <= c->mem_budget) {
+            dfree(c, c->vf);
+            c->vf = nullptr;
+            c->cap_vf = 0;
+            if (dmalloc_spare(c, (void**)&c->vf, (size_t)wide * 4) == hipSuccess) c->cap_vf = wide;
+            (void)hipGetLastError();
         }
-        (void)hipGetLastError();
-        c->vf = nullptr;
-        if (need == n1)
-            return fail(TRIM_E_NOMEM, "cannot allocate vertex features for %d vertices", g->n);
+        if (c->cap_vf < n1) {
+            dfree(c, c->vf);
+            c->vf = nullptr;
+            c->cap_vf = 0;
+            if (dmalloc(c, &c->vf, (size_t)n1 * 4) != hipSuccess) {
+                (void)hipGetLastError();
+                c->vf = nullptr;
+                return fail(TRIM_E_NOMEM, "cannot allocate vertex features for %d vertices", g->n);
+            }
+            c->cap_vf = n1;
+        }
     }
     return launched(trim::mlp_score_launch(g->row_off, g->col, indeg, src, g->n, g->m,
                                            (const short*)params_bf16, scores, c->vf,
-                                           c->cap_vf >= trim::kScoreWords * n1, c->cus,
+                                           c->cap_vf >= wide, c->cus,
                                            (hipStream_t)stream));
 }
 
@@ -880,9 +924,9 @@ int trim_edge_keys(trim_ctx* c, const trim_csr_t* g, int32_t kind, uint64_t seed
     // without room for it the keys come from the offsets
     const long long words = ((long long)g->n + 1) / 2;
     const bool many = kind == 0 && g->m >= 1LL << 25 && g->m >= 8LL * g->n;
-    if (many && words > c->cap_vf) {
+    if (many && words > c->cap_vf && may_allocate(stream)) {
         uint32_t* more = nullptr;
-        if (dmalloc(c, &more, (size_t)words * 4) == hipSuccess) {
+        if (dmalloc_spare(c, (void**)&more, (size_t)words * 4) == hipSuccess) {
             dfree(c, c->vf);
             c->vf = more;
             c->cap_vf = words;

@@ -146,7 +146,8 @@ typedef struct {
  * and stats.rechecks (the entries of the round lists from round 2 on) is the
  * excess over the plain AC-6 total, so edges_total - rechecks = T6.
  * stats.rounds = rounds run = K.  Working memory: 8 more bytes per vertex
- * (the round list), allocated on the first such call.
+ * (the round list) for implicit graphs and explicit ones of fewer than 4,096
+ * vertices, allocated on the first such call.
  */
 #define TRIM_MAX_ROUNDS 64
 

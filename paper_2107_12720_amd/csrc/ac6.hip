@@ -1086,6 +1086,13 @@ inline int round_blocks(long long n, int cus) {
     return (int)b;
 }
 
+// Late registration with a round list is the implicit graph's; explicit graphs
+// watch supports.
+template <class View>
+constexpr bool kRoundList = false;
+template <>
+constexpr bool kRoundList<ImplicitView> = true;
+
 template <class View>
 hipError_t ac6_run(View g, int n, const Work& w, const LaunchCfg& lc, uint32_t* bitmap,
                    uint64_t* worker_edges, trim_stats_t* stats, const int64_t* vbase = nullptr,
@@ -1099,7 +1106,8 @@ hipError_t ac6_run(View g, int n, const Work& w, const LaunchCfg& lc, uint32_t* 
     int* ext = (w.ext && n <= kSplitMaxN) ? w.ext : nullptr;
     // late support registration: R rounds, two round bitmaps in w.c (y[1] is
     // the sinks bitmap the first round reads), the round list in w.hl
-    const int R = (!bitmap_base && w.hl && w.hcap >= n) ? lc.rounds : 0;
+    // (an empty explicit graph comes here for its statistics)
+    const int R = ((kRoundList<View> || n == 0) && !bitmap_base && w.hl && w.hcap >= n) ? lc.rounds : 0;
     const bool defer = R >= 2;
     uint32_t* y[2];
     y[1] = reinterpret_cast<uint32_t*>(w.c);
@@ -1129,7 +1137,7 @@ hipError_t ac6_run(View g, int n, const Work& w, const LaunchCfg& lc, uint32_t* 
                                g, n, chunk, w.a, ext, y[1], preset, w.b, w.q, w.ctr, worker_edges,
                                P, w.part, lc.schedule, lc.forest ? w.jp : nullptr,
                                lc.forest ? w.e : nullptr, nullptr, nullptr, 0LL, nullptr, flt);
-        } else {
+        } else if constexpr (kRoundList<View>) {
             // the round list in w.hl, the moved cursors in w.d
             {
                 Timed t(lc, "ac6_sweep");
@@ -1211,7 +1219,6 @@ hipError_t ac6_run(View g, int n, const Work& w, const LaunchCfg& lc, uint32_t* 
 // of 2,000 202 / 404 and 290 / 562, core+tail of 2^20 401 / 585 and 390 / 666;
 // R-MAT 15 39 / 83 and 51 / 56.  Without it, below this size (graphs of too many
 // edges for one workgroup) the lists stay: their place must hold the filters.
-constexpr int kWatchMinN = 4096;
 static_assert(2 * kWatchMinN >= 3 << (WatchFilter::log_for(kWatchMinN) - 5) &&
               2LL << 20 >= 3 * WatchFilter::kMaxWords, "the filters fit");
 
@@ -1229,9 +1236,10 @@ hipError_t ac6_watch_run(const trim_csr_t& g, const Work& w, const LaunchCfg& lc
     y[1] = reinterpret_cast<uint32_t*>(w.c);
     y[0] = y[1] + round_bitmap_words(n);
     uint32_t* dead = R ? y[(R + 1) & 1] : y[0];
-    // the filters lie behind the round list or where the heads will, which are
-    // made last if at all
-    const WatchFilter flt{reinterpret_cast<uint32_t*>(R ? w.hl + 2 * w.hcap : w.a),
+    // the filters lie where the heads will, which are made last if at all, or, for
+    // graphs too small for that, behind a round list
+    if (n < kWatchMinN && (!w.hl || w.hcap < n)) return hipErrorInvalidValue;
+    const WatchFilter flt{reinterpret_cast<uint32_t*>(n < kWatchMinN ? w.hl + 2 * w.hcap : w.a),
                           WatchFilter::log_for(n)};
     const WatchState a{g.row_off, g.col, n, w.d, w.b, dead, flt, w.ctr, worker_edges, P,
                        lc.schedule, R + 1, lc.forest};

@@ -19,6 +19,11 @@ constexpr long long work_capacity(long long need) {
 // ac6_init may write, up to a cache line.
 constexpr long long round_bitmap_words(long long n) { return ((n + 31) / 32 + 2 + 31) / 32 * 32; }
 
+// AC-6 of explicit graphs watches supports from more vertices than this on, with
+// late registration at every size (ac6.hip).  From this size on the filters of
+// its rounds find room in the list heads, which are made last.
+constexpr long long kWatchMinN = 4096;
+
 // Two-sided trimming watches supports from this many vertices on (ac6_two.hip).
 constexpr long long kTwoWatchMinN = 4096;
 // It keeps two status bitmaps and, behind them, the in-side supports.

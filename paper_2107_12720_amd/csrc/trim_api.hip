@@ -177,8 +177,9 @@ int ensure(trim_ctx* c, int64_t n) {
     return TRIM_OK;
 }
 
-// The round list of late support registration (2 ints per vertex) and its
-// three round filters, allocated on first use.
+// The round list of late support registration on an implicit graph (2 ints per
+// vertex) and its three round filters, allocated on first use.  (Explicit graphs
+// of fewer than kWatchMinN vertices use the filters.)
 int ensure_rounds(trim_ctx* c, int64_t n) {
     const long long need = n > 0 ? n : 1;
     if (need <= c->w.hcap) return TRIM_OK;
@@ -537,7 +538,9 @@ int trim_csr(trim_ctx* c, int algo, const trim_csr_t* g, const trim_opts_t* o,
     hipError_t e = hipSetDevice(c->device);
     if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
     if ((rc = ensure(c, g->n))) return rc;
-    if (algo == TRIM_AC6 && o && o->rounds > 1 && (rc = ensure_rounds(c, g->n))) return rc;
+    if (algo == TRIM_AC6 && o && o->rounds > 1 && g->n < trim::kWatchMinN &&
+        (rc = ensure_rounds(c, g->n)))
+        return rc;
     trim::LaunchCfg lc = launch_cfg(c, algo, o, stream);
     if (o && o->validate && (rc = validate_graph(c, *g, lc.stream))) return rc;
     switch (algo) {

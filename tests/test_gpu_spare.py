@@ -86,3 +86,29 @@ def test_degree_keys_captured_on_a_new_context():
         del graph
         c.close()
     eager.close()
+
+
+@pytest.mark.parametrize("n", [1, 4095, 4096, 4097, 70001])
+def test_late_registration_of_explicit_graphs_needs_no_round_list(n):
+    """Under a cap that holds the plain call's memory, from the size on at which
+    the rounds' filters lie in it; the counts as ever."""
+    import torch
+    import paper_2107_12720_amd as T
+    g = gg.core_tail(n, seed=n) if n > 1 else gg.from_edges(1, np.zeros(0, np.int32),
+                                                            np.zeros(0, np.int32))
+    r = oracle.peel(g)
+    dg = T.DeviceGraph.upload(g)
+    with T.Context(0) as c:
+        c.trim_csr(6, g.n, dg.row_off, dg.col if g.m else None)
+        plain = c.mem_used()
+    c = T.Context(0, mem_budget=plain if n >= 4096 else 0)
+    for _ in range(2):
+        res = c.trim_csr(6, g.n, dg.row_off, dg.col if g.m else None,
+                         opts=T.make_opts(rounds=4))
+        torch.cuda.synchronize()
+        assert np.array_equal(res.bitmap_numpy()[:(g.n + 31) // 32], oracle.bitmap(r.live))
+        st = res.stats_dict()
+        assert (st["edges_total"], st["rounds"], st["rechecks"]) == oracle.counts_deferred(g, r, 4)
+    if n >= 4096:
+        assert c.mem_used() == plain
+    c.close()

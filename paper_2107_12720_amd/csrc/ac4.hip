@@ -16,12 +16,13 @@
 // removed vertex walks both of its lists once.
 //
 // Kernels: ac4_init (counters), ac4_first (the vertices removed from the start,
-// spread evenly over the device; those that their removal takes down are
-// queued), ac4_propagate (persistent workers on per-wavefront LDS rings, WaveQueue;
-// a lane walks a short predecessor list of its removed vertex eight at a
-// time, with the eight decrements in flight together, and then goes on with
-// one of the vertices it removed itself, depth first; long lists are walked
-// by the whole wavefront), ac4_pack (bitmap from cnt > 0).
+// spread evenly over the device), ac4_long (their long lists, in pieces); those
+// that their removal takes down are queued for ac4_propagate (persistent workers
+// on per-wavefront LDS rings, WaveQueue; a lane walks a short predecessor list of
+// its removed vertex eight at a time, with the eight decrements in flight
+// together, and then goes on with one of the vertices it removed itself, depth
+// first; long lists are walked by the whole wavefront), ac4_pack (bitmap from
+// cnt > 0).
 #include "trim_device.h"
 #include "trim_stats.h"
 #include "trim_internal.h"
@@ -65,38 +66,126 @@ constexpr int kCoop = 16;   // predecessor lists longer than this are walked by 
 // core+tail graph 35 % and R-MAT 22 with half of its vertices preset 12 %
 // faster than with 64, the R-MAT 22 chain workload unchanged).
 constexpr int kShareEvery4 = 16;
+// Queue slots a wavefront of ac4_propagate takes at first: on small graphs, whose
+// few removals to start with all fit one or two wavefronts, fewer than its lanes.
+// Core+tail of 12,000 vertices 209 us with 16, 237 with 64, of 36,000 273 and 321;
+// R-MAT from 2^18 vertices on 3 to 12 % slower with 16.
+constexpr int kSpreadTickets = 16, kSpreadN = 1 << 16;
 
-// The removals of the vertices removed from the start (no successors, with kTwo
-// no predecessors either way, or preset; read off the offsets, since counters
-// reach zero while this runs).  On a power-law graph they are most of all
-// removals and nearly all have short lists or none: through the shared queue
-// the 9.4 * 10^6 of R-MAT 24, 2.1 * 10^6 reverse edges in all, took 3.4 of
-// 3.7 ms.  A wavefront takes 64 consecutive vertices at a time; lists of up to
-// kCoop entries are walked by their lanes, longer ones by the wavefront.  Steps
-// go to the workgroups by step_of: in turn 340 us on R-MAT 24, so 296.
-constexpr int kFirstBuf = 2048;   // removed vertices kept in LDS before one reservation
+// A wavefront's buffer in LDS to its reserved place.
+template <class X>
+__device__ __forceinline__ void write_out(const X* buf, X* to, int& fill) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    for (int i = lane_id(); i < fill; i += kWave) to[i] = buf[i];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    fill = 0;
+}
+// One reservation for all wavefronts of the workgroup (256 lanes); each gets
+// the place of its own k.
+template <class Reserve>
+__device__ __forceinline__ int block_reserve(int k, Reserve reserve) {
+    __shared__ int s_k[256 / kWave], s_base;
+    const int wv = threadIdx.x / kWave;
+    __syncthreads();
+    if (lane_id() == 0) s_k[wv] = k;
+    __syncthreads();
+    int before = 0, all = 0;
+    for (int w = 0; w < 256 / kWave; ++w) {
+        before += w < wv ? s_k[w] : 0;
+        all += s_k[w];
+    }
+    if (threadIdx.x == 0 && all > 0) s_base = reserve(all);
+    __syncthreads();
+    return all > 0 ? s_base + before : 0;
+}
+
+// Items that a wavefront collects in LDS (room for kStepItems more after
+// make_room), so that it makes one reservation in the queue for hundreds.  Its
+// size, with the pieces', leaves room for eight workgroups a CU (with seven,
+// 20 KB, ac4_first took 338 us on R-MAT 24).
+constexpr int kStepItems = kWave * kBatch;   // removals of one step at most
+struct ItemBuf {
+    static constexpr int kItems = kStepItems + 256;
+    uint32_t* buf;   // kItems words of LDS, the wavefront's own
+    uint32_t* q;
+    int* ctr;
+    int fill = 0;    // the same in every lane
+    __device__ __forceinline__ void make_room() {
+        if (fill > kItems - kStepItems) flush();
+    }
+    __device__ __forceinline__ void push(bool has, int u) {
+        const uint64_t m = ballot(has);
+        if (has) buf[fill + popc(m & lanes_below())] = make_item(0, u);
+        fill += popc(m);
+    }
+    __device__ __forceinline__ int reserve(int k) const {
+        add_dev(ctr + kPending, k);
+        return add_dev(ctr + kQTail, k);
+    }
+    __device__ __forceinline__ void flush() {
+        int base = 0;
+        if (lane_id() == 0) base = reserve(fill);
+        write_out(buf, q + __shfl(base, 0), fill);
+    }
+    // At the kernel's end, by all of the workgroup.
+    __device__ __forceinline__ void finish() {
+        const int base = block_reserve(fill, [&](int k) { return reserve(k); });
+        write_out(buf, q + base, fill);
+    }
+};
+
+// One step of a walk: entries j < nb of `at` (stride apart) lose a neighbour on
+// this side; the vertices whose last one it was are collected.
+template <bool kTwo>
+__device__ __forceinline__ void first_step(const int* at, int stride, int nb, int* ctr_of,
+                                           int* dead, ItemBuf& out, int sched, uint64_t key) {
+    int u[kBatch], old[kBatch];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j)
+        if (j < nb) u[j] = at[j * stride];
+    if (sched & TRIM_SCHED_JITTER) jitter_nap(key);
+    bool any = false;
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+        old[j] = 0;
+        if (j < nb) old[j] = add_dev(ctr_of + u[j], -1);
+    }
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) any = any || old[j] == 1;
+    if (!ballot(any)) return;
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) out.push(old[j] == 1 && removes<kTwo>(dead, u[j]), u[j]);
+}
+
+// The vertices removed from the start (no successors, with kTwo no predecessors
+// either way, or preset; read off the offsets, since counters reach zero while
+// this runs).  On a power-law graph they are most of all removals and nearly all
+// have no list to walk or a short one: through the shared queue the 9.4 * 10^6 of
+// R-MAT 24, 2.1 * 10^6 reverse edges in all, took 3.4 of 3.7 ms.  A lane takes a
+// list of up to kBatch entries itself, in one step.  Longer ones are listed in
+// pieces of `piece` entries (vertex, number of the piece) for ac4_long, which
+// spreads them over the device: walked here, the hubs of an R-MAT graph, its low
+// ids, met in few wavefronts (R-MAT 20 of edge factor 16 with 30 % of the vertices
+// kept: 3,608 us here, 148 + 1,463 with ac4_long, 2,771 through the queue).  (Two-sided, a vertex removed from the start has
+// one list at most.)  Steps go to the workgroups by step_of: in turn 340 us on
+// R-MAT 24, so 296.
+constexpr int kLongBuf = 128;   // pieces a wavefront buffers
 
 template <bool kTwo>
 __global__ __launch_bounds__(256) void ac4_first(const int* rrow_off, const int* rcol,
                                                  const int* row_off, const int* col,
                                                  const uint32_t* preset, int n, int* cnt,
                                                  int* dead, uint32_t* q, int* ctr,
-                                                 uint64_t* worker_edges, int P, int sched) {
-    __shared__ uint32_t buf[kFirstBuf];
-    __shared__ int s_n, s_base;
+                                                 uint64_t* worker_edges, int P, int sched,
+                                                 uint64_t* pieces, int piece) {
+    __shared__ uint32_t items[256 / kWave][ItemBuf::kItems];
+    __shared__ uint64_t longs[256 / kWave][kLongBuf];
     __shared__ uint64_t red[16];
-    if (threadIdx.x == 0) s_n = 0;
-    __syncthreads();
-    auto push = [&](bool has, int u) {
-        const uint64_t m = ballot(has);
-        if (!m) return;
-        int base = 0;
-        if (lane_id() == 0) base = atomicAdd(&s_n, popc(m));
-        base = __shfl(base, 0) + popc(m & lanes_below());
-        if (has && base < kFirstBuf) buf[base] = make_item(0, u);
-        const int slot = wave_append_slot(has && base >= kFirstBuf, ctr + kQTail, ctr + kPending);
-        if (slot >= 0) q[slot] = make_item(0, u);
-    };
+    const int wv = threadIdx.x / kWave;
+    ItemBuf out{items[wv], q, ctr};
+    int nlong = 0;   // the same in every lane
     uint64_t edges = 0;
     const int steps = (int)((n + (long long)blockDim.x - 1) / blockDim.x);
     for (int b0 = blockIdx.x; b0 < steps; b0 += gridDim.x) {
@@ -106,60 +195,70 @@ __global__ __launch_bounds__(256) void ac4_first(const int* rrow_off, const int*
         const bool gone = v < n && (b == be || (kTwo && rb == re) ||
                                     (preset && ((preset[x >> 5] >> (x & 31)) & 1u)));
         if (!ballot(gone)) continue;
-#pragma unroll
-        for (int ph = 0; ph < (kTwo ? 2 : 1); ++ph) {
-            const int* adj = ph ? col : rcol;
-            int* ctr_of = ph ? cnt + n : cnt;
-            int k = gone ? (ph ? b : rb) : 0;
-            const int e = gone ? (ph ? be : re) : 0;
-            edges += (uint64_t)(e - k);
-            for (uint64_t big = ballot(e - k > kCoop); big; big &= big - 1) {
-                const int owner = __ffsll((unsigned long long)big) - 1;
-                // (unsigned: see step_index)
-                const uint32_t kb = __shfl(k, owner), eb = __shfl(e, owner);
-                for (uint32_t at = kb; at < eb; at += kWave * kBatch) {
-                    int u[kBatch], old[kBatch];
-#pragma unroll
-                    for (int j = 0; j < kBatch; ++j) {
-                        const uint32_t p = at + j * kWave + lane_id();
-                        if (p < eb) u[j] = adj[p];
-                    }
-                    if (sched & TRIM_SCHED_JITTER) jitter_nap(((uint64_t)kb << 20) ^ at);
-#pragma unroll
-                    for (int j = 0; j < kBatch; ++j)
-                        if (at + j * kWave + lane_id() < eb) old[j] = add_dev(ctr_of + u[j], -1);
-#pragma unroll
-                    for (int j = 0; j < kBatch; ++j)
-                        push(at + j * kWave + lane_id() < eb && old[j] == 1 &&
-                                 removes<kTwo>(dead, u[j]), u[j]);
-                }
-                if (lane_id() == owner) k = e;
+        const bool post = kTwo && rb == re;   // the list is the successors
+        const int k = post ? b : rb, len = gone ? (post ? be : re) - k : 0;
+        const uint64_t m = ballot(len > kBatch && len <= piece);
+        if (m) {
+            if (nlong > kLongBuf - kWave) {
+                int base = 0;
+                if (lane_id() == 0) base = add_dev(ctr + kA4Pieces, nlong);
+                write_out(longs[wv], pieces + __shfl(base, 0), nlong);
             }
-            while (ballot(k < e)) {
-                const int nb = min(kBatch, e - k);
-                int u[kBatch], old[kBatch];
-#pragma unroll
-                for (int j = 0; j < kBatch; ++j)
-                    if (j < nb) u[j] = adj[k + j];
-                if (sched & TRIM_SCHED_JITTER) jitter_nap(((uint64_t)k << 16) ^ v);
-#pragma unroll
-                for (int j = 0; j < kBatch; ++j)
-                    if (j < nb) old[j] = add_dev(ctr_of + u[j], -1);
-#pragma unroll
-                for (int j = 0; j < kBatch; ++j)
-                    push(j < nb && old[j] == 1 && removes<kTwo>(dead, u[j]), u[j]);
-                if (nb > 0) k += nb;
-            }
+            if (len > kBatch && len <= piece)
+                longs[wv][nlong + popc(m & lanes_below())] = (uint64_t)(uint32_t)v;
+            nlong += popc(m);
+        }
+        if (len > piece) {
+            const int c = (len - 1) / piece + 1, base = add_dev(ctr + kA4Pieces, c);
+            for (int i = 0; i < c; ++i) pieces[base + i] = (uint64_t)i << 32 | (uint32_t)v;
+        }
+        const int nb = len <= kBatch ? len : 0;
+        if (!ballot(nb > 0)) continue;
+        out.make_room();
+        edges += (uint64_t)nb;
+        first_step<kTwo>((post ? col : rcol) + k, 1, nb, post ? cnt + n : cnt, dead, out, sched,
+                         ((uint64_t)k << 16) ^ v);
+    }
+    out.finish();
+    const int base = block_reserve(nlong, [&](int k) { return add_dev(ctr + kA4Pieces, k); });
+    write_out(longs[wv], pieces + base, nlong);
+    edges = block_sum(edges, red);
+    if (threadIdx.x == 0 && edges) add_dev(worker_edges + (blockIdx.x % P), edges);
+}
+
+// The long lists of ac4_first, a piece per wavefront at a time.
+template <bool kTwo>
+__global__ __launch_bounds__(256) void ac4_long(const int* rrow_off, const int* rcol,
+                                                const int* row_off, const int* col, int n,
+                                                int* cnt, int* dead, uint32_t* q, int* ctr,
+                                                uint64_t* worker_edges, int P, int sched,
+                                                const uint64_t* pieces, int piece) {
+    __shared__ uint32_t items[256 / kWave][ItemBuf::kItems];
+    __shared__ uint64_t red[16];
+    const int c = ctr[kA4Pieces];
+    if (c == 0) return;
+    const int waves = (int)(gridDim.x * blockDim.x / kWave);
+    const int wave = (int)(blockIdx.x * blockDim.x + threadIdx.x) / kWave;
+    ItemBuf out{items[threadIdx.x / kWave], q, ctr};
+    uint64_t edges = 0;
+    for (int i = wave; i < c; i += waves) {
+        const uint64_t x = pieces[i];
+        const int v = (int)(uint32_t)x;
+        const bool post = kTwo && rrow_off[v] == rrow_off[v + 1];
+        const int* off = post ? row_off : rrow_off;
+        const uint32_t e = off[v + 1];   // (unsigned: see step_index)
+        const uint32_t p0 = off[v] + (uint32_t)(x >> 32) * (uint32_t)piece;
+        const uint32_t p1 = min(e, p0 + (uint32_t)piece);
+        if (lane_id() == 0) edges += p1 - p0;
+        for (uint32_t p = p0; p < p1; p += kStepItems) {
+            out.make_room();
+            const int mine = (int)(p1 - p) - lane_id();   // entry j of the lane: j * kWave < mine
+            first_step<kTwo>((post ? col : rcol) + p + lane_id(), kWave,
+                             (mine + kWave - 1) / kWave, post ? cnt + n : cnt, dead, out, sched,
+                             ((uint64_t)p << 20) ^ v);
         }
     }
-    __syncthreads();
-    const int k = min(s_n, kFirstBuf);
-    if (threadIdx.x == 0 && k > 0) {
-        add_dev(ctr + kPending, k);
-        s_base = add_dev(ctr + kQTail, k);
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < k; i += blockDim.x) q[s_base + i] = buf[i];
+    out.finish();
     edges = block_sum(edges, red);
     if (threadIdx.x == 0 && edges) add_dev(worker_edges + (blockIdx.x % P), edges);
 }
@@ -172,13 +271,14 @@ __global__ __launch_bounds__(256) void ac4_propagate(const int* rrow_off, const 
                                                      const int* row_off, const int* col, int n,
                                                      int* cnt, int* dead, uint32_t* q, int* ctr,
                                                      uint64_t* worker_edges, uint64_t* part,
-                                                     int sched, int budget) {
+                                                     int sched, int budget, int tickets) {
     __shared__ uint32_t rings[256 / kWave][kLocalQ];
     __shared__ int ring_tail[256 / kWave];
     WaveQueue wq;
     const int wv = threadIdx.x / kWave;
     wq.init(rings[wv], &ring_tail[wv], q, ctr + kQHead, ctr + kQTail, ctr + kPending,
             ctr + kStall, budget, kShareEvery4);
+    wq.claim(tickets);
     uint32_t item = kNone;
     int k = 0, e = 0, ph = 0;
     bool started = false;
@@ -306,6 +406,8 @@ hipError_t ac4_run(const trim_csr_t& g, const Work& w, const LaunchCfg& lc, uint
                    uint64_t* worker_edges, trim_stats_t* stats, const uint32_t* preset) {
     const int n = g.n, P = lc.workers;
     int pack_blocks = 0;
+    uint64_t* pieces = reinterpret_cast<uint64_t*>(w.e);   // the three arrays of w.e and w.jp
+    const int piece = piece_entries(n, g.m, kStepItems);
     {
         Timed t(lc, kTwo ? "ac4t_init" : "ac4_init");
         hipLaunchKernelGGL(ac4_init<kTwo>, dim3(grid_for(n, 256, 16384)), dim3(256), 0,
@@ -317,13 +419,19 @@ hipError_t ac4_run(const trim_csr_t& g, const Work& w, const LaunchCfg& lc, uint
             Timed t(lc, kTwo ? "ac4t_first" : "ac4_first");
             hipLaunchKernelGGL(ac4_first<kTwo>, dim3(grid_for(n, 256, lc.cus * 8)), dim3(256), 0,
                                lc.stream, g.rrow_off, g.rcol, g.row_off, g.col, preset, n, w.a,
-                               w.d, w.q, w.ctr, worker_edges, P, lc.schedule);
+                               w.d, w.q, w.ctr, worker_edges, P, lc.schedule, pieces, piece);
+        }
+        {
+            Timed t(lc, kTwo ? "ac4t_long" : "ac4_long");
+            hipLaunchKernelGGL(ac4_long<kTwo>, dim3(lc.cus * 8), dim3(256), 0, lc.stream,
+                               g.rrow_off, g.rcol, g.row_off, g.col, n, w.a, w.d, w.q, w.ctr,
+                               worker_edges, P, lc.schedule, pieces, piece);
         }
         {
             Timed t(lc, kTwo ? "ac4t_propagate" : "ac4_propagate");
             hipLaunchKernelGGL(ac4_propagate<kTwo>, dim3(P), dim3(256), 0, lc.stream, g.rrow_off,
                                g.rcol, g.row_off, g.col, n, w.a, w.d, w.q, w.ctr, worker_edges,
-                               w.part, lc.schedule, lc.budget);
+                               w.part, lc.schedule, lc.budget, n <= kSpreadN ? kSpreadTickets : kWave);
         }
         Timed t(lc, kTwo ? "ac4t_pack" : "ac4_pack");
         pack_blocks = grid_for(n, 256, lc.cus * 4);

@@ -34,6 +34,13 @@ constexpr long long work_c_ints(long long cap) {
     return cap < kTwoWatchMinN ? cap : two_watch_ints(cap);
 }
 
+// AC-4's long lists in pieces of whole steps: at most n + m / piece <= 1.5 n pieces,
+// for which three arrays of n ints have room (eight bytes each).
+constexpr int piece_entries(long long n, long long m, int step) {
+    const long long k = n > 0 && m > 0 ? (2 * m + n - 1) / n : 1;
+    return k > (1 << 30) ? 1 << 30 : (int)((k + step - 1) / step * step);
+}
+
 // Edge positions go up to 2^31 - 1, the end of the last list, so a scan in steps
 // of several entries keeps them unsigned: a position plus a step stays below 2^32.
 // Entry j of the step at p of a list that ends at e, the last one from there on.

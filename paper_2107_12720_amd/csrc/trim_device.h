@@ -321,11 +321,12 @@ struct WaveQueue {
         }
     }
 
-    // Every lane takes a ticket (only when none is outstanding).
-    __device__ __forceinline__ void claim() {
+    // The first `width` lanes take a ticket (only when none is outstanding).
+    __device__ __forceinline__ void claim(int width = kWave) {
         int base = 0;
-        if (lane_id() == 0) base = add_dev(qhead, kWave);
+        if (lane_id() == 0) base = add_dev(qhead, width);
         ticket = __shfl(base, 0) + lane_id();
+        if (lane_id() >= width) ticket = -1;
     }
 
     __device__ __forceinline__ void spill_ring(int k) {

@@ -29,6 +29,7 @@ enum Ctr : int {
     kLvCnt0 = 212,   // AC-6 level-synchronous phases: list sizes, rotating over 3 slots
     kLvPhases = 215, // phases run
     kAcWork = 216,   // AC-3: live-list entries processed over all rounds
+    kA4Pieces = 220, // AC-4: pieces of long lists of the vertices removed from the start
     kCnt0 = 224,     // AC-3 live-list sizes, rotating over 3 slots
     kStall = 240,    // watchdog: nonzero once a persistent kernel gave up (opts.budget)
     // AC-6 with late support registration (opts.rounds): the round list's

@@ -82,3 +82,16 @@ def test_scans_end_at_the_largest_edge_number(tmp_path):
                     if (next != e) ++bad;
                 }""", ["layout.h"])
     assert r.returncode == 0, r.stdout
+
+
+def test_pieces_of_long_lists_fit(tmp_path):
+    # n lists of m entries in all make at most n + m / piece pieces, eight bytes each, in three
+    # arrays of n ints (n at least 64 of capacity)
+    r = run_cpp(tmp_path, """
+        for (long long n : {1LL, 2LL, 3LL, 64LL, 100LL, 1000LL, 65536LL, 1LL << 26, 1LL << 29})
+            for (long long m : {0LL, 1LL, 511LL, 100000LL, 1LL << 24, (1LL << 31) - 1}) {
+                const long long piece = piece_entries(n, m, 512);
+                if (piece < 1 || piece > 1 << 30 || (piece % 512 && piece != 1 << 30)) ++bad;
+                if (8 * (n + m / piece) > 12 * work_capacity(n)) ++bad;
+            }""", ["layout.h"])
+    assert r.returncode == 0, r.stdout

@@ -46,10 +46,12 @@ __device__ __forceinline__ ClosedLists close_lists(int* head, int* ext, int x) {
 // list of the first live neighbour found; `edges` receives the positions
 // checked.  S: memory scope of the record store and the join (agent scope
 // unless one workgroup owns the whole graph).  ext: the split S_more lists,
-// or nullptr.
+// or nullptr.  bits: the neighbours' statuses in LDS, or nullptr (their list
+// heads tell).
 template <class View, int S = __HIP_MEMORY_SCOPE_AGENT>
 __device__ __forceinline__ bool resume(const View& g, int u, int p0, int* head, uint64_t* rec,
-                                       uint64_t& edges, int sched, int* ext = nullptr) {
+                                       uint64_t& edges, int sched, int* ext = nullptr,
+                                       const uint32_t* bits = nullptr) {
     // kScan successors at a time: their targets, then their list heads, each
     // group of loads in flight together, then the joins in list order.
     constexpr int kScan = 4;
@@ -63,7 +65,10 @@ __device__ __forceinline__ bool resume(const View& g, int u, int p0, int* head, 
             if (p + j < end) w[j] = g.target(u, (int)(p + j), ctx);
 #pragma unroll
         for (int j = 0; j < kScan; ++j)
-            if (p + j < end) h[j] = ld_cached(join_slot(head, ext, w[j], p + j + 1 == end, u));
+            if (p + j < end)
+                h[j] = bits && ((bits[w[j] >> 5] >> (w[j] & 31)) & 1u)
+                           ? kDead
+                           : ld_cached(join_slot(head, ext, w[j], p + j + 1 == end, u));
 #pragma unroll
         for (int j = 0; j < kScan; ++j) {
             if (p + j >= end) break;

@@ -14,24 +14,14 @@
 // resumed scans in the middling graphs; with supporting sets as lists in
 // device memory it was the dependent accesses of every phase.
 //
-// Larger graphs are trimmed over lists (own_graph):
-//   init   both list heads kDead (no successor) or kEmpty;
-//   sweep  DoPost for every vertex: the first successor that is not a sink
-//          becomes its support (join: exchange into the support's S_more or
-//          S_last head, whichever its position selects); vertices with none
-//          become CLOSE items;
-//   phases each phase takes the list the previous one built: CLOSE(x)
-//          exchanges both heads of x with kDead and walks the two lists it
-//          got back -- every S_last member is removed with x (a CLOSE item
-//          for the next phase), every S_more member resumes its scan after
-//          its old support (a RESCAN item); RESCAN(x) resumes x's scan and
-//          closes x on the spot if it finds nothing.  A workgroup barrier
-//          ends a phase; the graph is done when a phase builds an empty list.
-//   pack   the graph's own bitmap words, its live count, its traversed-edge
-//          total (exact: one workgroup makes all of the graph's checks).
-// Items and list counters live in LDS; heads, records and the two phase lists
-// of a graph live in device memory at the graph's own vertex range, where the
-// workgroup's L2 keeps them for the graph's lifetime.
+// Larger graphs are trimmed over lists (own_graph; group_lists.h): the first
+// successor that is not a sink becomes a vertex's support, joined by an exchange
+// of the support's S_more or S_last head, whichever its position selects;
+// vertices with none start the phases.  Heads, records and the two phase lists of
+// a graph live in device memory at the graph's own vertex range, where the
+// workgroup's L2 keeps them for the graph's lifetime; there, too, a smaller graph
+// finds its positions, its supports if the LDS does not hold them, and the lists
+// of a deep, narrow remainder.
 #include <climits>
 
 #include "trim_internal.h"
@@ -43,20 +33,7 @@
 namespace trim {
 namespace {
 
-// One graph of the batch: global vertex ids vb + local id.
-struct OwnedView {
-    const int* row_off;
-    const int* col;
-    int vb;
-    __device__ __forceinline__ int vctx(int) const { return vb; }
-    __device__ __forceinline__ int begin(int v) const { return row_off[v]; }
-    __device__ __forceinline__ int end(int v) const { return row_off[v + 1]; }
-    __device__ __forceinline__ int target(int, int p, int b) const { return b + col[p]; }
-};
-
-enum : uint32_t { kOwnClose = 0, kOwnRescan = 1 };
 constexpr int kOwnMaxBlock = 1024;
-constexpr int kOwnStage = 128;    // items staged per wavefront before one reservation
 constexpr int kOwnUnroll = 2;     // sweep vertices per lane in flight
 // LDS of a workgroup, shared out as the graph at hand needs it; a sixteenth for
 // each wavefront with a graph of its own, which holds the statuses, supports
@@ -70,7 +47,9 @@ static_assert(watch_fits(kOwnWaveN, kWave, kOwnWaveN) &&
 static_assert(kWatchLdsN / 8 + kWatchLdsN * 2 + 16 * kWatchList * 2 <= kOwnLds,
               "statuses, supports and lists of the largest graph with supports in LDS");
 static_assert(kWatchMaxN / 8 + 16 * kWatchList * 4 <= kOwnLds &&
-              kOwnLds - kWatchMaxN / 8 >= kWatchMaxN / 8, "the same without the supports");
+              2 * (kWatchMaxN / 8) + sizeof(ListStage<16>) <= kOwnLds,
+              "the same without the supports; a second bitmap and the stage of the lists");
+static_assert(sizeof(ListStage<1>) <= kOwnWaveN * 2, "a wavefront's stage in its supports' place");
 // A wavefront trims a graph alone up to this n + m (and kOwnWaveN vertices).
 constexpr uint32_t kOwnWaveSize = 1u << 16;
 constexpr int kKeys = 2 * 33;
@@ -109,11 +88,6 @@ __global__ void batch_order(const int64_t* vbase, const int* row_off, int G, int
         order[atomicAdd(&hist[size_key(vbase, row_off, gi)], 1)] = gi;
 }
 
-// Every word of a graph's state (heads, records, phase lists) is touched by
-// its owning workgroup only, so workgroup-scope accesses keep it coherent;
-// the workgroup's L2 serves them.
-constexpr int kWG = __HIP_MEMORY_SCOPE_WORKGROUP;
-
 // Shared state of an owned-graph kernel's workgroup (LDS).
 struct OwnShared {
     __attribute__((aligned(16))) unsigned char raw[kOwnLds];
@@ -122,15 +96,6 @@ struct OwnShared {
     int claim;
     uint64_t red[16];
 };
-// own_graph's use of raw: per-wavefront item staging, the length of the list
-// being built.
-struct OwnStage {
-    uint32_t item[kOwnMaxBlock / kWave][kOwnStage];
-    int n[kOwnMaxBlock / kWave];
-    int cnt;
-};
-static_assert(sizeof(OwnStage) <= kOwnLds, "");
-
 // Per-thread running totals of the kernel.
 struct OwnTotals {
     WatchTotals w;
@@ -153,81 +118,56 @@ struct OwnArgs {
     int sched;
 };
 
-// Trim graph gi over lists, by the whole workgroup; phases end at workgroup
-// barriers.
-__device__ void own_graph(const OwnArgs& a, int gi, OwnShared& sh, OwnTotals& t) {
-    OwnStage& st = *reinterpret_cast<OwnStage*>(sh.raw);
-    const int wv = threadIdx.x / kWave;
+// Graph gi's part of the arrays.
+__device__ __forceinline__ CachedView own_view(const OwnArgs& a, int gi) {
+    return CachedView{a.row_off + a.vbase[gi], a.col, a.total_m};
+}
+__device__ __forceinline__ ListArrays own_lists(const OwnArgs& a, int gi) {
+    const int64_t vb = a.vbase[gi];
+    return ListArrays{a.head + 2 * vb, a.rec + vb, a.l0 + vb, a.l1 + vb};
+}
+
+using OwnLists = GroupLists<CachedView, false>;
+
+// The first list of graph gi, larger than watch.h takes, by the whole workgroup.
+__device__ __forceinline__ void own_graph(const OwnArgs& a, int gi, OwnLists& l, OwnTotals& t) {
+    const int n = (int)(a.vbase[gi + 1] - a.vbase[gi]);
     const int rank = threadIdx.x, size = blockDim.x;
-    const int *row_off = a.row_off, *col = a.col;
-    int* head = a.head;
-    uint64_t* rec = a.rec;
-    auto sync = [&]() {
-        complete_mem();
-        __syncthreads();
-    };
-    const int vb = (int)a.vbase[gi], ve = (int)a.vbase[gi + 1];
-    const OwnedView g{row_off, col, vb};
-    uint32_t* out = nullptr;
-    // move this wavefront's staged items to the list being built (wave-uniform)
-    auto flush = [&]() {
-        const int k = st.n[wv];
-        if (k == 0) return;
-        int base = 0;
-        if (lane_id() == 0) base = atomicAdd(&st.cnt, k);
-        base = __shfl(base, 0);
-        for (int i = lane_id(); i < k; i += kWave) out[base + i] = st.item[wv][i];
-        __builtin_amdgcn_wave_barrier();
-        if (lane_id() == 0) st.n[wv] = 0;
-        __builtin_amdgcn_wave_barrier();
-    };
-    // stage this lane's item, if any (wave-uniform)
-    auto emit = [&](uint32_t it) {
-        const uint64_t mk = ballot(it != kNone);
-        const int k = popc(mk);
-        if (k == 0) return;
-        if (st.n[wv] + k > kOwnStage) flush();
-        const int base = st.n[wv];
-        if (it != kNone) st.item[wv][base + popc(mk & lanes_below())] = it;
-        __builtin_amdgcn_wave_barrier();
-        if (lane_id() == 0) st.n[wv] = base + k;
-        __builtin_amdgcn_wave_barrier();
-    };
+    const CachedView& g = l.g;
+    const ListArrays& m = l.m;
     uint64_t edges = 0;
-    if (lane_id() == 0) st.n[wv] = 0;
-    if (rank == 0) st.cnt = 0;
+    l.begin();
     // init: the heads of the graph's vertices
-    for (int v = vb + rank; v < ve; v += size) {
-        const int b = row_off[v], e = row_off[v + 1];
+    for (int v = rank; v < n; v += size) {
+        const int b = g.begin(v), e = g.end(v);
         const int h = b == e ? kDead : kEmpty;
-        reinterpret_cast<int2*>(head)[v] = make_int2(h, h);
+        reinterpret_cast<int2*>(m.head)[v] = make_int2(h, h);
         t.w.deg += (uint64_t)(e - b);
     }
-    sync();
+    l.sync();
     // sweep: only sinks are removed while it runs, so a target is live iff it
     // has a successor
-    auto sink = [&](int w) { return row_off[w] == row_off[w + 1]; };
-    out = a.l0 + vb;
-    for (int base = vb; base < ve; base += kOwnUnroll * size) {
+    auto sink = [&](int w) { return g.begin(w) == g.end(w); };
+    for (int base = 0; base < n; base += kOwnUnroll * size) {
         int v[kOwnUnroll], b[kOwnUnroll], e[kOwnUnroll], p[kOwnUnroll], w[kOwnUnroll];
         bool ok[kOwnUnroll];
 #pragma unroll
         for (int k = 0; k < kOwnUnroll; ++k) {
             v[k] = base + k * size + rank;
             b[k] = e[k] = 0;
-            if (v[k] < ve) {
-                b[k] = row_off[v[k]];
-                e[k] = row_off[v[k] + 1];
+            if (v[k] < n) {
+                b[k] = g.begin(v[k]);
+                e[k] = g.end(v[k]);
             }
             p[k] = b[k];
-            w[k] = b[k] < e[k] ? vb + col[b[k]] : vb;
+            w[k] = b[k] < e[k] ? g.col[b[k]] : 0;
         }
 #pragma unroll
         for (int k = 0; k < kOwnUnroll; ++k) {
             ok[k] = b[k] < e[k] && !sink(w[k]);
             if (b[k] < e[k] && !ok[k]) {
                 for (++p[k]; p[k] < e[k]; ++p[k]) {
-                    w[k] = vb + col[p[k]];
+                    w[k] = g.col[p[k]];
                     if (!sink(w[k])) break;
                 }
                 ok[k] = p[k] < e[k];
@@ -239,115 +179,73 @@ __device__ void own_graph(const OwnArgs& a, int gi, OwnShared& sh, OwnTotals& t)
             if (ok[k]) {
                 if (a.sched & TRIM_SCHED_JITTER)
                     jitter_nap(((uint64_t)gi << 32) ^ (uint32_t)v[k]);
-                old[k] = xchg_s<kWG>(head + 2 * w[k] + (p[k] + 1 == e[k]), v[k]);
+                old[k] = xchg_s<kWG>(m.head + 2 * w[k] + (p[k] + 1 == e[k]), v[k]);
             }
         }
 #pragma unroll
         for (int k = 0; k < kOwnUnroll; ++k) {
             uint32_t it = kNone;
             if (ok[k]) {
-                st_s<kWG>(rec + v[k], pack_rec(old[k], p[k]));
+                st_s<kWG>(m.rec + v[k], pack_rec(old[k], p[k]));
                 edges += (uint64_t)(p[k] - b[k] + 1);
             } else if (b[k] < e[k]) {
                 it = make_item(kOwnClose, v[k]);
                 edges += (uint64_t)(e[k] - b[k]);
             }
-            emit(it);
+            l.emit(it);
         }
     }
-    flush();
+    l.flush();
     t.w.sweep += edges;
-    sync();
-    // phases
-    uint32_t* in = a.l0 + vb;
-    out = a.l1 + vb;
-    int ph = 0;
-    for (int n_in = st.cnt; n_in > 0; n_in = st.cnt) {
-        sync();   // every thread has read the count
-        if (rank == 0) st.cnt = 0;
-        sync();
-        ++ph;
-        for (int base = 0; base < n_in; base += size) {
-            const int i = base + rank;
-            const uint32_t it = i < n_in ? (uint32_t)ld_s<kWG>((const int*)in + i) : kNone;
-            int walk_last = -1, walk_more = -1, cx = -1;
-            if (it != kNone) {
-                const int x = item_vertex(it);
-                if (item_kind(it) == kOwnRescan) {
-                    // x is in no list until it joins again: its record is stable
-                    const uint64_t r = ld_s<kWG>(rec + x);
-                    if (a.sched & TRIM_SCHED_JITTER) jitter_nap((uint64_t)x);
-                    if (resume<OwnedView, kWG>(g, x, rec_cursor(r) + 1, head, rec, edges, a.sched))
-                        t.w.joins += 1;
-                    else
-                        cx = x;
-                } else {
-                    cx = x;
-                }
-            }
-            if (cx >= 0) {
-                if (a.sched & TRIM_SCHED_JITTER) jitter_nap((uint64_t)cx << 8);
-                const int2 ab = xchg2_s<kWG>(head + 2 * cx, kDead, kDead);
-                t.w.closes += 1;
-                walk_more = ab.x;
-                walk_last = ab.y;
-            }
-            // a member's link is read before its item exists: its own
-            // processing, in the next phase, is the only thing that can change
-            // its record
-            while (ballot(walk_last >= 0 || walk_more >= 0)) {
-                uint32_t e = kNone;
-                if (walk_last >= 0) {
-                    const int nx = ld_s<kWG>(rec_link(rec, walk_last));
-                    e = make_item(kOwnClose, walk_last);
-                    walk_last = nx;
-                } else if (walk_more >= 0) {
-                    const int nx = ld_s<kWG>(rec_link(rec, walk_more));
-                    e = make_item(kOwnRescan, walk_more);
-                    walk_more = nx;
-                }
-                t.w.visited += e != kNone;
-                emit(e);
-            }
-        }
-        flush();
-        sync();
-        uint32_t* tmp = in;
-        in = out;
-        out = tmp;
-    }
+    t.w.edges += edges;
+    l.sync();
+}
+
+// Graph gi from its first list to its outputs; `before`: the totals' edges
+// before the graph, `passes`: those it had.
+__device__ __forceinline__ void own_finish(const OwnArgs& a, int gi, OwnLists& l, uint64_t before,
+                                           int passes, OwnShared& sh, OwnTotals& t) {
+    const int n = (int)(a.vbase[gi + 1] - a.vbase[gi]);
+    const int rank = threadIdx.x, size = blockDim.x;
+    const ListArrays& m = l.m;
+    const int ph = passes + l.run(INT_MAX);
     t.max_phases = ph > t.max_phases ? ph : t.max_phases;
     // pack: the graph's bitmap words (bits past its n stay zero)
     const int64_t wb = a.bitmap_base[gi], we = a.bitmap_base[gi + 1];
-    const int nwords = (ve - vb + 31) >> 5;
-    for (int base = vb + wv * kWave; base < ve; base += size) {
+    const int nwords = (n + 31) >> 5;
+    for (int base = l.wave() * kWave; base < n; base += size) {
         const int v = base + lane_id();
-        const uint64_t m = ballot(v < ve && ld_s<kWG>(head + 2 * v) != kDead);
+        const uint64_t b = ballot(v < n && ld_s<kWG>(m.head + 2 * v) != kDead);
         if (lane_id() == 0) {
-            const int wi = (base - vb) >> 5;
-            a.bitmaps[wb + wi] = (uint32_t)m;
-            if (wi + 1 < nwords) a.bitmaps[wb + wi + 1] = (uint32_t)(m >> 32);
-            t.w.live += (uint32_t)popc(m);
+            const int wi = base >> 5;
+            a.bitmaps[wb + wi] = (uint32_t)b;
+            if (wi + 1 < nwords) a.bitmaps[wb + wi + 1] = (uint32_t)(b >> 32);
+            t.w.live += (uint32_t)popc(b);
         }
     }
     for (int64_t wi = wb + nwords + rank; wi < we; wi += size) a.bitmaps[wi] = 0;
-    edges = block_sum(edges, sh.red);
-    if (rank == 0) {
-        a.graph_edges[gi] = edges;
-        t.w.edges += edges;
-    }
-    sync();
+    const uint64_t edges = block_sum(t.w.edges - before, sh.red);
+    if (rank == 0) a.graph_edges[gi] = edges;
+    l.sync();
+}
+
+// LDS of own_watch: the statuses, then the supports when they are 16-bit, then
+// the list.  Stage of the lists: the supports' place, or behind a second bitmap.
+template <class Sup>
+__device__ __forceinline__ unsigned char* own_stage(unsigned char* raw, int max_n) {
+    return raw + (sizeof(Sup) == 2 ? 1 : 2) * (max_n / 8);
 }
 
 // Trim graph gi as watch.h describes: by the workgroup, or (kWaveGroup) by this
-// wavefront.  `raw` holds its statuses, then its supports when they are 16-bit,
-// then its list.  The supports (32-bit) and positions in device memory lie in
-// the graph's own part of the head and record arrays.
+// wavefront.  Positions, and supports in device memory (32-bit), lie in the
+// graph's own part of the two phase lists.  A workgroup leaves a deep, narrow
+// remainder, its first list built, to own_finish (`end` kNarrow); returns the
+// passes.
 template <class Sup, class Item, bool kWaveGroup>
-__device__ __forceinline__ void own_watch(const OwnArgs& a, int gi, unsigned char* raw, int max_n,
-                                          int* cnt, OwnShared& sh, OwnTotals& t) {
-    const int vb = (int)a.vbase[gi], n = (int)a.vbase[gi + 1] - vb;
-    const CachedView g{a.row_off + vb, a.col, a.total_m};
+__device__ __forceinline__ int own_watch(const OwnArgs& a, int gi, unsigned char* raw, int max_n,
+                                         int* cnt, OwnShared& sh, OwnTotals& t, WatchEnd& end) {
+    const int n = (int)(a.vbase[gi + 1] - a.vbase[gi]);
+    const CachedView g = own_view(a, gi);
     uint32_t* bits = reinterpret_cast<uint32_t*>(raw);
     unsigned char* rest = raw + max_n / 8;
     Sup* sup;
@@ -355,15 +253,28 @@ __device__ __forceinline__ void own_watch(const OwnArgs& a, int gi, unsigned cha
         sup = reinterpret_cast<uint16_t*>(rest);
         rest += max_n * 2;
     } else {
-        sup = a.head + 2 * (long long)vb;
+        sup = reinterpret_cast<int*>(own_lists(a, gi).l1);
     }
     const uint64_t before = t.w.edges;
     Watch<CachedView, Sup, int, Item, kWaveGroup> w{
-        g, n, bits, sup, reinterpret_cast<int*>(a.rec + vb), reinterpret_cast<Item*>(rest), cnt,
+        g, n, bits, sup, reinterpret_cast<int*>(own_lists(a, gi).l0), reinterpret_cast<Item*>(rest), cnt,
         a.sched, t.w};
     w.init(nullptr);
     w.template sweep<false>((int*)nullptr);
-    w.passes(INT_MAX);
+    end = w.passes(INT_MAX, kWaveGroup         ? kNarrowLds
+                            : sizeof(Sup) == 2 ? narrow_limit(n)
+                                               : kNarrowMem);
+    if (__builtin_expect(end == kNarrow, 0)) {
+        using Lists = GroupLists<CachedView, kWaveGroup>;
+        Lists l{g, own_lists(a, gi), bits,
+                *reinterpret_cast<ListStage<Lists::kWaves>*>(own_stage<Sup>(raw, max_n)), a.sched,
+                t.w};
+        w.to_lists(l);
+        if constexpr (kWaveGroup)
+            w.steps += l.run(INT_MAX);
+        else
+            return w.steps;
+    }
     t.max_phases = w.steps > t.max_phases ? w.steps : t.max_phases;
     const int64_t wb = a.bitmap_base[gi], we = a.bitmap_base[gi + 1];
     const int nwords = (n + 31) >> 5;
@@ -376,6 +287,7 @@ __device__ __forceinline__ void own_watch(const OwnArgs& a, int gi, unsigned cha
                                       : block_sum(t.w.edges - before, sh.red);
     if (w.rank() == 0) a.graph_edges[gi] = edges;
     w.sync();
+    return w.steps;
 }
 
 // Graphs are claimed in order (largest first).  A workgroup trims the larger
@@ -401,12 +313,25 @@ __global__ __launch_bounds__(kOwnMaxBlock) void ac6_owned(OwnArgs a, int G, cons
             break;
         }
         const int64_t n = a.vbase[gi + 1] - a.vbase[gi];
-        if (watch_fits(n, (int)blockDim.x, kWatchLdsN))
-            own_watch<uint16_t, uint16_t, false>(a, gi, sh.raw, kWatchLdsN, sh.cnt[0], sh, t);
-        else if (n <= kWatchMaxN)
-            own_watch<int, uint32_t, false>(a, gi, sh.raw, kWatchMaxN, sh.cnt[0], sh, t);
-        else
-            own_graph(a, gi, sh, t);
+        const uint64_t before = t.w.edges;
+        WatchEnd end = kNarrow;
+        int passes = 0;
+        unsigned char* stage = sh.raw;
+        if (watch_fits(n, (int)blockDim.x, kWatchLdsN)) {
+            stage = own_stage<uint16_t>(sh.raw, kWatchLdsN);
+            passes = own_watch<uint16_t, uint16_t, false>(a, gi, sh.raw, kWatchLdsN, sh.cnt[0], sh,
+                                                          t, end);
+        } else if (n <= kWatchMaxN) {
+            stage = own_stage<int>(sh.raw, kWatchMaxN);
+            passes =
+                own_watch<int, uint32_t, false>(a, gi, sh.raw, kWatchMaxN, sh.cnt[0], sh, t, end);
+        }
+        if (__builtin_expect(end != kNarrow, 1)) continue;
+        const CachedView g = own_view(a, gi);
+        OwnLists l{g, own_lists(a, gi), n <= kWatchMaxN ? reinterpret_cast<uint32_t*>(sh.raw) : nullptr,
+                   *reinterpret_cast<ListStage<16>*>(stage), a.sched, t.w};
+        if (n > kWatchMaxN) own_graph(a, gi, l, t);
+        own_finish(a, gi, l, before, passes, sh, t);
     }
     // wavefront part: wavefront 0 takes the graph that ended the workgroup part
     __syncthreads();   // the workgroup's LDS is free for the wavefronts
@@ -418,8 +343,9 @@ __global__ __launch_bounds__(kOwnMaxBlock) void ac6_owned(OwnArgs a, int G, cons
             if (c >= G) break;
             gi = order[c];
         }
+        WatchEnd end;
         own_watch<uint16_t, uint16_t, true>(a, gi, sh.raw + wv * kOwnWaveLds, kOwnWaveN,
-                                            sh.cnt[wv], sh, t);
+                                            sh.cnt[wv], sh, t, end);
         gi = -1;
     }
     __syncthreads();

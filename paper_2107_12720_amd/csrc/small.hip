@@ -147,11 +147,11 @@ __global__ __launch_bounds__(kSmallBlock) void ac6_tiny(const int* row_off, cons
     a.template sweep<kForest>(keep);
     bool done = true;
     if (kForest) done = a.forest(keep, budget);
-    if (done) done = a.passes(budget);
+    if (done) done = a.passes(budget) == kDone;
     small_outputs(a, t, done, out, red);
 }
 
-// sup_g, cur: n ints each.  With kFront the status bits (`gbits`), the second
+// sup_g: n ints; the positions lie in m.l0.  With kFront the status bits (`gbits`), the second
 // bitmap (`gnone`), the links and the per-workgroup sums come from the two
 // front kernels.
 struct Front {
@@ -164,7 +164,7 @@ struct Front {
 
 template <class View, bool kForest, bool kFront>
 __global__ __launch_bounds__(kSmallBlock) void ac6_small(View g, int n, const uint32_t* preset,
-                                                         int* sup_g, int* cur, Front f,
+                                                         int* sup_g, ListArrays m, Front f,
                                                          SmallOut out, int sched, int budget) {
     __shared__ uint64_t table[StageSmall<View>::kWords];
     __shared__ __attribute__((aligned(16))) uint32_t bits[kWatchLdsN / 32];
@@ -176,7 +176,8 @@ __global__ __launch_bounds__(kSmallBlock) void ac6_small(View g, int n, const ui
     __shared__ SmallRed red;
     StageSmall<View>::apply(g, table);
     WatchTotals t;
-    Watch<View, uint16_t, int, uint16_t, false> a{g, n, bits, sup, cur, list, cnt, sched, t};
+    Watch<View, uint16_t, int, uint16_t, false> a{g, n, bits, sup, reinterpret_cast<int*>(m.l0),
+                                                  list, cnt, sched, t};
     if constexpr (kFront) {
         const int nwords = (n + 31) >> 5, tid = threadIdx.x;
         if (tid < kWatchCnt) cnt[tid] = 0;
@@ -217,7 +218,19 @@ __global__ __launch_bounds__(kSmallBlock) void ac6_small(View g, int n, const ui
     }
     bool done = true;
     if (kForest) done = a.forest(sup_g, budget);
-    if (done) done = a.passes(budget);
+    if (done) {
+        const WatchEnd end = a.passes(budget, kFront ? narrow_limit(n) : INT_MAX);
+        done = end != kStalled;
+        if constexpr (kFront) {
+            if (end == kNarrow) {
+                GroupLists<View, false> l{g, m, bits, *reinterpret_cast<ListStage<16>*>(sup), sched, t};
+                a.to_lists(l);
+                const int left = budget - a.steps - a.jumps, ph = l.run(left);
+                a.steps += ph;
+                done = ph < left;
+            }
+        }
+    }
     small_outputs(a, t, done, out, red);
 }
 
@@ -326,20 +339,21 @@ hipError_t ac6_small_csr(const trim_csr_t& g, const Work& w, const LaunchCfg& lc
         return hipGetLastError();
     }
     const CachedView v{g.row_off, g.col, (int)g.m};
-    int* sup = w.a;
-    int* cur = w.a + n;
+    // the lists' heads and records are made, if at all, when the rest is done with
+    const ListArrays m{w.a, w.b, w.e, w.e + n};
+    int* sup = reinterpret_cast<int*>(m.l1);
     if (n < kFrontN) {
         Timed t(lc, "ac6_small");
         if (lc.forest)
             hipLaunchKernelGGL((ac6_small<CachedView, true, false>), dim3(1), dim3(kSmallBlock), 0,
-                               st, v, n, preset, sup, cur, Front{}, out, lc.schedule, lc.budget);
+                               st, v, n, preset, sup, m, Front{}, out, lc.schedule, lc.budget);
         else
             hipLaunchKernelGGL((ac6_small<CachedView, false, false>), dim3(1), dim3(kSmallBlock),
-                               0, st, v, n, preset, sup, cur, Front{}, out, lc.schedule, lc.budget);
+                               0, st, v, n, preset, sup, m, Front{}, out, lc.schedule, lc.budget);
         return hipGetLastError();
     }
     uint32_t* bits = reinterpret_cast<uint32_t*>(w.c);
-    uint32_t* none = w.e;
+    uint32_t* none = bits + (n + 63) / 64 * 2;
     const int blocks = (n + kFrontBlock - 1) / kFrontBlock;
     {
         Timed t(lc, "ac6_init");
@@ -349,16 +363,16 @@ hipError_t ac6_small_csr(const trim_csr_t& g, const Work& w, const LaunchCfg& lc
     {
         Timed t(lc, "ac6_sweep");
         hipLaunchKernelGGL(small_sweep, dim3(blocks), dim3(kFrontBlock), 0, st, g.row_off, g.col,
-                           n, bits, sup, cur, w.jp, none, w.part);
+                           n, bits, sup, reinterpret_cast<int*>(m.l0), w.jp, none, w.part);
     }
     Timed t(lc, "ac6_small");
     const Front f{bits, none, w.jp, w.part, blocks};
     if (lc.forest)
         hipLaunchKernelGGL((ac6_small<CachedView, true, true>), dim3(1), dim3(kSmallBlock), 0, st,
-                           v, n, preset, sup, cur, f, out, lc.schedule, lc.budget);
+                           v, n, preset, sup, m, f, out, lc.schedule, lc.budget);
     else
         hipLaunchKernelGGL((ac6_small<CachedView, false, true>), dim3(1), dim3(kSmallBlock), 0, st,
-                           v, n, preset, sup, cur, f, out, lc.schedule, lc.budget);
+                           v, n, preset, sup, m, f, out, lc.schedule, lc.budget);
     return hipGetLastError();
 }
 
@@ -367,14 +381,15 @@ hipError_t ac6_small_implicit(const trim_implicit_t& g, const Work& w, const Lau
     const int n = 1 << g.log2n;
     const ImplicitView v{g.seed, g.zero_thr, g.deg_table, (uint32_t)(n - 1)};
     const SmallOut out{bitmap, worker_edges, lc.workers, stats, w.ctr};
+    const ListArrays m{w.a, w.b, w.e, w.e + n};
     Timed t(lc, "ac6_small");
     if (lc.forest)
         hipLaunchKernelGGL((ac6_small<ImplicitView, true, false>), dim3(1), dim3(kSmallBlock), 0,
-                           lc.stream, v, n, (const uint32_t*)nullptr, w.a, w.a + n, Front{}, out,
+                           lc.stream, v, n, (const uint32_t*)nullptr, w.a, m, Front{}, out,
                            lc.schedule, lc.budget);
     else
         hipLaunchKernelGGL((ac6_small<ImplicitView, false, false>), dim3(1), dim3(kSmallBlock), 0,
-                           lc.stream, v, n, (const uint32_t*)nullptr, w.a, w.a + n, Front{}, out,
+                           lc.stream, v, n, (const uint32_t*)nullptr, w.a, m, Front{}, out,
                            lc.schedule, lc.budget);
     return hipGetLastError();
 }

@@ -37,10 +37,15 @@
 //           sit in the supports' LDS array and are jumped in place until a
 //           round settles nothing more;
 //   passes  watch the supports and resume the scans of the vertices handed
-//           back, until a pass hands none back.
+//           back, until a pass hands none back, or many have handed back few:
+//   lists   every vertex left joins its support's list, and phases over the
+//           lists finish (group_lists.h).
 #pragma once
+#include <climits>
+
 #include "trim_device.h"
 #include "layout.h"
+#include "group_lists.h"
 
 namespace trim {
 
@@ -55,6 +60,20 @@ constexpr int kWatchSteps = 8;          // steps whose finds are listed in one g
 constexpr int kWatchList = 512;         // list entries of one wavefront
 static_assert(kWatchSlots * kWatchSteps == 64, "the finds of a lane are the bits of one word");
 constexpr int kWatchCnt = 4;            // LDS words of a group: flags, null vertex
+// A pass costs the same however few vertices it hands back: 3.5 us at 61,000
+// vertices, 2.1 at 20,000, 2.6 by one wavefront at 4,000, and 8 and 17 with the
+// supports of 100,000 and 300,000 in device memory; a phase over lists
+// (group_lists.h) takes about 1.8, after the vertices left were registered (0.2
+// ms at 61,000).  So a graph that had more than so many passes in which no
+// wavefront handed back more than kNarrowLanes vertices goes on with lists.
+// Paths v -> v + 1 with every edge twice, us: one of 61,000 vertices 203,000 ->
+// 108,000; in a batch one of 3,000 among 100,000 vertices 23,800 -> 6,130 (lists
+// from the start 5,680), of 1,000 among 500,000 27,200 -> 4,780 (4,890).
+constexpr int kNarrowLanes = 8;
+constexpr int kNarrowLds = 64, kNarrowMem = 24;   // supports in LDS, in device memory
+// The limit for a workgroup with supports in LDS; below 16,384 vertices its
+// passes cost no more than phases.
+__device__ __forceinline__ int narrow_limit(int n) { return n < 16384 ? INT_MAX : kNarrowLds; }
 
 // Graph views with plain loads: a small graph is read again from the caches.
 struct CachedView {
@@ -116,11 +135,7 @@ __device__ __forceinline__ bool wt_bit(const uint32_t* bits, int v) {
 // a wavefront's accesses in order).
 __device__ __forceinline__ void wt_order() { asm volatile("" ::: "memory"); }
 
-// Per-lane totals of the graphs trimmed so far.
-struct WatchTotals {
-    uint64_t edges = 0, sweep = 0, deg = 0;
-    uint32_t closes = 0, joins = 0, visited = 0, forest = 0, live = 0;
-};
+enum WatchEnd { kStalled, kDone, kNarrow };
 
 // One graph: vertices 0 .. n - 1 of the view g, targets in the same numbering.
 //   Sup   uint16_t: supports in LDS; int: in device memory
@@ -496,12 +511,13 @@ struct Watch {
         return any;
     }
 
-    // Passes until one hands no vertex back.  False when they and the forest
-    // rounds would exceed `budget`.  At the end the null vertex's bit is set
-    // again.
-    __device__ __forceinline__ bool passes(int budget) {
+    // Passes until one hands no vertex back (kDone), until they and the forest
+    // rounds would exceed `budget` (kStalled), or until more than `narrow_limit`
+    // were narrow (kNarrow: go on by to_lists).  At the end the null vertex's bit
+    // is set again.
+    __device__ __forceinline__ WatchEnd passes(int budget, int narrow_limit = INT_MAX) {
         const int null = null_vertex();
-        if (null < 0) return true;   // nothing was removed before the sweep, nothing ever is
+        if (null < 0) return kDone;   // nothing was removed before the sweep, nothing ever is
         if (rank() < 3) cnt[rank()] = 0;
         if (rank() == 0) bits[null >> 5] &= ~(1u << (null & 31));
         const int waves = size() / kWave;
@@ -510,24 +526,94 @@ struct Watch {
             for (int v = n + rank(); v < watch_padded(n, size()); v += size()) wt_set(sup, v, null);
         sync();
         Item* mine = list + wave * kWatchList;
-        bool done = true;
+        WatchEnd end = kDone;
+        int narrow = 0;
         for (;; ++steps) {
+            const uint32_t before = t.visited;
             const bool any = watch(mine, wave, waves, null);
-            // flags rotate over three words, as the forest's
+            // flags rotate over three words, as the forest's; bit 1: many finds
             int* flag = cnt + steps % 3;
-            if (any && lane_id() == 0) atomicOr(flag, 1);
+            if (any) {
+                const int wide = popc(ballot(t.visited != before)) > kNarrowLanes ? 2 : 0;
+                if (lane_id() == 0) atomicOr(flag, 1 | wide);
+            }
             sync_lds();
             const int more = __hip_atomic_load(flag, __ATOMIC_RELAXED, kWatchWG);
             if (rank() == 0) cnt[(steps + 2) % 3] = 0;
             if (!more) break;   // the same in every lane of the group
             if (steps + jumps >= budget) {
-                done = false;
+                end = kStalled;
+                break;
+            }
+            narrow += more == 1;
+            if (__builtin_expect(narrow > narrow_limit, 0)) {
+                end = kNarrow;
+                ++steps;
                 break;
             }
         }
         if (rank() == 0) bits[null >> 5] |= 1u << (null & 31);
         sync();
-        return done;
+        return end;
+    }
+
+    // Every vertex left joins the list of its support (a plain exchange: nothing
+    // is closed meanwhile); those whose support is removed resume their scans in
+    // the first phase.  The positions may lie in m.l0, supports that are not in
+    // LDS in m.l1; l.st is LDS that nothing uses by then (the supports' own place,
+    // if they are there).
+    __device__ __forceinline__ void to_lists(GroupLists<View, kWaveGroup>& l) {
+        constexpr int U = 4;
+        const ListArrays& m = l.m;
+        const int rounds = (n + size() - 1) / size();
+        uint32_t* lost = reinterpret_cast<uint32_t*>(list);   // a bitmap, as in the sweep
+        for (int i = 0; i < rounds; ++i) {
+            const int v = i * size() + rank();
+            if (v >= n) break;
+            const int h = wt_bit(bits, v) ? kDead : kEmpty;
+            reinterpret_cast<int2*>(m.head)[v] = make_int2(h, h);
+        }
+        sync();
+        for (int i = 0; i < rounds; i += U) {
+            int v[U], s[U], p[U], e[U], old[U];
+            bool live[U], gone[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                v[k] = (i + k) * size() + rank();
+                const int x = min(v[k], n - 1);
+                live[k] = v[k] < n && !wt_bit(bits, x);
+                s[k] = wt_get(sup, x);
+                p[k] = wt_get(cur, x);
+                e[k] = g.end(x);
+            }
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                gone[k] = live[k] && wt_bit(bits, s[k]);
+                old[k] = kEmpty;
+                if (live[k] && !gone[k])
+                    old[k] = xchg_s<kWG>(m.head + 2 * s[k] + (p[k] + 1 == e[k]), v[k]);
+            }
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                if (live[k]) st_s<kWG>(m.rec + v[k], pack_rec(old[k], p[k]));
+                const uint64_t b = ballot(gone[k]);
+                if (lane_id() == 0 && v[k] < n) {
+                    lost[v[k] >> 5] = (uint32_t)b;
+                    lost[(v[k] >> 5) + 1] = (uint32_t)(b >> 32);
+                }
+            }
+        }
+        sync();   // supports and positions are not read any more
+        l.begin();
+        sync();
+        for (int i = 0; i < rounds; ++i) {
+            const int v = i * size() + rank();
+            const bool back = v < n && wt_bit(lost, v);
+            t.visited += back;
+            l.emit(back ? make_item(kOwnRescan, v) : kNone);
+        }
+        l.flush();
+        sync();
     }
 };
 

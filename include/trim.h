@@ -183,9 +183,10 @@ typedef struct {
  * implicit ones up to 2^15 vertices and of batches finds the vertices whose
  * support was removed by watching their statuses instead of by walks over the
  * supports' lists.  What a deep graph has left after many such passes goes on
- * over lists: a large one after 64 rounds, fewer above 2^21 vertices; one that a
- * workgroup or a wavefront trims after 24 or 64 passes that handed back few
- * vertices, except below 16,384 vertices by a workgroup.  The successor checks
+ * over lists: a large one after 64 rounds, fewer above 2^21 vertices, or after 8
+ * that removed few vertices; one that a workgroup or a wavefront trims after 24
+ * or 64 passes that handed back few vertices, except below 16,384 vertices by a
+ * workgroup.  The successor checks
  * are the same; a vertex that finds its support removed counts in `visited`, one
  * that finds another in `joins`, one that finds none in `closes`; `phases` counts
  * the passes over the vertices and the phases over lists.

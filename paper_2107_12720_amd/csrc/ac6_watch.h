@@ -23,7 +23,8 @@
 //                 scans.  round_launches(n) launches; a round that removes
 //                 nothing is the last, and what follows returns at once;
 //   watch_tail    further rounds in one launch with grid barriers, up to
-//                 watch_rounds(n) rounds in all; then the list heads;
+//                 watch_rounds(n) rounds in all or kNarrowRounds narrow ones;
+//                 then the list heads;
 //   watch_register
 //                 if that did not end it (a deep, narrow remainder): every
 //                 vertex left joins its support's list, and the propagation
@@ -444,14 +445,16 @@ __global__ __launch_bounds__(kRoundThreads) void watch_tail(WatchState a, int r0
     __shared__ uint64_t red[16];
     if (ld_dev(a.ctr + kHyStop)) return;
     WatchSums t;
-    int r = r0;
+    int r = r0, narrow = 0;   // the same in every workgroup
     for (;; ++r) {
         const int before = removed_before(a, r);
         if (before == 0) {
             if (blockIdx.x == 0 && threadIdx.x == 0) st_dev(a.ctr + kHyStop, 1);
             break;
         }
-        if (r > last) {   // the lists' heads; nothing reads the filters there any more
+        narrow += before <= narrow_removals(a.n);
+        if (r > last || narrow > kNarrowRounds) {
+            // the lists' heads; nothing reads the filters there any more
             for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < a.n;
                  v += gridDim.x * blockDim.x) {
                 const int h = (ld_dev(a.dead + (v >> 5)) >> (v & 31)) & 1u ? kDead : kEmpty;

@@ -26,12 +26,21 @@ constexpr int kWatchRounds = 64;
 // takes 6 to 9 us up to 2^20 vertices and 19 at 2^22, a phase over lists 5 (one
 // removal) to 60 (thousands), registering 50 and 170.  Core+tail graphs of mean
 // degree 30 and 2^20 vertices (some 60 rounds) take 2.4 ms with 64 rounds, with
-// lists alone 3.8 (a limit of 40 cost 0.5 more).  66 rounds of one removal each,
-// the worst case, take 0.68 ms, with lists alone 0.46.
+// lists alone 3.8 (a limit of 40 cost 0.5 more).  Rounds that remove few end
+// sooner: kNarrowRounds.
 constexpr int watch_rounds(int n) {
     const int r = n <= (1 << 21) ? kWatchRounds : (int)(((long long)kWatchRounds << 21) / n);
     return r > 8 ? r : 8;
 }
+// Rounds of the tail that removed so few vertices that a phase over lists would
+// have taken them sooner, of which so many register the rest: a round costs the
+// same whatever it removes.  One path of 66 levels (every edge twice) among 2^17
+// vertices 437 -> 328 us a call (lists from the start 353), 2^20 685 -> 498 (458),
+// 2^22 1,225 -> 1,061 (907); five of them 454 -> 455 (518), 687 -> 547 (653), 1,259
+// -> 1,107 (1,101).  With 12 rounds 2 to 3 % more, with 32 removals at 2^17 vertices
+// uniform graphs of mean degree 1.1 lose 5 %, with 64 at 2^22 50 paths 3 %.
+constexpr int kNarrowRounds = 8;
+constexpr int narrow_removals(int n) { return n >> 17 > 1 ? n >> 17 : 1; }
 constexpr int kSweepFlight = 8;         // vertices per lane in flight
 constexpr int kRoundFlight = 8;
 constexpr int kRoundThreads = 512;      // the tail: one workgroup per CU

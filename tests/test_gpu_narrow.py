@@ -1,6 +1,7 @@
-"""Deep, narrow graphs in one workgroup (csrc/watch.h): many passes that hand back
-few vertices, then support lists (csrc/group_lists.h), as one graph and in
-batches, in each form of the supports, against the oracle."""
+"""Deep, narrow graphs: many passes in one workgroup (csrc/watch.h) or many rounds
+over the device (csrc/watch_rounds.h) that hand back few vertices, then support
+lists, as one graph and in batches, in each form of the supports, against the
+oracle."""
 import numpy as np
 import pytest
 
@@ -109,3 +110,34 @@ def test_watchdog_in_the_lists(ctx):
     ctx.trim_csr(6, g.n, *dev, opts=T.make_opts(budget=PASSES + 200))
     assert ctx.status() == -6
     check_all(ctx, g, algos=(6,), name="after a stall")
+
+
+ROUNDS = 8   # narrow rounds of the device-wide tail
+
+
+@pytest.mark.parametrize("n,width,depths", [(70_001, 1, (3, ROUNDS - 1, ROUNDS, ROUNDS + 1,
+                                                         ROUNDS + 2, ROUNDS + 3, 40)),
+                                            (300_007, 2, (ROUNDS + 1, ROUNDS + 3, ROUNDS + 5, 60)),
+                                            (300_007, 3, (30,)), (1 << 20, 8, (ROUNDS + 6, 30)),
+                                            (1 << 20, 9, (30,))])
+def test_device_wide_rounds(ctx, n, width, depths):
+    """Narrow rounds over the whole device, around their limit, with the first of
+    them in launches of their own; one-sided, with late registration and presets."""
+    import torch
+    import paper_2107_12720_amd as T
+    for depth in depths:
+        g = deep(n, depth, width, n + depth, 500)
+        say(f"  n={n}: {width} x {depth}")
+        r, _ = check_all(ctx, g, algos=(6,), name="deep")
+        ro, col = T.to_device(g.row_off), T.to_device(g.col)
+        res = ctx.trim_csr(6, n, ro, col, opts=T.make_opts(rounds=4))
+        torch.cuda.synchronize()
+        st = res.stats_dict()
+        assert np.array_equal(res.bitmap_numpy()[:(n + 31) // 32], oracle.bitmap(r.live))
+        assert (st["edges_total"], st["rounds"], st["rechecks"]) == oracle.counts_deferred(g, r, 4)
+        preset, pbm = gg.sample_vertices(n, 0.97, seed=depth)
+        rp = oracle.peel(g, preset=preset)
+        res = ctx.trim_csr_preset(6, n, ro, col, T.to_device(pbm.view(np.int32)))
+        torch.cuda.synchronize()
+        assert np.array_equal(res.bitmap_numpy()[:(n + 31) // 32], oracle.bitmap(rp.live))
+        assert int(res.worker_edges.sum()) == oracle.counts(g, rp, preset=preset).T6

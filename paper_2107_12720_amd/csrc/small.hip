@@ -305,15 +305,21 @@ int small_block(int n) {
 
 }  // namespace
 
-// Where the line lies, one workgroup against the device-wide rounds, us a call:
-// core+tail of 17,000 vertices 125 / 195, 32,768 173 / 242, 50,000 257 / 254,
-// 65,536 312 / 257; R-MAT of edge factor 16 and 32,768 29 / 44, 65,536 47 / 46, of
-// 4 51 / 48, with a chain 76 / 80; uniform of mean degree 2 and 50,000 90 / 100,
-// 65,536 104 / 102, of 1.1 334 / 443, of 16 30 / 37.  The edge limit keeps graphs
-// of long lists away, whose scans one compute unit runs slowly: tails of 30
-// successors a vertex, nearly all of them removed, take 908 / 1,358 with 17,000
-// vertices, 2,302 / 1,430 with 50,000.
-constexpr long long kSmallMaxN = 61440;
+// Where the line lies: depth and list lengths divide one workgroup from the
+// device-wide rounds, which the sizes do not tell, so it lies where neither is the
+// faster over all kinds.  Twelve kinds of graph (core+tail of mean degree 6.5, 8 and
+// 15, uniform of 1.1 to 16, R-MAT with and without a chain), device-wide over one
+// workgroup, geometric mean (least, largest): 36,000 vertices 1.30 (0.87, 1.60),
+// 50,000 1.06 (0.62, 1.47), 54,000 1.05 (0.60, 1.41), 58,000 0.99 (0.55, 1.46),
+// 65,536 0.91 (0.56, 1.26).  A pass goes in batches of 8,192 supports; seven are
+// below the crossing, the eighth starts there.  us, one workgroup / device-wide, at
+// 54,000 and 65,536: core+tail 265 / 243 and 308 / 249, with lists of 15 857 / 511 and
+// 999 / 556, uniform of 1.1 221 / 302 and 334 / 422, of 16 28 / 39 and 31 / 38, R-MAT
+// of edge factor 16 43 / 50 and 47 / 50.  The edge limit keeps graphs of long lists
+// away, whose scans one compute unit runs slowly: tails of 30 successors a vertex,
+// nearly all of them removed, take 908 / 1,358 with 17,000 vertices, 2,302 / 1,430
+// with 50,000.
+constexpr long long kSmallMaxN = 7 * 8192;
 static_assert(kSmallMaxN <= kWatchLdsN, "the LDS holds the supports");
 bool ac6_small_ok(long long n, long long m, int rounds) {
     return rounds < 2 && n <= kSmallMaxN && m <= kSmallMaxM;

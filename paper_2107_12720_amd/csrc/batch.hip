@@ -261,9 +261,9 @@ __device__ __forceinline__ int own_watch(const OwnArgs& a, int gi, unsigned char
         a.sched, t.w};
     w.init(nullptr);
     w.template sweep<false>((int*)nullptr);
-    end = w.passes(INT_MAX, kWaveGroup         ? kNarrowLds
-                            : sizeof(Sup) == 2 ? narrow_limit(n)
-                                               : kNarrowMem);
+    end = w.template passes<true>(INT_MAX, kWaveGroup         ? kNarrowLds
+                                           : sizeof(Sup) == 2 ? narrow_limit(n)
+                                                              : kNarrowMem);
     if (__builtin_expect(end == kNarrow, 0)) {
         using Lists = GroupLists<CachedView, kWaveGroup>;
         Lists l{g, own_lists(a, gi), bits,

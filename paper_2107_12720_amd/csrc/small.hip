@@ -219,7 +219,7 @@ __global__ __launch_bounds__(kSmallBlock) void ac6_small(View g, int n, const ui
     bool done = true;
     if (kForest) done = a.forest(sup_g, budget);
     if (done) {
-        const WatchEnd end = a.passes(budget, kFront ? narrow_limit(n) : INT_MAX);
+        const WatchEnd end = a.template passes<kFront>(budget, narrow_limit(n));
         done = end != kStalled;
         if constexpr (kFront) {
             if (end == kNarrow) {

@@ -513,8 +513,9 @@ struct Watch {
 
     // Passes until one hands no vertex back (kDone), until they and the forest
     // rounds would exceed `budget` (kStalled), or until more than `narrow_limit`
-    // were narrow (kNarrow: go on by to_lists).  At the end the null vertex's bit
+    // were narrow (kNarrow, with kCounted: go on by to_lists).  At the end the null vertex's bit
     // is set again.
+    template <bool kCounted = false>
     __device__ __forceinline__ WatchEnd passes(int budget, int narrow_limit = INT_MAX) {
         const int null = null_vertex();
         if (null < 0) return kDone;   // nothing was removed before the sweep, nothing ever is
@@ -534,8 +535,9 @@ struct Watch {
             // flags rotate over three words, as the forest's; bit 1: many finds
             int* flag = cnt + steps % 3;
             if (any) {
-                const int wide = popc(ballot(t.visited != before)) > kNarrowLanes ? 2 : 0;
-                if (lane_id() == 0) atomicOr(flag, 1 | wide);
+                int bits_found = 1;
+                if (kCounted && popc(ballot(t.visited != before)) > kNarrowLanes) bits_found = 3;
+                if (lane_id() == 0) atomicOr(flag, bits_found);
             }
             sync_lds();
             const int more = __hip_atomic_load(flag, __ATOMIC_RELAXED, kWatchWG);
@@ -546,7 +548,7 @@ struct Watch {
                 break;
             }
             narrow += more == 1;
-            if (__builtin_expect(narrow > narrow_limit, 0)) {
+            if (kCounted && __builtin_expect(narrow > narrow_limit, 0)) {
                 end = kNarrow;
                 ++steps;
                 break;

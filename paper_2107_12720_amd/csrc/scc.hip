@@ -153,14 +153,14 @@ __global__ void scc_pivot(int n, const int* row_off, const int* rrow_off, const 
 __device__ __forceinline__ uint32_t ritem(int dir, int v) { return ((uint32_t)dir << 30) | (uint32_t)v; }
 
 // The pivot, marked and placed in the frontier in both directions (one
-// thread; misc[kSccFront] = 2).
+// thread; misc[kSccNext] = 2).
 __global__ void scc_seed_pivot(unsigned long long* misc, int* flags, uint32_t* front) {
     if (threadIdx.x == 0) {
         const int v = (int)(misc[kSccPivot] & 0xFFFFFFFFull);
         flags[v] = 3;
         front[0] = ritem(0, v);
         front[1] = ritem(1, v);
-        misc[kSccFront] = 2;
+        misc[kSccNext] = 2;
     }
 }
 
@@ -209,14 +209,14 @@ __device__ __forceinline__ void append_item(bool has, uint32_t it, uint32_t* out
 }
 
 // Roots (unassigned v with colour v): marked backward, placed in the frontier
-// backward (misc[kSccFront] zeroed before).
+// backward (misc[kSccNext] zeroed before).
 __global__ void scc_seed_roots(int n, const uint32_t* live, const int* color, int* flags,
                                uint32_t* front, unsigned long long* misc) {
     for (int base = blockIdx.x * blockDim.x; base < n; base += gridDim.x * blockDim.x) {
         const int v = base + threadIdx.x;
         const bool root = v < n && has_bit(live, v) && color[v] == v;
         if (root) flags[v] = 2;
-        append_item(root, ritem(1, v), front, misc + kSccFront);
+        append_item(root, ritem(1, v), front, misc + kSccNext);
     }
 }
 
@@ -246,7 +246,7 @@ __global__ __launch_bounds__(256) void scc_scan_chunks(const uint32_t* front, co
                                                        uint32_t* bsum,
                                                        const unsigned long long* misc) {
     __shared__ uint32_t s_w[256 / kWave];
-    const long long F = (long long)misc[kSccFront];
+    const long long F = (long long)misc[kSccNext];
     const long long chunks = (F + kScanChunk - 1) / kScanChunk;
     for (long long c = blockIdx.x; c < chunks; c += gridDim.x) {
         const long long i0 = c * kScanChunk + threadIdx.x * 4;
@@ -279,11 +279,12 @@ __global__ __launch_bounds__(256) void scc_scan_chunks(const uint32_t* front, co
 
 // Step 2 (one block): exclusive scan of the chunk sums, and the frontier's
 // total entries into misc[kSccTotal].  From `pull` entries on the level is
-// scc_pull's.
+// scc_pull's.  The items that the level before counted in misc[kSccNext] become
+// this level's frontier, misc[kSccFront].
 __global__ void scc_scan_sums(uint32_t* bsum, unsigned long long* misc, unsigned long long pull) {
     __shared__ uint32_t s_w[16];
     __shared__ uint32_t s_carry;
-    const long long F = (long long)misc[kSccFront];
+    const long long F = (long long)misc[kSccNext];
     const long long chunks = (F + kScanChunk - 1) / kScanChunk;
     if (threadIdx.x == 0) s_carry = 0;
     __syncthreads();
@@ -307,7 +308,9 @@ __global__ void scc_scan_sums(uint32_t* bsum, unsigned long long* misc, unsigned
     if (threadIdx.x == 0) {
         misc[kSccTotal] = s_carry;
         if (s_carry < pull) misc[kSccEdges] += s_carry;
+        misc[kSccFront] = (unsigned long long)F;
         misc[kSccNext] = 0;
+        misc[kSccLevels] += 1;
     }
 }
 
@@ -572,14 +575,6 @@ __global__ void scc_live_from_preset(int n, const uint32_t* preset, uint32_t* li
     }
 }
 
-// After a level: the next frontier becomes the current one.
-__global__ void scc_level_done(unsigned long long* misc) {
-    if (threadIdx.x == 0) {
-        misc[kSccFront] = misc[kSccNext];
-        misc[kSccLevels] += 1;
-    }
-}
-
 // Unassigned vertices with the wanted marks join a component: mode 0 (both
 // marks) gets the pivot's id, mode 1 (backward mark) the colour (its root).
 // One wavefront per 64 consecutive vertices, so each assigned word has one
@@ -645,7 +640,7 @@ hipError_t scc_run(const trim_csr_t& g, const Work& w, const Work2& x, const Scc
     auto reset = [&](int mask) {
         hipLaunchKernelGGL(scc_reset, dim3(1), dim3(256), 0, st, s.misc, mask, w.ctr);
     };
-    // level-synchronous search from the items in front[0] (misc[kSccFront] of
+    // level-synchronous search from the items in front[0] (misc[kSccNext] of
     // them); ends when a level takes nothing
     auto search = [&](const int* color) -> hipError_t {
         const int ge = lc.cus * 8;
@@ -669,11 +664,10 @@ hipError_t scc_run(const trim_csr_t& g, const Work& w, const Work2& x, const Scc
                 hipLaunchKernelGGL(scc_pull, dim3(gv), dim3(256), 0, st, n, g.row_off, g.col,
                                    g.rrow_off, g.rcol, s.live, s.flags, s.front[cur ^ 1], s.misc,
                                    pull);
-            hipLaunchKernelGGL(scc_level_done, dim3(1), dim3(64), 0, st, s.misc);
             hipError_t r = hipGetLastError();
             if (r == hipSuccess) r = read_misc();
             if (r != hipSuccess) return r;
-            if (host[kSccFront] == 0) break;
+            if (host[kSccNext] == 0) break;
         }
         return hipSuccess;
     };
@@ -759,7 +753,7 @@ hipError_t scc_run(const trim_csr_t& g, const Work& w, const Work2& x, const Scc
             counts->color_sweeps += 1;
             if (host[kSccChanged] == 0) break;
         }
-        reset((1 << kSccTaken) | (1 << kSccFront));
+        reset((1 << kSccTaken) | (1 << kSccNext));
         hipLaunchKernelGGL(scc_seed_roots, dim3(gv), dim3(256), 0, st, n, s.live, s.color, s.flags,
                            s.front[0], s.misc);
         if ((e = search(s.color)) != hipSuccess) return e;

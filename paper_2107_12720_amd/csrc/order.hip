@@ -184,11 +184,15 @@ constexpr int kBinPer = 32;                 // targets per thread of a tile
 constexpr int kBinTile = kBinThreads * kBinPer;
 constexpr int kBinSlices = 1024;
 constexpr long long kBinChunk = 1 << 21;    // targets one workgroup counts at most
-// Fewer edges (in one bin, in several): the plain counters.  Scores of R-MAT
-// graphs, plain / binned, us: 30,000 vertices of edge factor 4 36 / 37, 16 79 / 47;
-// 60,000 of 4 54 / 76, 8 82 / 81, 16 123 / 89; 2^18 of 4 168 / 101.
+// Fewer edges (in one bin, in several): the plain counters.  One bin, scores of
+// R-MAT graphs of 30,000 vertices, plain / binned, us: edge factor 4 36 / 37, 16
+// 79 / 47.  Several bins take 60 to 68 us up to 2 * 10^6 edges, trim_mlp_prepare
+// plain / binned: 40,000 vertices, 560,000 edges 56 / 68, 640,000 62 / 67; 60,000,
+// 600,000 59 / 65, 720,000 67 / 66; 90,000, 540,000 53 / 64, 720,000 63 / 63; 140,000,
+// 560,000 57 / 62, 840,000 72 / 61; 260,000, 520,000 71 / 70.  (Just above one bin
+// they meet sooner: 33,000 vertices, 400,000 edges 69 / 68.)
 constexpr long long kBinMinM = 1 << 16;
-constexpr long long kBinsMinM = 1 << 19;
+constexpr long long kBinsMinM = 11 << 16;
 constexpr int kBinCountThreads = 1024;
 static_assert(kBinMax == 2 * kBinThreads && kBinMax == kBinCountThreads, "scans of the bins' totals");
 

@@ -7,7 +7,8 @@ graph resident in HBM.  The value is input edges per second (m / step time).
 The live bitmap and the traversed-edge total are checked against the CPU
 oracle in the same run.
 
-Also reported on the same JSON line:
+Also measured (kernel tables and counts go to stderr, after "details", the rest on
+the JSON line):
   roofline      the dominant kernel's algorithmic bytes / its average event-timed
                 duration, against the 8 TB/s HBM peak (plus HBM traffic measured by
                 rocprofv3 counters when a summary for the current kernel source is
@@ -46,6 +47,7 @@ INT32_VALU_PEAK_OPS = 256 * 64 * 2.4e9
 KERNEL_SOURCES = ("paper_2107_12720_amd/csrc/ac6.hip", "paper_2107_12720_amd/csrc/ac6_support.h",
                   "paper_2107_12720_amd/csrc/ac6_watch.h",
                   "paper_2107_12720_amd/csrc/watch_rounds.h",
+                  "paper_2107_12720_amd/csrc/layout.h",
                   "paper_2107_12720_amd/csrc/forest_jump.h",
                   "paper_2107_12720_amd/csrc/trim_device.h",
                   "paper_2107_12720_amd/csrc/trim_stats.h",
@@ -54,6 +56,26 @@ KERNEL_SOURCES = ("paper_2107_12720_amd/csrc/ac6.hip", "paper_2107_12720_amd/csr
 
 def log(*a):
     print(*a, file=sys.stderr, flush=True)
+
+
+# What the printed line leaves to the details on stderr: with everything it is
+# 31 KB long, and readers of the end of the output miss its beginning.
+DETAILS = {"kernels", "kernels_ms", "kernels_us", "stats", "by_rounds", "breakdown", "step_stats",
+           "edges_total", "max_worker", "traversed", "sweep_roofline"}
+
+
+def short_line(x, top=True, sampling=False):
+    """The result without per-kernel tables and counts, numbers to six digits
+    (the top level's exact); of the sampling sweeps the times only."""
+    if isinstance(x, dict):
+        if sampling and "ms" in x:
+            return short_line(x["ms"], False)
+        return {k: v if top and isinstance(v, float) else
+                short_line(v, False, sampling or k == "sampling")
+                for k, v in x.items() if k not in DETAILS}
+    if isinstance(x, list):
+        return [short_line(v, False, sampling) for v in x]
+    return float(f"{x:.6g}") if isinstance(x, float) else x
 
 
 def source_hash():
@@ -1349,7 +1371,8 @@ def main():
     if not args.no_cpu:
         oracle_leg(g, checks, args.cpu_seconds, out)
         log(f"oracle leg: parity={out['parity']}")
-    print(json.dumps(out), flush=True)
+    log("details " + json.dumps(out))
+    print(json.dumps(short_line(out)), flush=True)
     ctx.close()
 
 

@@ -112,8 +112,9 @@ typedef struct {
                            pseudo-random pauses inside the race windows (join versus
                            close, AC-4 decrements).  Results never depend on them. */
     int32_t budget;     /* watchdog: loop iterations a wavefront of a persistent kernel
-                           (AC-6 and AC-4 propagation) may make, and polls a workgroup may
-                           spend waiting at an AC-3 round barrier, before the call is
+                           (AC-6 and AC-4 propagation) may make, passes over its vertices
+                           where one workgroup trims a graph, and polls a workgroup may
+                           spend waiting at a round barrier, before the call is
                            abandoned: every wavefront then exits normally, the outputs
                            are invalid and trim_ctx_status() returns TRIM_E_STALLED.
                            0 = TRIM_DEFAULT_BUDGET (a run that legitimately needs more
@@ -371,7 +372,10 @@ typedef struct {
     int32_t color_rounds;  /* colouring rounds after the forward-backward search */
     int32_t color_sweeps;  /* max-label sweeps over all colouring rounds */
     int32_t search_levels; /* frontier levels of all searches */
-    int64_t search_edges;  /* list entries examined by the forward and backward searches */
+    int64_t search_edges;  /* list entries examined by the forward and backward searches; a
+                              level that holds a quarter of all edges is searched from the
+                              unreached vertices, which stop at the first reached neighbour,
+                              so the number depends on the schedule then */
     int64_t search_ors;    /* mark fetch-ors the searches issued (a measure of contention:
                               at most 2 per vertex win) */
     double trim_ms;        /* host-timed phases: trimming passes, */
@@ -458,8 +462,9 @@ int trim_batch(trim_ctx *ctx, int32_t G, const int64_t *vbase, const int32_t *ro
 /*
  * For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, hosts that forbid hipMalloc): AC-6 on an
- * explicit graph exactly as trim_csr with TRIM_AC6, with no context and no
- * allocation of any kind.  The working memory is a fixed array inside the
+ * explicit graph with the results of trim_csr with TRIM_AC6, with no context and
+ * no allocation of any kind (above 57,344 vertices or 2^21 edges over support
+ * lists, which its array has room for, so slower than trim_csr).  The working memory is a fixed array inside the
  * library, one copy per GPU (about 69 MB, held until the process ends), on
  * the calling thread's current device.  The caller passes inputs and outputs
  * as for trim_csr; worker_edges needs opts.workers entries, or

@@ -567,9 +567,9 @@ inline int grid_for(long long n, int block, int max_blocks = 1 << 20) {
 
 namespace {
 
-// Smaller graphs keep the lists (two launches fewer): core+tail of 4,096 vertices
-// 246 us by lists, 141 by rounds, but uniform of 4,096 164 / 173 and R-MAT 12 71 /
-// 75.  The filters need room in the heads.
+// Smaller graphs keep the lists (two launches fewer).  Lists / rounds, us: core+tail
+// of 4,096 vertices 234 / 136, uniform of 4,096 163 / 167, of 10,000 157 / 147, R-MAT
+// 12 of edge factor 4 and 16 73 / 70 and 72 / 69.  The filters need room in the heads.
 static_assert(2 * kTwoWatchMinN >= 3LL << (WatchFilter::log_for(kTwoWatchMinN) - 5), "filters fit");
 
 hipError_t two_watch_run(const TwoGraph& g, long long m, int n, const Work& w, const Work2& x,

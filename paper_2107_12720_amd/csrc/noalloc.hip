@@ -1,7 +1,9 @@
 // noalloc.hip -- trim_csr_noalloc: AC-6 trimming of an explicit graph whose
 // working memory is a fixed device array of this library, for callers that
 // cannot allocate (code under HIP graph capture, tight serving loops, hosts
-// that forbid hipMalloc).  The kernels are those of trim_csr with AC-6.
+// that forbid hipMalloc).  Graphs that trim_csr gives to one workgroup
+// (small.hip) take the same kernels here; larger ones the list kernels of ac6.hip,
+// since the array has no place for the supports that trim_csr watches instead.
 //
 // The array, `scratch`, is a file-scope __device__ variable: every GPU the
 // library runs on holds its own copy, at its own address, until the process

@@ -168,9 +168,9 @@ __device__ __forceinline__ void first_step(const int* at, int stride, int nb, in
 // pieces of `piece` entries (vertex, number of the piece) for ac4_long, which
 // spreads them over the device: walked here, the hubs of an R-MAT graph, its low
 // ids, met in few wavefronts (R-MAT 20 of edge factor 16 with 30 % of the vertices
-// kept: 3,608 us here, 148 + 1,463 with ac4_long, 2,771 through the queue).  (Two-sided, a vertex removed from the start has
-// one list at most.)  Steps go to the workgroups by step_of: in turn 340 us on
-// R-MAT 24, so 296.
+// kept: 3,608 us here, 148 + 1,463 with ac4_long, 2,771 through the queue).
+// (Two-sided, a vertex removed from the start has one list at most.)  Steps go to
+// the workgroups by step_of: in turn 340 us on R-MAT 24, so 296.
 constexpr int kLongBuf = 128;   // pieces a wavefront buffers
 
 template <bool kTwo>

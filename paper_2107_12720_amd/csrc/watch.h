@@ -60,14 +60,15 @@ constexpr int kWatchSteps = 8;          // steps whose finds are listed in one g
 constexpr int kWatchList = 512;         // list entries of one wavefront
 static_assert(kWatchSlots * kWatchSteps == 64, "the finds of a lane are the bits of one word");
 constexpr int kWatchCnt = 4;            // LDS words of a group: flags, null vertex
-// A pass costs the same however few vertices it hands back: 3.5 us at 61,000
+// A pass costs the same however few vertices it hands back: 3.4 us at 56,000
 // vertices, 2.1 at 20,000, 2.6 by one wavefront at 4,000, and 8 and 17 with the
 // supports of 100,000 and 300,000 in device memory; a phase over lists
 // (group_lists.h) takes about 1.8, after the vertices left were registered (0.2
-// ms at 61,000).  So a graph that had more than so many passes in which no
+// ms at 56,000).  So a graph that had more than so many passes in which no
 // wavefront handed back more than kNarrowLanes vertices goes on with lists.
-// Paths v -> v + 1 with every edge twice, us: one of 61,000 vertices 203,000 ->
-// 108,000; in a batch one of 3,000 among 100,000 vertices 23,800 -> 6,130 (lists
+// Paths v -> v + 1 with every edge twice, us: one of 56,000 vertices 188,700 ->
+// 101,800 (device-wide lists 175,900), of 66 levels among them 387 -> 386 (341); in
+// a batch one of 3,000 among 100,000 vertices 23,800 -> 6,130 (lists
 // from the start 5,680), of 1,000 among 500,000 27,200 -> 4,780 (4,890).
 constexpr int kNarrowLanes = 8;
 constexpr int kNarrowLds = 64, kNarrowMem = 24;   // supports in LDS, in device memory

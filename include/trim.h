@@ -464,15 +464,15 @@ int trim_batch(trim_ctx *ctx, int32_t G, const int64_t *vbase, const int32_t *ro
  * capture, tight serving loops, hosts that forbid hipMalloc): AC-6 on an
  * explicit graph with the results of trim_csr with TRIM_AC6, with no context and
  * no allocation of any kind (above 57,344 vertices or 2^21 edges over support
- * lists, which its array has room for, so slower than trim_csr).  The working memory is a fixed array inside the
- * library, one copy per GPU (about 69 MB, held until the process ends), on
- * the calling thread's current device.  The caller passes inputs and outputs
+ * lists, which its array has room for, so slower than trim_csr).  The working
+ * memory is a fixed array inside the library, one copy per GPU (about 69 MB, held
+ * until the process ends), on the calling thread's current device.  The caller passes inputs and outputs
  * as for trim_csr; worker_edges needs opts.workers entries, or
  * TRIM_NOALLOC_WORKERS when opts.workers is 0.  g->rrow_off / g->rcol are
  * ignored.  TRIM_E_INVAL for n > TRIM_NOALLOC_MAX_N, opts.workers >
  * TRIM_NOALLOC_WORKERS, opts.graph != 0 or opts.rounds > 1 (late support
- * registration needs a round list it would have to allocate).  Every call on one GPU shares that
- * GPU's array: calls that overlap on one GPU (two streams, two threads) race
+ * registration needs working memory that this array lacks).  Every call on one
+ * GPU shares that GPU's array: calls that overlap on one GPU (two streams, two threads) race
  * and must be serialised by the caller.  The watchdog (opts.budget) works as
  * for trim_csr; a stall shows in stats.stalled (no context to query).
  */
